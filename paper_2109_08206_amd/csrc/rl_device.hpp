@@ -241,7 +241,10 @@ __device__ __forceinline__ Decision decide_from(const DecideIn &in, long long k,
     }
     double al = in.aprev;
     if (sy > 0.0) {
-        al = ((k - 1) % 2 == 0) ? ss / sy : sy / yy;
+        // one division: the step rule is on every kernel's critical path
+        const bool bb1 = ((k - 1) & 1) == 0;
+        const double num = bb1 ? ss : sy, den = bb1 ? sy : yy;
+        al = num / den;
         al = al < in.amin ? in.amin : (al > in.amax ? in.amax : al);
     }
     d.alpha = al;

@@ -267,6 +267,11 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
                   const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
                   double *gamma, SolveArgs *a, bool trusted = false);
 int apply_impl(rl_ctx *h, SolveArgs &a, double *w);
+// small problems: the whole loop in one workgroup (rl_solo.hip), iterations
+// k0 .. kend - 1 of a prepared solve that solo_takes
+constexpr int kSoloSlots = 3072;  // constraint slots of its largest form (48 bytes of LDS each)
+bool solo_takes(int64_t n, int64_t nc);
+hipError_t launch_solo(hipStream_t st, const SolveArgs &a, long long k0, long long kend);
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
                const int *perm = nullptr);
 // xu (may be null): unwrapped centres, += h U_t without wrapping

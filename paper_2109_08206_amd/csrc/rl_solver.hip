@@ -723,6 +723,16 @@ static hipError_t launch_velocity(hipStream_t st, const SolveArgs &a, bool uni, 
     return hipGetLastError();
 }
 
+// The solves that one workgroup takes (rl_solo.hip).  Sampled timing of the
+// loop kernels needs the loop kernels.
+static bool solo_fits(const rl_ctx *h, const SolveArgs &a)
+{
+    return solo_takes(a.n, a.nc) && (h->prof_every == 0 || h->arena_on);
+}
+
+// iterations of one launch of it (under 20 ms)
+constexpr long long kSoloChunk = 2048;
+
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
                const int *perm)
 {
@@ -744,6 +754,22 @@ int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamm
                                (const double2 *)a.st, gamma_out);
             RL_HIP(hipGetLastError());
         }
+    } else if (a.nc > 0 && solo_fits(h, a)) {
+        // one workgroup runs the whole solve; a long one is cut into launches
+        // so that each ends soon, and whatever reads the result is queued
+        // behind the launch that is expected to be the last
+        for (long long k0 = 0;; k0 += kSoloChunk) {
+            RL_HIP(launch_solo(st, a, k0, k0 + kSoloChunk));
+            RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
+            if (gamma_out) RL_HIP(launch_unpack_gamma(st, a, gamma_out));
+            if (U && a.n > 0) {
+                RL_HIP(launch_velocity(st, a, uni, F, perm, U));
+                vel_queued = true;
+            }
+            RL_HIP(hipStreamSynchronize(st));
+            if (h->state_host->done) break;
+        }
+        iters = h->state_host->iter;
     } else if (a.nc > 0) {
         RL_HIP(launch_rod<kModeInit>(st, a, uni, 0));
         RL_HIP(launch_con<kModeInit>(st, a, 0));

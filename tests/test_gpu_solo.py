@@ -1,0 +1,103 @@
+"""The one-workgroup solve at the edges of its forms: constraint counts
+around the slots of each form, rod counts around the threads, one, two and
+four lanes per rod, lists longer than the records a rod holds, contact-only
+and general sets, and solves longer than one launch.  Bars as for every
+solve: the answer certified by the oracle's operator (residual <= 1e-8), the
+velocities within 1e-6 of the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+import rodsynth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _t(a, dtype=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=dtype, device="cuda")
+
+
+def _problem(n, nc, lengths):
+    """n rods and nc of their near pairs (a sorted random choice)."""
+    s = rodsynth.make_system(n, seed=n + nc, phi=max(1.3 * nc / (156.0 * n), 0.004),
+                             length=(0.5, 1.5) if lengths else 1.0)
+    d = oracle.directors(s.quat)
+    L = s.length if lengths else 1.0
+    pr = oracle.pairs(s.x, d, L, s.box, s.diam, s.cutoff)
+    assert pr.n >= nc
+    pick = np.sort(np.random.default_rng(nc).choice(pr.n, nc, replace=False))
+    pr = oracle.Pairs(pr.pi[pick].copy(), pr.pj[pick].copy(), pr.img[pick].copy(), pr.flags[pick].copy())
+    return s, d, L, pr, oracle.assemble(s.x, d, L, s.box, s.diam, s.eta, s.dt, pr, s.force)
+
+
+# around 1,024, 2,048 and 3,072 slots and 512, 1,024 and 2,048 rods; (60, 900)
+# and (200, 1600) have lists far longer than a rod holds
+EDGES = [(30, 1, False), (64, 65, True), (129, 300, False), (512, 1023, True), (513, 1023, False),
+         (300, 1024, False), (1024, 2047, False), (1025, 700, True), (700, 2048, False), (2048, 3071, True),
+         (2049, 3071, False), (900, 3072, True), (60, 450, False), (200, 1600, False)]
+
+
+@pytest.mark.parametrize("n,nc,lengths", EDGES)
+def test_solve_at_the_edges(gpu_lib, n, nc, lengths):
+    s, d, L, pr, cs = _problem(n, nc, lengths)
+    ref = oracle.bbpgd(d, L, s.diam, s.eta, pr, cs, tol=1e-8)
+    assert ref.status == oracle.OK
+    Uref = oracle.velocity(d, L, s.diam, s.eta, pr, cs, ref.gamma, s.force)
+    with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-8) as slv:
+        g, U, info = slv.solve_lcp(_t(d), _t(L) if lengths else L, _t(pr.pi, torch.int32), _t(pr.pj, torch.int32),
+                                   _t(cs.e), _t(cs.arm), _t(cs.q), F=_t(s.force))
+    g, U = g.cpu().numpy(), U.cpu().numpy()
+    assert info.status == gpu_lib.OK and info.residual <= 1e-8
+    w = oracle.apply_Mc(d, L, s.diam, s.eta, pr, cs, g)
+    cert = np.abs(np.minimum(g, w)).max()
+    assert g.min() >= 0 and cert <= 1e-8 * 1.01
+    assert info.residual == pytest.approx(cert, abs=1e-11 * np.abs(cs.q).max())
+    assert np.linalg.norm(U - Uref) <= 1e-6 * np.linalg.norm(Uref)
+
+
+@pytest.mark.parametrize("n,nc,lengths", [(40, 60, False), (512, 1023, False), (1000, 2047, True), (2048, 3071, False)])
+def test_general_solve_at_the_edges(gpu_lib, n, nc, lengths):
+    s, d, L, pr, cs = _problem(n, nc, lengths)
+    rng = np.random.default_rng(n)
+    kind = (rng.random(nc) < 0.2).astype(np.uint8)          # Hookean rows
+    cmp = np.where(kind == 1, rng.uniform(20.0, 60.0, nc), 0.0)
+    pj = pr.pj.copy()
+    pj[rng.random(nc) < 0.1] = -1                           # against a fixed body
+    order = rng.permutation(nc)
+    gc = oracle.General(pr.pi[order].copy(), pj[order].copy(), cs.e[order].copy(), cs.arm[order].copy(),
+                        cs.q[order].copy(), kind[order].copy(), cmp[order].copy())
+    ref = oracle.bbpgd_gen(d, L, s.diam, s.eta, gc, tol=1e-8)
+    assert ref.status == oracle.OK
+    Uref = oracle.velocity_gen(d, L, s.diam, s.eta, gc, ref.gamma, s.force)
+    with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-8) as slv:
+        g, U, info = slv.solve_general(_t(d), _t(L) if lengths else L, _t(gc.pi, torch.int32),
+                                       _t(gc.pj, torch.int32), _t(gc.e), _t(gc.arm), _t(gc.q),
+                                       _t(gc.kind, torch.uint8), _t(gc.cmp), F=_t(s.force))
+    g, U = g.cpu().numpy(), U.cpu().numpy()
+    assert info.status == gpu_lib.OK and info.residual <= 1e-8
+    w = oracle.apply_Mc_gen(d, L, s.diam, s.eta, gc, g)
+    r = np.where(gc.kind == 1, np.abs(w), np.abs(np.minimum(g, w)))
+    assert g[gc.kind == 0].min() >= 0 and r.max() <= 1e-8 * 1.01
+    assert np.linalg.norm(U - Uref) <= 1e-6 * np.linalg.norm(Uref)
+
+
+def test_solve_over_several_launches(gpu_lib):
+    """A dense system that needs thousands of iterations (20,683 for the
+    oracle): the iteration cap holds exactly on both sides of a launch's end,
+    and the solution is certified."""
+    s = rodsynth.make_system(300, seed=3, phi=0.05)
+    d = oracle.directors(s.quat)
+    pr = oracle.pairs(s.x, d, 1.0, s.box, s.diam, s.cutoff)
+    cs = oracle.assemble(s.x, d, 1.0, s.box, s.diam, s.eta, s.dt, pr, s.force)
+    args = (_t(d), 1.0, _t(pr.pi, torch.int32), _t(pr.pj, torch.int32), _t(cs.e), _t(cs.arm), _t(cs.q))
+    for cap in (1, 2047, 2048, 2049, 4097):
+        with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=0.0,
+                            max_iter=cap) as slv:
+            _, _, info = slv.solve_lcp(*args)
+        assert info.status == gpu_lib.NOT_CONVERGED and info.iterations == cap
+    with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-8) as slv:
+        g, _, info = slv.solve_lcp(*args)
+    assert info.status == gpu_lib.OK
+    w = oracle.apply_Mc(d, 1.0, s.diam, s.eta, pr, cs, g.cpu().numpy())
+    assert np.abs(np.minimum(g.cpu().numpy(), w)).max() <= 1e-8 * 1.01

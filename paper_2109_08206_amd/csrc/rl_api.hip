@@ -266,6 +266,7 @@ static int step_general(rl_ctx *h, int64_t n, double *x, double *quat, const dou
     const int *ord = nullptr;
     rc = prepare_general(h, n, ds, lsv, len0, nc, cpi, cpj, ce, carm, cq, ckind, ccmp, cgam, true, &a, &ord);
     if (rc) return rc;
+    a.ordered = true;
     rc = solve_impl(h, a, F, Uw, nullptr, info, perm);
     if (rc < 0) return rc;
     // the forces back in input order: contacts, links, walls
@@ -343,6 +344,7 @@ int rl_create(rl_handle *out, const rl_params *prm)
         set_error("rl_create: no HIP device");
         return RL_ERR_HIP;
     }
+    if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) h->cus = 0;
     if (hipMalloc(&h->state, sizeof(SolverState)) != hipSuccess ||
         hipMalloc(&h->flag_dev, sizeof(int) * 4) != hipSuccess ||
         hipHostMalloc(&h->state_host, sizeof(SolverState), hipHostMallocDefault) != hipSuccess ||
@@ -613,6 +615,7 @@ int rl_step(rl_handle h, int64_t n, double *x, double *quat, const double *len, 
     SolveArgs a;
     rc = prepare_solve(h, n, ds, lsv, len0, np, pi, pj, e, arm, q, gamma, &a, true);
     if (rc) return rc;
+    a.ordered = true;
     rc = solve_impl(h, a, F, Uw, tape_mode != RL_TAPE_NONE && np > 0 ? gamma_tape : gamma, info, perm);
     if (rc < 0) return rc;
     // gamma (or the tape) holds the forces in the step's constraint order
@@ -717,6 +720,7 @@ int rl_step_adjoint(rl_handle h, int64_t n, const double *x, const double *quat,
     SolveArgs a;
     rc = prepare_solve(h, n, ds, lsv, len0, np, pi, pj, e, arm, q, gamma, &a, true);
     if (rc) return rc;
+    a.ordered = true;
     rl_solve_info si{0, 0.0, 0.0, RL_OK, 0};
     const int src = solve_impl(h, a, F, Uc, nullptr, &si, perm);
     if (src < 0) return src;

@@ -226,27 +226,21 @@ __device__ __forceinline__ Decision decide_from(const DecideIn &in, long long k,
 {
     Decision d{0.0, 0, RL_OK};
     const double ss = t[0], sy = t[1], yy = t[2], res = t[3];
-    if (!isfinite(ss) || !isfinite(sy) || !isfinite(yy) || !isfinite(res)) {
+    // one test for the common case (a finite number times zero is zero,
+    // anything else is NaN)
+    const bool finite = fma(ss, 0.0, fma(sy, 0.0, fma(yy, 0.0, res * 0.0))) == 0.0;
+    if (__builtin_expect(!finite || res <= in.tol || ss == 0.0 || k >= in.max_iter, 0)) {
         d.stop = 1;
-        d.status = RL_ERR_NONFINITE;
-    } else if (res <= in.tol) {
-        d.stop = 1;
-        d.status = RL_OK;
-    } else if (ss == 0.0) {
-        d.stop = 1;
-        d.status = RL_STAGNATED;
-    } else if (k >= in.max_iter) {
-        d.stop = 1;
-        d.status = RL_NOT_CONVERGED;
+        d.status = !finite ? RL_ERR_NONFINITE
+                           : (res <= in.tol ? RL_OK : (ss == 0.0 ? RL_STAGNATED : RL_NOT_CONVERGED));
     }
-    double al = in.aprev;
-    if (sy > 0.0) {
-        // one division: the step rule is on every kernel's critical path
-        const bool bb1 = ((k - 1) & 1) == 0;
-        const double num = bb1 ? ss : sy, den = bb1 ? sy : yy;
-        al = num / den;
-        al = al < in.amin ? in.amin : (al > in.amax ? in.amax : al);
-    }
+    // one division and no branch: the step rule is on every iteration's
+    // critical path
+    const bool bb1 = ((k - 1) & 1) == 0;
+    const double num = bb1 ? ss : sy, den = bb1 ? sy : yy;
+    double al = num / den;
+    al = al < in.amin ? in.amin : (al > in.amax ? in.amax : al);
+    al = sy > 0.0 ? al : in.aprev;
     d.alpha = al;
     return d;
 }

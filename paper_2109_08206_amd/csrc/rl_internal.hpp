@@ -46,7 +46,7 @@ struct SolverState {
     double inner_tol, rho64;
     long long refreshes;
     int refresh;  // set by the rod kernel when the inner round ends
-    int pad;
+    int fail;     // solves on chip: 1 a wait ran out, 2 the problem does not fit
 };
 
 // Per-rod mobility: a_par, a_perp (translation along / normal to the axis),
@@ -121,6 +121,7 @@ struct SolveArgs {
     const float4 *qgeo32;   // [nc] Q-side list order: (ex, ey, ez, s_j)
     float *uP32;            // [nc] contact velocities of the correction, P side
     float *uQ32;            // [nc] the same, Q side in list order
+    bool ordered;           // rods numbered along the cells of the pair search
     // general constraint sets (bilateral links, fixed bodies): constraints
     // sorted by (pi, kind), Q lists by (kind, index)
     bool gen;               // the set holds bilateral or one-sided constraints
@@ -160,6 +161,14 @@ struct rl_ctx {
     rl_params prm;
     hipStream_t stream = nullptr;
     int device = 0;
+    int cus = 0;  // compute units
+    // exchange words of the solves on chip: what of the buffer holds no
+    // number above `xchg_num` (0: nothing yet), and solves left to the two
+    // kernels after one that did not fit or gave up waiting
+    void *xchg_buf = nullptr;
+    size_t xchg_cap = 0;
+    unsigned xchg_num = 0;
+    int xchg_skip = 0;
     // grow-only workspace slots
     static constexpr int kSlots = 128;
     void *buf[kSlots] = {};
@@ -212,7 +221,7 @@ enum Slot : int {
     kWsGenPsplit, kWsGenQsplit, kWsLinkLen, kWsLinkFlags, kWsInvPerm, kWsWallCnt, kWsWallOff,
     kWsCatPi, kWsCatPj, kWsCatE, kWsCatArm, kWsCatQ, kWsCatKind, kWsCatCmp, kWsCatLen, kWsStepUnc,
     kWsFtot, kWsWarmKeys, kWsWarmGam, kWsWarmKeysNew, kWsWarmGamNew, kWsStress,
-    kWsKmcCount, kWsKmcFlag, kWsKmcOff, kWsKmcKey, kWsKmcKeyOut, kWsKmcPerm,
+    kWsXchg, kWsKmcCount, kWsKmcFlag, kWsKmcOff, kWsKmcKey, kWsKmcKeyOut, kWsKmcPerm,
     kWsCount  // number of slots; must not exceed rl_ctx::kSlots
 };
 static_assert(kWsCount <= rl_ctx::kSlots, "workspace slot table too small");
@@ -267,11 +276,20 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
                   const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
                   double *gamma, SolveArgs *a, bool trusted = false);
 int apply_impl(rl_ctx *h, SolveArgs &a, double *w);
-// small problems: the whole loop in one workgroup (rl_solo.hip), iterations
-// k0 .. kend - 1 of a prepared solve that solo_takes
-constexpr int kSoloSlots = 3072;  // constraint slots of its largest form (48 bytes of LDS each)
-bool solo_takes(int64_t n, int64_t nc);
-hipError_t launch_solo(hipStream_t st, const SolveArgs &a, long long k0, long long kend);
+// Solves that stay on chip (rl_resident.hip): which form takes a problem, the
+// exchange words it needs between workgroups, and its launch over iterations
+// k0 .. kend - 1 of a prepared solve.  ordered: neighbouring rods have
+// neighbouring numbers.
+struct ResPlan {
+    int form, groups, ln;  // groups = 0: none takes it
+};
+constexpr int kResSolo = 1536;  // constraints up to which one workgroup is as fast as several
+constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64 are needed
+ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered);
+bool resident_larger(ResPlan &p);
+int64_t resident_words(const ResPlan &p, int64_t nc);
+hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, unsigned long long *words,
+                           unsigned base, long long k0, long long kend);
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
                const int *perm = nullptr);
 // xu (may be null): unwrapped centres, += h U_t without wrapping

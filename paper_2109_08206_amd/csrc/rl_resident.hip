@@ -1,0 +1,907 @@
+// BBPGD with the whole problem on chip: one launch runs the start phases,
+// every iteration and the stop, in one workgroup (small problems) or in up to
+// one per compute unit that exchange what crosses between them.
+//
+// The two-kernel loop costs about 8 us per iteration in launches whatever the
+// size, and beyond that streams 188 bytes per constraint and iteration.  Here
+// a workgroup owns a contiguous range of rods and keeps, for the whole solve,
+// the iterate of its constraints in registers (thread t: slots t, t + T, ...:
+// gamma, g, q) and the records of its rods in its threads' registers and LDS.
+// Nothing is read from or written to memory per iteration but the exchange.
+//
+// One product: the slots' gamma' goes to LDS, the rods sum their records,
+// apply the mobility and leave the contact velocities of their records in
+// LDS, and the slots read w = u_P - u_Q back (three workgroup barriers per
+// iteration with the one of the dot products).
+//
+// Across workgroups: a constraint belongs to the workgroup of its P rod.  One
+// whose Q rod lives elsewhere has a second slot there that follows the same
+// iterate bit for bit, so only the two contact velocities travel, and then
+// the four sums of every workgroup, which all of them add in the same order.
+// Both exchanges are 64-bit words of 32 data bits and a 32-bit sequence
+// number, written and polled with relaxed device-scope accesses: a word is
+// its own flag, so there is no barrier, no fence (an L2 write-back on this
+// part) and no clearing between iterations.  A workgroup sends its sums after
+// it has read the velocities of the same product and writes the next
+// velocities after it has read everybody's sums, so no word is overwritten
+// unread; the sums alternate between two buffers for the same reason.  A round
+// of the sums takes 1.05 us between up to 64 workgroups and 1.4 us between
+// 128, with velocities in front of it 1.9 and 2.5 us; a grid
+// barrier with device-scope fences took 17 us and more.  Every wait is
+// bounded: past the bound (or where the problem turns out not to fit) all
+// workgroups leave without a result, and the caller runs the two kernels.
+//
+// What bounds it: the exchanges, and the instruction issue of a compute unit
+// and the dependent chain between the barriers, not memory.  Hence few waves
+// (every wave runs the reduction and the step rule itself: at 1,024 threads
+// these took 3,400 clocks of an iteration whatever the size), and rods dealt
+// to the threads in descending order of their number of records (a wave takes
+// as long as its longest list, and a random 64 rods nearly always hold one
+// two or three times the average).
+#include <algorithm>
+#include <cmath>
+
+#include "rl_device.hpp"
+
+namespace rl {
+
+typedef unsigned long long u64;
+
+// Where the workgroups of one solve meet.  Words carry (data << 32 | number).
+struct Exchange {
+    u64 *u;         // [2][workgroups][NC] low and high halves of the velocities a workgroup
+                    // sends, in its own order (consecutive lanes, consecutive words)
+    u64 *at;        // [nc][2] where in it u_P and -u_Q of a constraint are found
+    u64 *tot;       // [2][2][kResMost][kSlot] the four sums, by parity of the number: of
+                    // the workgroups, and of the groups of kTeam workgroups
+    unsigned base;  // numbers base + 1, ... belong to this launch
+    int *fail;      // set when a wait ran out (1) or the problem does not fit (2)
+};
+
+constexpr int kResMost = 256;  // workgroups of a solve
+constexpr int kSlot = 32;      // words from one workgroup's sums to the next (256 bytes)
+// Above 64 workgroups their sums meet in two steps, teams of 16 and then the
+// teams: every workgroup polling 128 or 256 others takes 1.4 or 2.2 us, the
+// two steps 1.65 us for either.
+constexpr int kTeam = 16, kFlat = 64;
+
+// polls of one word before the wait is given up (about 0.3 s)
+constexpr int kSpin = 1 << 18;
+
+__device__ __forceinline__ void word_put(u64 *p, u64 v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ u64 word_get(const u64 *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ u64 half_word(int half, unsigned num) { return ((u64)(unsigned)half << 32) | num; }
+
+__device__ __forceinline__ void pair_put(u64 *p, double v, unsigned num)
+{
+    word_put(p, half_word(__double2loint(v), num));
+    word_put(p + 1, half_word(__double2hiint(v), num));
+}
+
+__device__ __forceinline__ double pair_value(u64 lo, u64 hi)
+{
+    return __hiloint2double((int)(hi >> 32), (int)(lo >> 32));
+}
+
+// whether poll number `spin` was one too many, or somebody else gave up
+__device__ __forceinline__ bool give_up(int spin, int *fail, int *bad)
+{
+    if (spin < kSpin && ((spin & 1023) != 1023 ||
+                         __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
+        return false;
+    __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *bad = 1;
+    return true;
+}
+
+// the two words of a number, polled until both carry `num`
+__device__ __forceinline__ double pair_wait(const u64 *p, unsigned num, int *fail, int *bad)
+{
+    for (int spin = 0;; ++spin) {
+        const u64 lo = word_get(p), hi = word_get(p + 1);
+        if (((unsigned)lo == num && (unsigned)hi == num) || give_up(spin, fail, bad)) return pair_value(lo, hi);
+    }
+}
+
+// The second half of it: lane l of every wave holds a part of number l & 3.
+template <int NW>
+__device__ __forceinline__ void res_sum4_lanes(double c, double p[4], double (*red)[4 * NW])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    c += dpp_f64<0x124>(c);  // row_ror:4
+    c += dpp_f64<0x128>(c);  // row_ror:8
+    if ((lane & 12) == 0) red[lane & 3][4 * wave + (lane >> 4)] = c;
+    __syncthreads();
+    // every row of lanes: lane 4 g + i sums NW row sums of number i
+    const double2 *s = reinterpret_cast<const double2 *>(&red[lane & 3][NW * ((lane >> 2) & 3)]);
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW / 2; ++k) {
+        const double2 x = s[k];
+        v += x.x + x.y;
+    }
+    v += dpp_f64<0x124>(v);
+    v += dpp_f64<0x128>(v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = lane_f64(v, i);
+}
+
+// Sums of four numbers over a workgroup of NW waves, the same bits in every
+// thread.  Two exchanges inside each quad leave lane i with the quad's sum of
+// number i, two rotations add the quads of a row, and the row sums (red[i]
+// holds 4 NW of them for number i) meet in LDS.  One barrier: the caller has
+// another one, or another red, between two of these.
+template <int NW>
+__device__ __forceinline__ void res_sum4(double p[4], double (*red)[4 * NW])
+{
+    const int lane = threadIdx.x & 63;
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const double a = (b0 ? p[1] : p[0]) + dpp_f64<0xb1>(b0 ? p[0] : p[1]);
+    const double b = (b0 ? p[3] : p[2]) + dpp_f64<0xb1>(b0 ? p[2] : p[3]);
+    double c = (b1 ? b : a) + dpp_f64<0x4e>(b1 ? a : b);
+    res_sum4_lanes<NW>(c, p, red);
+}
+
+// largest value over the workgroup (only where a stop reports its residual)
+template <int NW>
+__device__ __forceinline__ double res_max(double v, double *red)
+{
+    v = wave_total<true>(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) v = fmax(v, red[w]);
+    return v;
+}
+
+// A lane's share of one rod: records sub, sub + ln, ... of its P list
+// followed by its Q list.  The first R are held: the arclength s, the slot,
+// and with HELD the normal, its sign turned on the Q side so that both sides
+// add.  Longer lists look the rest up.
+template <int R, bool HELD>
+struct ResRod {
+    int rod, pb, np, qb, cnt;
+    int wmax;  // longest list of the wave, at most R
+    double d[3], s[R], e[HELD ? R : 1][3], mob[HELD ? 3 : 1];
+    int c[R];
+};
+
+constexpr int kGroup = 4;  // records handled together; R is a multiple
+
+struct ResLds {
+    const double *ex, *ey, *ez;    // the normals by slot
+    const double *sP, *sQ;         // with HELD: arclengths by slot (P side) and Q-list position
+    const unsigned short *qslot;   // slots of the Q lists
+    const double *G;               // what the product takes, by slot
+    double *U;                     // u of the P side, then -u of the Q side, NC each, by slot
+    int c0, q0;                    // the workgroup's first constraint and Q-list position
+};
+
+// record t of a rod's list: slot, arclength and side
+template <int R, bool HELD>
+__device__ __forceinline__ bool res_record(const SolveArgs &a, const ResLds &l, const ResRod<R, HELD> &r, int t,
+                                           int &c, double &s)
+{
+    const bool pside = t < r.np;
+    const int k = pside ? r.pb + t : r.qb + t - r.np;
+    c = pside ? k - l.c0 : (int)l.qslot[k - l.q0];
+    if (HELD) s = pside ? l.sP[k - l.c0] : l.sQ[k - l.q0];
+    else s = (pside ? a.geo : a.qgeo)[4 * (int64_t)k + 3];
+    return pside;
+}
+
+template <int NC, int R, bool HELD>
+__device__ __forceinline__ void res_rod_setup(const SolveArgs &a, const ResLds &l, int rod, int sub, int ln,
+                                              ResRod<R, HELD> &r)
+{
+    r.rod = rod < 0 ? 0 : rod;
+    r.pb = r.np = r.qb = r.cnt = 0;
+    r.d[0] = r.d[1] = r.d[2] = 0.0;
+    if (rod >= 0) {
+        r.pb = a.pptr[rod];
+        r.np = a.pptr[rod + 1] - r.pb;
+        r.qb = a.qptr[rod];
+        const int tot = r.np + a.qptr[rod + 1] - r.qb;
+        r.cnt = tot > sub ? (tot - sub + ln - 1) / ln : 0;
+        for (int d = 0; d < 3; ++d) r.d[d] = a.dir[3 * (int64_t)rod + d];
+    }
+    if (HELD) rod_mob(a, r.rod, a.coef == nullptr, r.mob[0], r.mob[HELD ? 1 : 0], r.mob[HELD ? 2 : 0]);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        r.c[i] = NC - 1;  // past the list: the zero slot
+        r.s[i] = 0.0;
+        bool pside = true;
+        if (i < r.cnt) pside = res_record(a, l, r, sub + i * ln, r.c[i], r.s[i]);
+        if (HELD) {
+            const double e[3] = {l.ex[r.c[i]], l.ey[r.c[i]], l.ez[r.c[i]]};
+            for (int d = 0; d < 3; ++d) r.e[i][d] = pside ? e[d] : -e[d];
+        }
+    }
+    int m = min(r.cnt, R);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) m = max(m, __shfl_xor(m, o, 64));
+    r.wmax = __builtin_amdgcn_readfirstlane(m);
+}
+
+// D v summed over the rod's records, the mobility, and u of every record
+template <int NC, int R, bool HELD>
+__device__ __forceinline__ void res_rod(const SolveArgs &a, const ResLds &l, int sub, int ln,
+                                        const ResRod<R, HELD> &r)
+{
+    if (r.wmax == 0) return;  // none in the wave
+    double f[3] = {0.0, 0.0, 0.0}, m[3] = {0.0, 0.0, 0.0};
+    auto add = [&](double v, double s, const double e[3]) {
+        const double vs = v * s;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            f[d] += v * e[d];
+            m[d] += vs * e[d];
+        }
+    };
+    auto normal = [&](int c, bool pside, double e[3]) {
+        e[0] = l.ex[c];
+        e[1] = l.ey[c];
+        e[2] = l.ez[c];
+        for (int d = 0; d < 3; ++d) e[d] = pside ? e[d] : -e[d];
+    };
+    // records past the held ones, looked up kTail at a time
+    constexpr int kTail = 4;
+    auto tail = [&](int i, auto &&use) {
+        int c[kTail];
+        double s[kTail];
+        bool pside[kTail];
+#pragma unroll
+        for (int k = 0; k < kTail; ++k)
+            pside[k] = res_record(a, l, r, sub + min(i + k, r.cnt - 1) * ln, c[k], s[k]);
+#pragma unroll
+        for (int k = 0; k < kTail; ++k)
+            if (i + k < r.cnt) use(c[k], pside[k], s[k]);
+    };
+    double apar = r.mob[0], aperp = r.mob[HELD ? 1 : 0], rperp = r.mob[HELD ? 2 : 0];
+    if (!HELD) rod_mob(a, r.rod, a.coef == nullptr, apar, aperp, rperp);
+    // kGroup records at a time without a branch between them: their loads go
+    // out together and their chains overlap (past the list: the zero slot)
+#pragma unroll
+    for (int b = 0; b < R; b += kGroup)
+        if (b < r.wmax) {
+            double gv[kGroup], e[kGroup][3];
+#pragma unroll
+            for (int i = 0; i < kGroup; ++i) {
+                gv[i] = l.G[r.c[b + i]];
+                if (!HELD) normal(r.c[b + i], sub + (b + i) * ln < r.np, e[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < kGroup; ++i) add(gv[i], r.s[b + i], HELD ? r.e[b + i] : e[i]);
+        }
+    for (int i = R; i < r.cnt; i += kTail)
+        tail(i, [&](int c, bool pside, double s) {
+            double e[3];
+            normal(c, pside, e);
+            add(l.G[c], s, e);
+        });
+    if (ln >= 2) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            f[d] += dpp_f64<0xb1>(f[d]);
+            m[d] += dpp_f64<0xb1>(m[d]);
+        }
+    }
+    if (ln >= 4) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            f[d] += dpp_f64<0x4e>(f[d]);
+            m[d] += dpp_f64<0x4e>(m[d]);
+        }
+    }
+    const double fd = (apar - aperp) * (r.d[0] * f[0] + r.d[1] * f[1] + r.d[2] * f[2]);
+    const double md = r.d[0] * m[0] + r.d[1] * m[1] + r.d[2] * m[2];
+    double V[3], W[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        V[d] = aperp * f[d] + fd * r.d[d];
+        W[d] = rperp * (m[d] - md * r.d[d]);
+    }
+    auto along = [&](double s, const double e[3]) {
+        return e[0] * (V[0] + s * W[0]) + e[1] * (V[1] + s * W[1]) + e[2] * (V[2] + s * W[2]);
+    };
+    // the normals come from LDS again: kept from the sums they would spill
+    if (!HELD) __asm__ volatile("" ::: "memory");
+#pragma unroll
+    for (int b = 0; b < R; b += kGroup)
+        if (b < r.wmax) {
+            double e[kGroup][3];
+            int at[kGroup];
+#pragma unroll
+            for (int i = 0; i < kGroup; ++i) {
+                // past the list: +-0 on the P side of the zero slot, which nobody reads
+                const int k = b + i;
+                const bool pside = sub + k * ln < r.np || k >= r.cnt;
+                at[i] = pside ? r.c[k] : NC + r.c[k];
+                if (!HELD) normal(r.c[k], pside, e[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < kGroup; ++i) l.U[at[i]] = along(r.s[b + i], HELD ? r.e[b + i] : e[i]);
+        }
+    for (int i = R; i < r.cnt; i += kTail)
+        tail(i, [&](int c, bool pside, double s) {
+            double e[3];
+            normal(c, pside, e);
+            l.U[pside ? c : NC + c] = along(s, e);
+        });
+}
+
+// First rod r with pptr[r] + qptr[r] + 2 r >= target (W(0) = 0, W(n) the
+// total), by a wave: 64 probes a round.
+__device__ __forceinline__ int res_boundary(const SolveArgs &a, int n, int64_t target)
+{
+    const int lane = threadIdx.x & 63;
+    int lo = 0, hi = n;  // W(hi) >= target; everything before lo is below it
+    while (lo < hi) {
+        const int step = (hi - lo + 63) / 64;
+        const int r = min(lo + lane * step, hi);
+        const bool ge = (int64_t)a.pptr[r] + a.qptr[r] + 2 * (int64_t)r >= target;
+        const unsigned long long m = __ballot(ge);
+        if (m == 0) {
+            lo = min(lo + 63 * step + 1, hi);
+            continue;
+        }
+        const int f = __ffsll(m) - 1;
+        const int rf = min(lo + f * step, hi);
+        lo = f == 0 ? lo : lo + (f - 1) * step + 1;
+        hi = rf;
+        if (f == 0) lo = hi;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// T threads; NC slots, the last one a zero that no constraint takes; J = NC /
+// T slots per thread; K rods per thread (1 or 2); HELD: the rods hold the
+// normals of their records in registers; BIL: general set; MANY: several
+// workgroups.  ln: lanes per rod.  The launch runs iterations k0 .. kend - 1
+// at most (k0 = 0: the start phases first); a stop is latched in the state,
+// else the iterate and the step length are left for the next launch.
+template <int T, int NC, int R1, int R2, bool HELD, bool BIL, bool MANY>
+__global__ void __launch_bounds__(T, 2) k_resident(SolveArgs a, Exchange x, int ln, long long k0, long long kend)
+{
+    constexpr int NW = T / 64, J = NC / T, kBins = 64;
+    static_assert(NC % T == 0 && J <= 16 && NC <= 0xffff && R1 % kGroup == 0 && R2 % kGroup == 0, "");
+    __shared__ double E[3][NC], G[NC], U[2 * NC];
+    __shared__ double sP[HELD ? NC : 1], sQ[HELD ? NC : 1];
+    __shared__ unsigned short qslot[NC];
+    __shared__ __align__(16) double red[MANY ? 2 : 1][4][4 * NW];
+    __shared__ int hist[kBins], share[4], bad;
+    const int tid = threadIdx.x;
+    const int n = (int)a.n, nc = (int)a.nc;
+    SolverState *S = a.state;
+    if (k0 > 0 && S->done) return;
+    const int lsh = ln == 4 ? 2 : (ln == 2 ? 1 : 0), sub = tid & (ln - 1);
+
+    // the workgroup's rods
+    int r0 = 0, r1 = n;
+    if (MANY) {
+        const int64_t total = (int64_t)a.pptr[n] + a.qptr[n] + 2 * (int64_t)n;
+        if (tid < 128) {
+            const int g = (int)blockIdx.x + (tid >> 6);
+            const int r = g >= (int)gridDim.x ? n : res_boundary(a, n, total * g / (int)gridDim.x);
+            if ((tid & 63) == 0) share[tid >> 6] = r;
+        }
+        __syncthreads();
+        r0 = share[0];
+        r1 = share[1];
+    }
+    const int c0 = a.pptr[r0], q0 = a.qptr[r0], own = a.pptr[r1] - c0, nq = a.qptr[r1] - q0;
+    bool fits = own < NC && nq <= NC;
+    if (tid == 0) {
+        share[2] = own;  // slots in use
+        share[3] = 0;    // rods with records
+        bad = 0;
+    }
+    if (tid < kBins) hist[tid] = 0;
+    __syncthreads();
+    // slots of the Q lists: the owner's, or a second one for a constraint
+    // whose P rod is elsewhere (its constraint left in `away` for now)
+    int *ord = reinterpret_cast<int *>(U), *away = reinterpret_cast<int *>(U + NC);
+    if (fits)
+        for (int k = tid; k < nq; k += T) {
+            const int c = a.qidx[q0 + k];
+            int s = c - c0;
+            if (s < 0 || s >= own) {
+                s = atomicAdd(&share[2], 1);
+                if (s < NC) away[s] = c;
+            }
+            qslot[k] = (unsigned short)min(s, NC - 1);
+        }
+    // the rods with records, by descending number of them: slot t of the
+    // order goes to lanes ln t ... of the workgroup (which rod a thread holds
+    // does not enter any sum)
+    auto key_of = [&](int r) {
+        return kBins - 1 - min(a.pptr[r + 1] - a.pptr[r] + a.qptr[r + 1] - a.qptr[r], kBins - 1);
+    };
+    for (int r = r0 + tid; r < r1; r += T) atomicAdd(&hist[key_of(r)], 1);
+    __syncthreads();
+    const int slots = share[2], cap = (R2 ? 2 : 1) * (T >> lsh);
+    if (tid < 64) {
+        const int v = hist[tid];
+        int incl = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d, 64);
+            if (tid >= d) incl += t;
+        }
+        hist[tid] = incl - v;
+        if (tid == kBins - 2) share[3] = incl;  // the last key holds the rods without records
+    }
+    __syncthreads();
+    const int nrod = share[3];  // share[3] counts the velocities to send from here on
+    fits = fits && slots < NC && nrod <= cap;
+    static_assert((R2 ? 2 : 1) * T <= 2 * NC, "the order fits in half of U");
+    if (fits)
+        for (int r = r0 + tid; r < r1; r += T) {
+            const int key = key_of(r);
+            if (key < kBins - 1) ord[atomicAdd(&hist[key], 1)] = r;
+        }
+    __syncthreads();
+    if (tid == 0) share[3] = 0;
+
+    unsigned num = x.base;  // number of the last exchange
+    // sums over the workgroups of what every thread holds the same, p[0..3]
+    const int groups = (int)gridDim.x;
+    auto publish = [&](u64 *slot, const double p[4]) {
+        if (tid < 4) pair_put(slot + 2 * tid, tid == 0 ? p[0] : (tid == 1 ? p[1] : (tid == 2 ? p[2] : p[3])), num);
+    };
+    // number tid & 3 of the slots tid >> 2, ... of cnt at buf, summed
+    auto collect = [&](const u64 *buf, int cnt) {
+        double c = 0.0;
+        for (int i = tid; i < 4 * cnt; i += T) {
+            const u64 *u = buf + (i >> 2) * kSlot + 2 * (i & 3);
+            c += pair_wait(u, num, x.fail, &bad);
+        }
+        return c;
+    };
+    auto gather4 = [&](double p[4]) {
+        if (!MANY) return;
+        u64 *buf = x.tot + (num & 1) * 2 * kResMost * kSlot;
+        publish(buf + (int)blockIdx.x * kSlot, p);
+        int cnt = groups;
+        if (groups > kFlat) {
+            const int team = (int)blockIdx.x / kTeam;
+            cnt = (groups + kTeam - 1) / kTeam;
+            if (blockIdx.x % kTeam == 0) {
+                const int first = team * kTeam;
+                res_sum4_lanes<NW>(collect(buf + first * kSlot, min(kTeam, groups - first)), p, red[MANY]);
+                publish(buf + (kResMost + team) * kSlot, p);
+                res_sum4_lanes<NW>(collect(buf + kResMost * kSlot, cnt), p, red[0]);
+                return;
+            }
+            buf += kResMost * kSlot;
+        }
+        res_sum4_lanes<NW>(collect(buf, cnt), p, red[MANY]);
+    };
+    auto max_all = [&](double v) {
+        v = res_max<NW>(v, &red[0][0][0]);
+        if (MANY) {
+            ++num;
+            u64 *buf = x.tot + (num & 1) * 2 * kResMost * kSlot;
+            if (tid == 0) pair_put(buf + (int)blockIdx.x * kSlot, v, num);
+            double c = 0.0;
+            for (int i = tid; i < groups; i += T) {
+                const u64 *u = buf + i * kSlot;
+                c = fmax(c, pair_wait(u, num, x.fail, &bad));
+            }
+            v = res_max<NW>(c, &red[0][0][0]);
+        }
+        return v;
+    };
+    if (MANY) {
+        // everybody is here, and everybody's share fits
+        double p[4] = {fits ? 0.0 : 1.0, 0.0, 0.0, 0.0};
+        ++num;
+        gather4(p);
+        if (bad || p[0] > 0.0) {
+            if (tid == 0) __hip_atomic_store(x.fail, bad ? 1 : 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+    } else if (!fits) {
+        if (tid == 0) *x.fail = 2;
+        return;
+    }
+
+    if (MANY) {
+        // the second slots in the order of their constraints (by rank), so
+        // that neighbouring lanes send and receive neighbouring words
+        int *moved = reinterpret_cast<int *>(U) + (R2 ? 2 : 1) * T;
+        static_assert(!MANY || (R2 ? 2 : 1) * T + NC <= 2 * NC, "order and moved slots fit in half of U");
+        int c[J], rank[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int s = own + tid + j * T;
+            rank[j] = 0;
+            if (s < slots) {
+                c[j] = away[s];
+                for (int k = own; k < slots; ++k) rank[j] += away[k] < c[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int s = own + tid + j * T;
+            if (s < slots) {
+                moved[s - own] = own + rank[j];
+                away[own + rank[j]] = c[j];
+            }
+        }
+        __syncthreads();
+        for (int k = tid; k < nq; k += T)
+            if (qslot[k] >= own) qslot[k] = (unsigned short)moved[qslot[k] - own];
+        __syncthreads();
+    }
+    const ResLds l{E[0], E[1], E[2], sP, sQ, qslot, G, U, c0, q0};
+    // Slot state.  A slot past the last one is a constraint without rods that
+    // stays at zero, so the iteration needs no test.  cross: bit j set where
+    // the other rod is in another workgroup; out, in: byte offsets in x.u of
+    // our velocity and of the other (their high halves `high` further).
+    double gam[J], g[J], q[J], cm[BIL ? J : 1];
+    unsigned out[MANY ? J : 1], in[MANY ? J : 1];
+    unsigned cross = 0;
+    const unsigned high = 8u * (unsigned)(MANY ? gridDim.x : 0) * NC;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int s = tid + j * T;
+        const bool ok = s < slots;
+        const int c = !ok ? 0 : (s < own ? c0 + s : away[s]);
+        gam[j] = g[j] = q[j] = 0.0;
+        if (BIL) cm[j] = -1.0;
+        if (MANY) out[j] = in[j] = 0;
+        if (ok) {
+            const double2 st = a.st[c];
+            gam[j] = st.x;
+            g[j] = st.y;
+            q[j] = a.qv[c];
+            if (BIL) cm[j] = a.cmpv[c];
+            if (MANY) {
+                const int r = a.pp[c].y;  // the Q rod (below 0: a fixed body)
+                if (s >= own || (r >= 0 && (r < r0 || r >= r1))) {
+                    cross |= 1u << j;
+                    const unsigned k = (unsigned)blockIdx.x * NC + (unsigned)atomicAdd(&share[3], 1);
+                    out[j] = 8u * k;
+                    in[j] = 2u * (unsigned)c + (s < own ? 1u : 0u);
+                    word_put(x.at + 2 * (int64_t)c + (s < own ? 0 : 1), ((u64)k << 32) | num);
+                }
+            }
+        }
+        const double2 *gd = reinterpret_cast<const double2 *>(a.geo + 4 * (int64_t)c);
+        const double2 g0 = gd[0], g1 = gd[1];
+        E[0][s] = ok ? g0.x : 0.0;
+        E[1][s] = ok ? g0.y : 0.0;
+        E[2][s] = ok ? g1.x : 0.0;
+        if (HELD) {
+            sP[s] = ok ? g1.y : 0.0;
+            if (s < nq) sQ[s] = a.qgeo[4 * (int64_t)(q0 + s) + 3];
+        }
+        G[s] = 0.0;
+    }
+    ResRod<R1, HELD> rod1;
+    ResRod<R2 ? R2 : kGroup, HELD> rod2;
+    __syncthreads();
+    {
+        const int t = tid >> lsh, st = T >> lsh;
+        res_rod_setup<NC>(a, l, t < nrod ? ord[t] : -1, sub, ln, rod1);
+        // the second rods backwards, so that no wave has the longest of both
+        const int t2 = 2 * st - 1 - t;
+        if (R2) res_rod_setup<NC>(a, l, t2 < nrod ? ord[t2] : -1, sub, ln, rod2);
+    }
+    __syncthreads();
+    if (MANY) {
+        // where the other velocities will be
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if ((cross >> j) & 1u) {
+                u64 v = 0;
+                for (int spin = 0;; ++spin) {
+                    v = word_get(x.at + in[j]);
+                    if ((unsigned)v == num || give_up(spin, x.fail, &bad)) break;
+                }
+                in[j] = (unsigned)v == num ? 8u * (unsigned)(v >> 32) : 0u;
+            }
+    }
+    // a constraint without a Q side keeps u_Q = 0, an empty slot both
+#pragma unroll
+    for (int j = 0; j < J; ++j) U[tid + j * T] = U[NC + tid + j * T] = 0.0;
+
+    // one product: G holds v, w[j] receives D^T M D v of the thread's slots
+    auto product = [&](double w[J]) {
+        if (MANY) ++num;
+        __syncthreads();
+        res_rod<NC>(a, l, sub, ln, rod1);
+        if (R2) res_rod<NC>(a, l, sub, ln, rod2);
+        __syncthreads();
+        double up[J], uq[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            up[j] = U[tid + j * T];
+            uq[j] = U[NC + tid + j * T];
+        }
+        if (MANY) {
+            // our halves out, then all of the others polled together (a round
+            // trip is most of the wait: one slot after the other would take
+            // one each)
+            unsigned char *base = reinterpret_cast<unsigned char *>(x.u);
+            auto word = [&](unsigned o) { return reinterpret_cast<u64 *>(base + o); };
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                if ((cross >> j) & 1u) {
+                    const double v = tid + j * T < own ? up[j] : uq[j];
+                    word_put(word(out[j]), half_word(__double2loint(v), num));
+                    word_put(word(out[j] + high), half_word(__double2hiint(v), num));
+                }
+            unsigned left = cross;
+            for (int spin = 0; left; ++spin) {
+                u64 lo[J], hi[J];
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+                    if ((left >> j) & 1u) {
+                        lo[j] = word_get(word(in[j]));
+                        hi[j] = word_get(word(in[j] + high));
+                    }
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+                    if (((left >> j) & 1u) && (unsigned)lo[j] == num && (unsigned)hi[j] == num) {
+                        const double v = pair_value(lo[j], hi[j]);
+                        if (tid + j * T < own) uq[j] = v;
+                        else up[j] = v;
+                        left &= ~(1u << j);
+                    }
+                if (left && give_up(spin, x.fail, &bad)) break;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) w[j] = up[j] + uq[j];
+    };
+    auto bil = [&](int j) { return BIL && cm[BIL ? j : 0] >= 0.0; };
+    auto diag = [&](int j, double v) { return bil(j) ? cm[BIL ? j : 0] * v : 0.0; };
+    // its sums are over the constraints: a second slot does not enter them
+    auto ours = [&](int j) { return !MANY || tid + j * T < own; };
+
+    const double tol = S->tol;
+    const long long max_iter = S->max_iter;
+    double alpha = 0.0, alpha0 = 0.0, amin = 0.0, amax = 0.0, rmax = 0.0;
+    if (k0 > 0) {
+        alpha = S->alpha;
+        alpha0 = S->alpha0;
+        amin = S->amin;
+        amax = S->amax;
+    }
+    int status = RL_OK;
+    bool done = false;
+    long long iter = 0;
+    double p[4], w[J];
+    auto sum_all = [&]() {
+        res_sum4<NW>(p, red[0]);
+        gather4(p);
+    };
+    if (k0 == 0) {
+        // g0 = Mc gamma0 + q on the projected start
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (!bil(j)) gam[j] = gamma_prime<kModeInit>(gam[j], 0.0, 0.0);
+            G[tid + j * T] = gam[j];
+        }
+        product(w);
+        p[0] = p[1] = p[2] = p[3] = 0.0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            g[j] = w[j] + (q[j] + diag(j, gam[j]));
+            const double gn = ours(j) ? g[j] : 0.0;
+            p[2] += gn * gn;
+            rmax = fmax(rmax, ours(j) ? fabs(!bil(j) && gam[j] < g[j] ? gam[j] : g[j]) : 0.0);
+        }
+        p[3] = rmax > tol ? 1.0 : 0.0;
+        sum_all();
+        if (!isfinite(p[2])) {
+            status = RL_ERR_NONFINITE;
+            done = true;
+        } else if (!(p[3] > 0.0)) {
+            done = true;
+        }
+        if (!done && !(MANY && bad)) {
+            // the Cauchy step on the projected gradient
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                G[tid + j * T] = bil(j) ? g[j] : gamma_prime<kModeAlpha0>(gam[j], g[j], 0.0);
+            product(w);
+            p[0] = p[1] = p[2] = p[3] = 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const double gh = !ours(j) ? 0.0 : (bil(j) ? g[j] : gamma_prime<kModeAlpha0>(gam[j], g[j], 0.0));
+                p[0] += gh * gh;
+                p[1] += gh * (w[j] + diag(j, gh));
+            }
+            sum_all();
+            if (!isfinite(p[0]) || !isfinite(p[1])) {
+                status = RL_ERR_NONFINITE;
+                done = true;
+            } else if (p[0] == 0.0) {
+                done = true;
+            } else {
+                alpha0 = p[1] > 0.0 ? p[0] / p[1] : 1.0;
+                alpha = alpha0;
+                amin = 1e-12 * alpha0;
+                amax = 1e12 * alpha0;
+                if (max_iter <= 0) {
+                    status = RL_NOT_CONVERGED;
+                    done = true;
+                }
+            }
+        }
+    }
+    // The iterations, written to fall through: a taken branch costs about as
+    // much as ten instructions here.
+    if (!done && !(MANY && bad))
+        for (long long k = k0; k < kend; ++k) {
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                G[tid + j * T] = bil(j) ? gamma_free<kModeLoop>(gam[j], g[j], alpha)
+                                        : gamma_prime<kModeLoop>(gam[j], g[j], alpha);
+            product(w);
+            // (s.s, s.y, y.y, whether a residual is above the tolerance)
+            p[0] = p[1] = p[2] = rmax = 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                // gamma' again (cheaper than registers held across the rods' turn)
+                const double v = bil(j) ? gamma_free<kModeLoop>(gam[j], g[j], alpha)
+                                        : gamma_prime<kModeLoop>(gam[j], g[j], alpha);
+                const double gn = w[j] + (q[j] + diag(j, v));
+                const double sc = ours(j) ? v - gam[j] : 0.0, yc = ours(j) ? gn - g[j] : 0.0;
+                const double r = fabs(!bil(j) && v < gn ? v : gn);
+                p[0] += sc * sc;
+                p[1] += sc * yc;
+                p[2] += yc * yc;
+                rmax = fmax(rmax, ours(j) ? r : 0.0);
+                gam[j] = v;
+                g[j] = gn;
+            }
+            p[3] = rmax > tol ? 1.0 : 0.0;
+            sum_all();
+            // the step rule's residual only has to be on the right side of
+            // the tolerance here; the stop takes the true one below
+            const double t[4] = {p[0], p[1], p[2], p[3] > 0.0 ? 2.0 * tol + 1.0 : 0.0};
+            const Decision d = decide_from(DecideIn{tol, amin, amax, alpha, max_iter}, k + 1, t);
+            alpha = d.alpha;
+            if (__builtin_expect(d.stop || (MANY && bad), 0)) {
+                done = !(MANY && bad);
+                status = d.status;
+                iter = k + 1;
+                break;
+            }
+        }
+    double res = 0.0;
+    if (done) {
+        res = max_all(rmax);
+        if (!isfinite(res)) status = RL_ERR_NONFINITE;
+    }
+    if (MANY) {
+        __syncthreads();
+        if (bad) return;  // the flag is set
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int s = tid + j * T;
+        if (s < own) {
+            const int c = c0 + s, k = a.qpos[c];
+            const double2 v = make_double2(gam[j], g[j]);
+            a.st[c] = v;
+            if (!BIL || k >= 0) a.stq[k] = v;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        S->alpha = alpha;
+        S->alpha0 = alpha0;
+        S->amin = amin;
+        S->amax = amax;
+        S->res = res;
+        S->iter = iter;
+        S->status = status;
+        S->done = done ? 1 : 0;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+// The forms: threads, slots, records held by a thread's first and second rod,
+// whether with their normals.
+constexpr int kResForms = 5;
+constexpr int kResSlots[kResForms] = {1024, 1536, 2048, 2560, 3072};
+
+template <int T, int NC, int R1, int R2, bool HELD, bool MANY>
+static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, const ResPlan &p, long long k0,
+                              long long kend)
+{
+    SolveArgs aa = a;
+    int ln = p.ln;
+    void *args[] = {&aa, &x, &ln, &k0, &kend};
+    const void *f = a.gen ? (const void *)k_resident<T, NC, R1, R2, HELD, true, MANY>
+                          : (const void *)k_resident<T, NC, R1, R2, HELD, false, MANY>;
+    // cooperative: all workgroups are resident before any waits for another
+    if (MANY) return hipLaunchCooperativeKernel(f, dim3(p.groups), dim3(T), args, 0, st);
+    return hipLaunchKernel(f, dim3(1), dim3(T), args, 0, st);
+}
+
+// Form, workgroups and lanes per rod of a problem; groups = 0: none takes it.
+ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered)
+{
+    ResPlan p{0, 0, 1};
+    if (nc <= 0 || nc >= (1 << 29)) return p;
+    if (n <= 512 && nc < 1024) {
+        p.groups = 1;
+    } else if (n <= 1024 && nc < kResSolo) {
+        p.form = 1;
+        p.groups = 1;
+    } else {
+        // slots of a workgroup: its own constraints and those that reach in
+        // from outside (the fullest workgroup of the 100,000-rod nematic
+        // suspensions has 1.24 times the mean), nearly all of them when the
+        // rods are in no spatial order: there the largest forms lose (100,000
+        // rods, 281,000 constraints: 23.5 us per iteration, two kernels 20.8;
+        // 50,000 and 90,000: 14.3 and 16.8).  A problem that does not fit
+        // after all is tried again with more slots.
+        const double reach = ordered ? 1.30 : 2.05;
+        const int forms = ordered ? kResForms : 3;
+        const int most = std::min(h->cus, kResMost);
+        auto fits = [&](int g, int form) {
+            return (double)nc * reach / g <= 0.96 * kResSlots[form] && 1.15 * (double)n / g + 8.0 <= 512.0;
+        };
+        int g = (int)std::min<int64_t>((nc + kResPer - 1) / kResPer, kFlat);
+        g = std::max(g, 2);
+        if (!fits(g, 0)) g = 2 * kFlat;
+        if (!fits(g, 0)) g = most;
+        if (g > most) return p;
+        while (p.form < forms && !fits(g, p.form)) ++p.form;
+        if (p.form == forms) return p;
+        p.groups = g;
+    }
+    // several lanes per rod while that leaves one rod per thread (the single
+    // workgroup has two, and takes them for long lists)
+    const bool two = p.groups == 1;
+    const int T = two && p.form == 0 ? 256 : 512;
+    const double rods = two ? (double)n : 1.15 * (double)n / p.groups + 8.0;
+    while (p.ln < 4 && (2 * p.ln * rods <= T || (two && 2 * p.ln * rods <= 2 * T && 2.0 * nc > 6.0 * p.ln * n)))
+        p.ln *= 2;
+    return p;
+}
+
+// the next larger form; false: there is none
+bool resident_larger(ResPlan &p) { return p.groups > 1 && ++p.form < kResForms; }
+
+int64_t resident_words(const ResPlan &p, int64_t nc)
+{
+    return p.groups > 1 ? 2 * (int64_t)p.groups * kResSlots[kResForms - 1] + 2 * nc + 4 * (int64_t)kResMost * kSlot : 0;
+}
+
+hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, unsigned long long *words,
+                           unsigned base, long long k0, long long kend)
+{
+    u64 *at = words ? words + 2 * (int64_t)p.groups * kResSlots[p.form] : nullptr;
+    const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail};
+    if (p.groups == 1) {
+        if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, p, k0, kend);
+        return launch_form<512, 2048, 8, 4, true, false>(st, a, x, p, k0, kend);
+    }
+    switch (p.form) {
+    case 0: return launch_form<512, 1024, 8, 0, true, true>(st, a, x, p, k0, kend);
+    case 1: return launch_form<512, 1536, 12, 0, true, true>(st, a, x, p, k0, kend);
+    case 2: return launch_form<512, 2048, 8, 0, true, true>(st, a, x, p, k0, kend);
+    case 3: return launch_form<512, 2560, 16, 0, false, true>(st, a, x, p, k0, kend);
+    default: return launch_form<512, 3072, 12, 0, false, true>(st, a, x, p, k0, kend);
+    }
+}
+
+}  // namespace rl

@@ -1,7 +1,8 @@
-"""The one-workgroup solve at the edges of its forms: constraint counts
+"""Solves that stay on chip, at the edges of their forms: constraint counts
 around the slots of each form, rod counts around the threads, one, two and
-four lanes per rod, lists longer than the records a rod holds, contact-only
-and general sets, and solves longer than one launch.  Bars as for every
+four lanes per rod, lists longer than the records a rod holds, one workgroup
+and several, contact-only and general sets, and solves longer than one
+launch.  Bars as for every
 solve: the answer certified by the oracle's operator (residual <= 1e-8), the
 velocities within 1e-6 of the oracle's."""
 import numpy as np
@@ -31,11 +32,13 @@ def _problem(n, nc, lengths):
     return s, d, L, pr, oracle.assemble(s.x, d, L, s.box, s.diam, s.eta, s.dt, pr, s.force)
 
 
-# around 1,024, 2,048 and 3,072 slots and 512, 1,024 and 2,048 rods; (60, 900)
-# and (200, 1600) have lists far longer than a rod holds
+# one workgroup: up to 1,023 constraints and 512 rods, 1,535 and 1,024; beyond,
+# workgroups that exchange (2 and 3 of them, then up to 64 flat, then teams);
+# (60, 450), (200, 1600) and (700, 4000) have lists longer than a rod holds
 EDGES = [(30, 1, False), (64, 65, True), (129, 300, False), (512, 1023, True), (513, 1023, False),
-         (300, 1024, False), (1024, 2047, False), (1025, 700, True), (700, 2048, False), (2048, 3071, True),
-         (2049, 3071, False), (900, 3072, True), (60, 450, False), (200, 1600, False)]
+         (300, 1024, False), (1024, 1535, False), (1025, 500, True), (1024, 1536, True), (60, 450, False),
+         (200, 1600, False), (900, 3072, True), (700, 4000, False), (2049, 3071, False), (6000, 17000, True),
+         (40_000, 33_000, False)]
 
 
 @pytest.mark.parametrize("n,nc,lengths", EDGES)
@@ -56,7 +59,7 @@ def test_solve_at_the_edges(gpu_lib, n, nc, lengths):
     assert np.linalg.norm(U - Uref) <= 1e-6 * np.linalg.norm(Uref)
 
 
-@pytest.mark.parametrize("n,nc,lengths", [(40, 60, False), (512, 1023, False), (1000, 2047, True), (2048, 3071, False)])
+@pytest.mark.parametrize("n,nc,lengths", [(40, 60, False), (512, 1023, False), (1000, 2047, True), (5000, 9000, False)])
 def test_general_solve_at_the_edges(gpu_lib, n, nc, lengths):
     s, d, L, pr, cs = _problem(n, nc, lengths)
     rng = np.random.default_rng(n)
@@ -80,6 +83,25 @@ def test_general_solve_at_the_edges(gpu_lib, n, nc, lengths):
     r = np.where(gc.kind == 1, np.abs(w), np.abs(np.minimum(g, w)))
     assert g[gc.kind == 0].min() >= 0 and r.max() <= 1e-8 * 1.01
     assert np.linalg.norm(U - Uref) <= 1e-6 * np.linalg.norm(Uref)
+
+
+def test_rod_that_fits_no_workgroup(gpu_lib):
+    """One rod in 5,000 constraints: more than any workgroup holds."""
+    n, nc = 5001, 5000
+    rng = np.random.default_rng(5)
+    d, e = rng.normal(size=(n, 3)), rng.normal(size=(nc, 3))
+    d, e = d / np.linalg.norm(d, axis=1)[:, None], e / np.linalg.norm(e, axis=1)[:, None]
+    kind = (rng.random(nc) < 0.5).astype(np.uint8)
+    gc = oracle.General(np.zeros(nc, np.int32), np.arange(1, n, dtype=np.int32), e, rng.uniform(-0.5, 0.5, (nc, 2)),
+                        rng.uniform(-1.0, 0.2, nc), kind, np.where(kind == 1, 2000.0, 0.0))
+    with gpu_lib.Solver(box=10.0, diam=0.08, cutoff=0.1, eta=1.0, dt=1e-3, tol=1e-8) as slv:
+        g, _, info = slv.solve_general(_t(d), 1.0, _t(gc.pi, torch.int32), _t(gc.pj, torch.int32), _t(gc.e),
+                                       _t(gc.arm), _t(gc.q), _t(gc.kind, torch.uint8), _t(gc.cmp))
+    assert info.status == gpu_lib.OK and info.residual <= 1e-8
+    g = g.cpu().numpy()
+    w = oracle.apply_Mc_gen(d, 1.0, 0.08, 1.0, gc, g)
+    r = np.where(kind == 1, np.abs(w), np.abs(np.minimum(g, w)))
+    assert g[kind == 0].min() >= 0 and r.max() <= 1e-8 * 1.01
 
 
 def test_solve_over_several_launches(gpu_lib):

@@ -10,9 +10,12 @@ starts from the same resident configuration (a device copy inside the timed
 region), so each step does the same work.
 
 Prints one JSON line: BBPGD iterations per second over the timed steps (the
-whole step is timed, pair search included), LCP solves per second, the
-roofline of the dominant solver kernel from HIP events sampled during the
-timed steps, and the CPU oracle timed on a bounded sample.
+whole step is timed, pair search included), LCP solves per second, the rate
+at which the loop covers its algorithmic bytes, and the CPU oracle timed on a
+bounded sample.  The timed steps run unsampled: solves of this size stay on
+chip in one launch, and sampling the loop kernels with HIP events makes a
+handle run the two-kernel loop instead, which two more steps after the timed
+ones do for the kernel figures.
 """
 from __future__ import annotations
 
@@ -517,8 +520,6 @@ def form_dynamics(args, torch, rl, rodsynth) -> dict:
 
     for k in range(args.warmup):
         coupled(k)
-    slv.profile_enable(args.profile_every)
-    slv.profile_read()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     iters, status, res = [], 0, 0.0
@@ -531,22 +532,15 @@ def form_dynamics(args, torch, rl, rodsynth) -> dict:
         counts.append((npairs, nlinks, nwall))
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
-    prof = slv.profile_read()
-    slv.profile_enable(0)
     stress = slv.last_stress
     slv.close()
     npairs, nlinks, nwall = counts[-1]
     nc = npairs + nlinks + nwall
     nq = npairs + nlinks
-    # general-mode loop kernels: the contact-only records plus per rod its two
-    # split indices (8 B) and per constraint the compliance (8 B); a wall
-    # constraint has no Q side
-    kb = {"rod": 40 * n + 56 * nc + 56 * nq, "con": 60 * nc + 24 * nq}
-    avg = {"rod": prof["rod_ms"] / max(1, prof["rod_launches"]),
-           "con": prof["con_ms"] / max(1, prof["con_launches"])}
-    names = {"rod": "k_rod<2,true,gen,3,4>", "con": con_kernel_name(nc)[:-1] + ",gen>"}
-    dom = max(avg, key=avg.get)
-    achieved = kb[dom] / (avg[dom] * 1e-3) / 1e9 if avg[dom] > 0 else 0.0
+    # what the loop kernels over memory move per iteration: the contact-only
+    # records plus per rod its two split indices (8 B) and per constraint the
+    # compliance (8 B); a wall constraint has no Q side
+    loop_gbps = (40 * n + 56 * nc + 56 * nq + 60 * nc + 24 * nq) * sum(iters) / el / 1e9
     return {
         "metric": "dynamics form: coupled steps per second (crosslinker kinetics, then contacts, crosslinker links "
                   "and the confining shell as one constraint set with Brownian forces, warm-started, with the "
@@ -562,12 +556,9 @@ def form_dynamics(args, torch, rl, rodsynth) -> dict:
         "bbpgd_iters_per_s": sum(iters) / el, "iterations_per_step": iters, "max_residual": res, "status": status,
         "constraints_last_step": {"contacts": npairs, "links": nlinks, "wall": nwall},
         "stress_trace_last_step": {"contacts": float(stress[0].trace()), "links": float(stress[1].trace())},
-        "roofline": {"bound": "hbm", "kernel": names[dom], "achieved": achieved, "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "alg_bytes_per_launch": kb[dom], "avg_launch_us": 1e3 * avg[dom]},
-        "kernels": {names[k]: {"avg_us": 1e3 * avg[k], "alg_bytes": kb[k],
-                               "alg_gbps": kb[k] / (avg[k] * 1e-3) / 1e9 if avg[k] > 0 else 0.0,
-                               "samples": prof[f"{k}_launches"]} for k in ("rod", "con")},
+        "roofline": {"bound": "hbm", "kernel": "whole timed step: the bytes a loop over memory would move per iteration",
+                     "achieved": loop_gbps, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": loop_gbps / HBM_PEAK_GBS,
+                     "traffic": None},
     }
 
 
@@ -673,8 +664,6 @@ def main() -> int:
 
     for _ in range(args.warmup):
         one_step()
-    slv.profile_enable(args.profile_every)
-    slv.profile_read()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     iters, npairs, res, status = 0, 0, 0.0, 0
@@ -685,6 +674,10 @@ def main() -> int:
         status = max(status, info.status)
     torch.cuda.synchronize()
     t1 = time.perf_counter()
+    slv.profile_enable(args.profile_every)
+    slv.profile_read()
+    for _ in range(2):
+        one_step()
     prof = slv.profile_read()
     slv.profile_enable(0)
 
@@ -697,6 +690,7 @@ def main() -> int:
     achieved = kb[dom] / (avg[dom] * 1e-3) / 1e9 if avg[dom] > 0 else 0.0
     traffic = measured_traffic(dom)
     per_iter_bytes = kb["rod"] + kb["con"]
+    loop_gbps = per_iter_bytes * iters / elapsed / 1e9
     out = {
         "metric": METRIC,
         "value": iters / elapsed,
@@ -717,10 +711,13 @@ def main() -> int:
         "iters_per_solve": iters / args.steps,
         "max_residual": res,
         "status": status,
-        "solver_alg_gbps": per_iter_bytes * iters / elapsed / 1e9,
-        "roofline": {"bound": "hbm", "kernel": names[dom], "achieved": achieved, "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": traffic, "alg_bytes_per_launch": kb[dom], "avg_launch_us": 1e3 * avg[dom]},
+        "solver_alg_gbps": loop_gbps,
+        "roofline": {"bound": "hbm", "kernel": "whole timed step: the bytes a loop over memory would move per iteration",
+                     "achieved": loop_gbps, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": loop_gbps / HBM_PEAK_GBS,
+                     "traffic": None},
+        "two_kernel_loop": {"kernel": names[dom], "achieved": achieved, "unit": "GB/s",
+                            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "alg_bytes_per_launch": kb[dom],
+                            "avg_launch_us": 1e3 * avg[dom]},
         "kernels": {names[k]: {"avg_us": 1e3 * avg[k], "alg_bytes": kb[k],
                                "alg_gbps": kb[k] / (avg[k] * 1e-3) / 1e9 if avg[k] > 0 else 0.0,
                                "samples": prof[f"{k}_launches"]} for k in ("rod", "con")},

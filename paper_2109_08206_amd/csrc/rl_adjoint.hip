@@ -32,7 +32,8 @@
 // scalars.  The constraint kernel applies the update, takes w = u_P - u_Q on
 // A and writes the partial sums.  No workgroup waits for another: every
 // workgroup of the next rod kernel sums the previous partials itself in a
-// fixed order.
+// fixed order.  Problems that fit on chip run all iterations in one launch
+// instead (rl_resident.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -626,8 +627,15 @@ int adjoint_core(rl_ctx *h, SolveArgs &a, bool step, const double *Ubar, const d
     double res = 0.0;
     int status = RL_OK;
     if (nc > 0) {
-        hipLaunchKernelGGL(k_cg_start, dim3(a.gcon), dim3(kConBlock), 0, st, g, (const double *)wsol);
-        RL_HIP(hipGetLastError());
+        const ResCg cg{g.cs, g.cr, g.cq};
+        bool solved = false;
+        auto start = [&]() {
+            hipLaunchKernelGGL(k_cg_start, dim3(a.gcon), dim3(kConBlock), 0, st, g, (const double *)wsol);
+            return hipGetLastError();
+        };
+        RL_HIP(start());
+        if ((rc = resident_run(h, a, &cg, cg_tol, [] { return hipSuccess; }, &solved))) return rc;
+        if (!solved) RL_HIP(start());
         const int every = p.check_every > 0 ? p.check_every : 32;
         const dim3 rgrid(rod_grid8(n > 0 ? n : 1));
         long long launched = 0;
@@ -655,8 +663,8 @@ int adjoint_core(rl_ctx *h, SolveArgs &a, bool step, const double *Ubar, const d
         // never idles on the host (iterations after the stop return at once)
         const int la = std::min(every, 8);
         if (!h->chk_ev) RL_HIP(hipEventCreateWithFlags(&h->chk_ev, hipEventDisableTiming));
-        if ((rc = enqueue(every))) return rc;
-        for (;;) {
+        if (!solved && (rc = enqueue(every))) return rc;
+        while (!solved) {
             RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
             RL_HIP(hipEventRecord(h->chk_ev, st));
             const long long checked = launched;

@@ -1,6 +1,7 @@
 // Internal declarations of the rodlcp HIP library (gfx950).
 #pragma once
 
+#include <functional>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -276,20 +277,19 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
                   const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
                   double *gamma, SolveArgs *a, bool trusted = false);
 int apply_impl(rl_ctx *h, SolveArgs &a, double *w);
-// Solves that stay on chip (rl_resident.hip): which form takes a problem, the
-// exchange words it needs between workgroups, and its launch over iterations
-// k0 .. kend - 1 of a prepared solve.  ordered: neighbouring rods have
-// neighbouring numbers.
-struct ResPlan {
-    int form, groups, ln;  // groups = 0: none takes it
+// Solves that stay on chip (rl_resident.hip).
+// What the conjugate gradients of the adjoint read and leave, in the layout of
+// their two-kernel form: (lambda, p, mask, .), (r, s, ., .) and, in the order
+// of the Q lists, (., ., ., lambda).
+struct ResCg {
+    double *cs, *cr, *cq;
 };
-constexpr int kResSolo = 1536;  // constraints up to which one workgroup is as fast as several
-constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64 are needed
-ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered);
-bool resident_larger(ResPlan &p);
-int64_t resident_words(const ResPlan &p, int64_t nc);
-hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, unsigned long long *words,
-                           unsigned base, long long k0, long long kend);
+// Runs a prepared solve (or cg) on chip if a form takes it.  `queue` queues
+// what reads the result, after each launch.  solved: state_host holds the
+// stop.  Else nothing was solved: the state is as k_state_init(tol) leaves it,
+// the iterate (and what cg holds) may be any of the solve.
+int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, const std::function<hipError_t()> &queue,
+                 bool *solved);
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
                const int *perm = nullptr);
 // xu (may be null): unwrapped centres, += h U_t without wrapping

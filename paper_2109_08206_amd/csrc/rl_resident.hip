@@ -364,13 +364,18 @@ __device__ __forceinline__ int res_boundary(const SolveArgs &a, int n, int64_t t
 
 // T threads; NC slots, the last one a zero that no constraint takes; J = NC /
 // T slots per thread; K rods per thread (1 or 2); HELD: the rods hold the
-// normals of their records in registers; BIL: general set; MANY: several
+// normals of their records in registers; KIND: a contact set, a general set,
+// or the conjugate gradients of a contact set's adjoint; MANY: several
 // workgroups.  ln: lanes per rod.  The launch runs iterations k0 .. kend - 1
 // at most (k0 = 0: the start phases first); a stop is latched in the state,
 // else the iterate and the step length are left for the next launch.
-template <int T, int NC, int R1, int R2, bool HELD, bool BIL, bool MANY>
-__global__ void __launch_bounds__(T, 2) k_resident(SolveArgs a, Exchange x, int ln, long long k0, long long kend)
+enum ResKind { kResContacts, kResGeneral, kResCg };
+
+template <int T, int NC, int R1, int R2, bool HELD, ResKind KIND, bool MANY>
+__global__ void __launch_bounds__(T, 2)
+    k_resident(SolveArgs a, Exchange x, ResCg io, int ln, long long k0, long long kend)
 {
+    constexpr bool BIL = KIND == kResGeneral, CG = KIND == kResCg;
     constexpr int NW = T / 64, J = NC / T, kBins = 64;
     static_assert(NC % T == 0 && J <= 16 && NC <= 0xffff && R1 % kGroup == 0 && R2 % kGroup == 0, "");
     __shared__ double E[3][NC], G[NC], U[2 * NC];
@@ -548,7 +553,10 @@ __global__ void __launch_bounds__(T, 2) k_resident(SolveArgs a, Exchange x, int 
     // stays at zero, so the iteration needs no test.  cross: bit j set where
     // the other rod is in another workgroup; out, in: byte offsets in x.u of
     // our velocity and of the other (their high halves `high` further).
-    double gam[J], g[J], q[J], cm[BIL ? J : 1];
+    // Conjugate gradients: lambda, r and s in the place of gamma, g and q, the
+    // direction in pv, and the active constraints in act.
+    double gam[J], g[J], q[J], cm[BIL ? J : 1], pv[CG ? J : 1];
+    unsigned act = 0;
     unsigned out[MANY ? J : 1], in[MANY ? J : 1];
     unsigned cross = 0;
     const unsigned high = 8u * (unsigned)(MANY ? gridDim.x : 0) * NC;
@@ -560,12 +568,23 @@ __global__ void __launch_bounds__(T, 2) k_resident(SolveArgs a, Exchange x, int 
         gam[j] = g[j] = q[j] = 0.0;
         if (BIL) cm[j] = -1.0;
         if (MANY) out[j] = in[j] = 0;
+        if (CG) pv[CG ? j : 0] = 0.0;
         if (ok) {
-            const double2 st = a.st[c];
-            gam[j] = st.x;
-            g[j] = st.y;
-            q[j] = a.qv[c];
-            if (BIL) cm[j] = a.cmpv[c];
+            if (CG) {
+                const double2 *cs = reinterpret_cast<const double2 *>(io.cs + 4 * (int64_t)c);
+                const double2 lp = cs[0], rs = *reinterpret_cast<const double2 *>(io.cr + 4 * (int64_t)c);
+                gam[j] = lp.x;
+                pv[CG ? j : 0] = lp.y;
+                g[j] = rs.x;
+                q[j] = rs.y;
+                if (cs[1].x > 0.0) act |= 1u << j;
+            } else {
+                const double2 st = a.st[c];
+                gam[j] = st.x;
+                g[j] = st.y;
+                q[j] = a.qv[c];
+                if (BIL) cm[j] = a.cmpv[c];
+            }
             if (MANY) {
                 const int r = a.pp[c].y;  // the Q rod (below 0: a fixed body)
                 if (s >= own || (r >= 0 && (r < r0 || r >= r1))) {
@@ -687,6 +706,96 @@ __global__ void __launch_bounds__(T, 2) k_resident(SolveArgs a, Exchange x, int 
         res_sum4<NW>(p, red[0]);
         gather4(p);
     };
+    if constexpr (CG) {
+        double rho = 0.0, bb = 0.0, nact = 0.0, res = 0.0;
+        if (k0 == 0) {
+            p[0] = p[1] = p[2] = p[3] = 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                p[0] += ours(j) ? g[j] * g[j] : 0.0;
+                p[2] += ours(j) ? (double)((act >> j) & 1u) : 0.0;
+            }
+            if (MANY) ++num;
+            sum_all();
+            bb = p[0];
+            nact = p[2];
+            if (!(bb > 0.0)) {
+                status = isfinite(bb) ? RL_OK : RL_ERR_NONFINITE;
+                done = true;
+            }
+        } else {
+            bb = S->alpha0;
+            nact = S->ss;
+            rho = S->amin;
+        }
+        if (!done && !(MANY && bad))
+            for (long long k = k0; k < kend; ++k) {
+#pragma unroll
+                for (int j = 0; j < J; ++j) G[tid + j * T] = g[j];
+                product(w);
+                p[0] = p[1] = p[2] = p[3] = 0.0;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    if (!((act >> j) & 1u)) w[j] = 0.0;
+                    const double rv = ours(j) ? g[j] : 0.0;
+                    p[0] += rv * rv;
+                    p[1] += rv * w[j];
+                }
+                sum_all();
+                // the rules of the two-kernel loop (alpha: of the iteration before)
+                double beta = 0.0, den = p[1];
+                if (k > 0) {
+                    beta = p[0] / rho;
+                    den = p[1] - beta * p[0] / alpha;
+                }
+                rho = p[0];
+                const double a1 = rho / den;
+                status = 1000;
+                if (!isfinite(rho) || !isfinite(p[1])) status = RL_ERR_NONFINITE;
+                else if (rho <= tol * tol * bb) status = RL_OK;
+                else if (k >= max_iter) status = RL_NOT_CONVERGED;
+                else if (!(a1 > 0.0) || !isfinite(a1)) status = RL_STAGNATED;
+                if (__builtin_expect(status != 1000 || (MANY && bad), 0)) {
+                    done = !(MANY && bad);
+                    iter = k;
+                    res = sqrt(rho / bb);
+                    break;
+                }
+                alpha = a1;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    q[j] = fma(beta, q[j], w[j]);
+                    pv[CG ? j : 0] = fma(beta, pv[CG ? j : 0], g[j]);
+                    gam[j] = fma(alpha, pv[CG ? j : 0], gam[j]);
+                    g[j] = fma(-alpha, q[j], g[j]);
+                }
+            }
+        if (MANY) {
+            __syncthreads();
+            if (bad) return;  // the flag is set
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int s = tid + j * T;
+            if (s < own) {
+                const int c = c0 + s;
+                *reinterpret_cast<double2 *>(io.cs + 4 * (int64_t)c) = make_double2(gam[j], pv[CG ? j : 0]);
+                *reinterpret_cast<double2 *>(io.cr + 4 * (int64_t)c) = make_double2(g[j], q[j]);
+                io.cq[4 * (int64_t)a.qpos[c] + 3] = gam[j];
+            }
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            S->alpha = alpha;
+            S->alpha0 = bb;
+            S->amin = rho;
+            S->ss = nact;
+            S->res = res;
+            S->iter = iter;
+            S->status = done ? status : RL_OK;
+            S->done = done ? 1 : 0;
+        }
+        return;
+    }
     if (k0 == 0) {
         // g0 = Mc gamma0 + q on the projected start
 #pragma unroll
@@ -816,27 +925,36 @@ __global__ void __launch_bounds__(T, 2) k_resident(SolveArgs a, Exchange x, int 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+// form, workgroups (0: no form takes the problem) and lanes per rod
+struct ResPlan {
+    int form, groups, ln;
+};
+constexpr int kResSolo = 1536;  // constraints up to which one workgroup is as fast as several
+constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64 are needed
+
 // The forms: threads, slots, records held by a thread's first and second rod,
 // whether with their normals.
 constexpr int kResForms = 5;
 constexpr int kResSlots[kResForms] = {1024, 1536, 2048, 2560, 3072};
 
 template <int T, int NC, int R1, int R2, bool HELD, bool MANY>
-static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, const ResPlan &p, long long k0,
-                              long long kend)
+static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, const ResCg *cg, const ResPlan &p,
+                              long long k0, long long kend)
 {
     SolveArgs aa = a;
+    ResCg io = cg ? *cg : ResCg{nullptr, nullptr, nullptr};
     int ln = p.ln;
-    void *args[] = {&aa, &x, &ln, &k0, &kend};
-    const void *f = a.gen ? (const void *)k_resident<T, NC, R1, R2, HELD, true, MANY>
-                          : (const void *)k_resident<T, NC, R1, R2, HELD, false, MANY>;
+    void *args[] = {&aa, &x, &io, &ln, &k0, &kend};
+    const void *f = cg ? (const void *)k_resident<T, NC, R1, R2, HELD, kResCg, MANY>
+                    : a.gen ? (const void *)k_resident<T, NC, R1, R2, HELD, kResGeneral, MANY>
+                            : (const void *)k_resident<T, NC, R1, R2, HELD, kResContacts, MANY>;
     // cooperative: all workgroups are resident before any waits for another
     if (MANY) return hipLaunchCooperativeKernel(f, dim3(p.groups), dim3(T), args, 0, st);
     return hipLaunchKernel(f, dim3(1), dim3(T), args, 0, st);
 }
 
 // Form, workgroups and lanes per rod of a problem; groups = 0: none takes it.
-ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered)
+static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered)
 {
     ResPlan p{0, 0, 1};
     if (nc <= 0 || nc >= (1 << 29)) return p;
@@ -879,29 +997,104 @@ ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered)
 }
 
 // the next larger form; false: there is none
-bool resident_larger(ResPlan &p) { return p.groups > 1 && ++p.form < kResForms; }
+static bool resident_larger(ResPlan &p) { return p.groups > 1 && ++p.form < kResForms; }
 
-int64_t resident_words(const ResPlan &p, int64_t nc)
+static int64_t resident_words(const ResPlan &p, int64_t nc)
 {
     return p.groups > 1 ? 2 * (int64_t)p.groups * kResSlots[kResForms - 1] + 2 * nc + 4 * (int64_t)kResMost * kSlot : 0;
 }
 
-hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, unsigned long long *words,
-                           unsigned base, long long k0, long long kend)
+static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, const ResCg *cg,
+                           unsigned long long *words, unsigned base, long long k0, long long kend)
 {
     u64 *at = words ? words + 2 * (int64_t)p.groups * kResSlots[p.form] : nullptr;
     const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail};
     if (p.groups == 1) {
-        if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, p, k0, kend);
-        return launch_form<512, 2048, 8, 4, true, false>(st, a, x, p, k0, kend);
+        if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, cg, p, k0, kend);
+        return launch_form<512, 2048, 8, 4, true, false>(st, a, x, cg, p, k0, kend);
     }
     switch (p.form) {
-    case 0: return launch_form<512, 1024, 8, 0, true, true>(st, a, x, p, k0, kend);
-    case 1: return launch_form<512, 1536, 12, 0, true, true>(st, a, x, p, k0, kend);
-    case 2: return launch_form<512, 2048, 8, 0, true, true>(st, a, x, p, k0, kend);
-    case 3: return launch_form<512, 2560, 16, 0, false, true>(st, a, x, p, k0, kend);
-    default: return launch_form<512, 3072, 12, 0, false, true>(st, a, x, p, k0, kend);
+    case 0: return launch_form<512, 1024, 8, 0, true, true>(st, a, x, cg, p, k0, kend);
+    case 1: return launch_form<512, 1536, 12, 0, true, true>(st, a, x, cg, p, k0, kend);
+    case 2: return launch_form<512, 2048, 8, 0, true, true>(st, a, x, cg, p, k0, kend);
+    case 3: return launch_form<512, 2560, 16, 0, false, true>(st, a, x, cg, p, k0, kend);
+    default: return launch_form<512, 3072, 12, 0, false, true>(st, a, x, cg, p, k0, kend);
     }
+}
+
+// iterations of one launch of a solve on chip (under 20 ms)
+constexpr long long kResChunk = 2048;
+
+// The form of a solve on chip, and its exchange words cleared of any number
+// it could take for one of its own.  groups = 0: the two kernels take it
+// (sampled timing of the loop kernels needs them too).
+static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsigned long long **words)
+{
+    *words = nullptr;
+    plan->groups = 0;
+    if (h->prm.precision != RL_FP64 || (h->prof_every > 0 && !h->arena_on)) return RL_OK;
+    *plan = resident_plan(h, a.n, a.nc, a.ordered);
+    if (plan->groups <= 1) return RL_OK;
+    if (h->xchg_skip > 0) {
+        --h->xchg_skip;
+        plan->groups = 0;
+        return RL_OK;
+    }
+    const size_t bytes = sizeof(unsigned long long) * (size_t)resident_words(*plan, a.nc);
+    if (h->arena_on && h->arena_used + bytes + 512 > kScratchBytes) {
+        plan->groups = 0;  // the list itself fits, the exchange does not
+        return RL_OK;
+    }
+    int err = 0;
+    *words = (unsigned long long *)ws_get(h, kWsXchg, bytes, &err);
+    if (err) return err;
+    // a new buffer, the scratch array (anybody's) or numbers about to run out
+    const bool arena = h->arena_on;
+    if (arena || h->xchg_buf != *words || h->xchg_cap != h->cap[kWsXchg] || h->xchg_num > 0xf0000000u) {
+        RL_HIP(hipMemsetAsync(*words, 0, arena ? bytes : h->cap[kWsXchg], h->stream));
+        h->xchg_buf = arena ? nullptr : *words;
+        h->xchg_cap = arena ? 0 : h->cap[kWsXchg];
+        h->xchg_num = 0;
+    }
+    return RL_OK;
+}
+
+int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, const std::function<hipError_t()> &queue,
+                 bool *solved)
+{
+    hipStream_t st = h->stream;
+    *solved = false;
+    ResPlan plan{0, 0, 1};
+    unsigned long long *words = nullptr;
+    const int rc = resident_prepare(h, a, &plan, &words);
+    if (rc) return rc;
+    // a long solve is cut into launches so that each ends soon
+    for (long long k0 = 0; plan.groups > 0 && !*solved;) {
+        if (words && h->xchg_num > 0xf8000000u) {
+            RL_HIP(hipMemsetAsync(words, 0, sizeof(*words) * (size_t)resident_words(plan, a.nc), st));
+            h->xchg_num = 0;
+        }
+        const unsigned base = h->xchg_num;
+        h->xchg_num += (unsigned)kResChunk + 8;
+        RL_HIP(launch_resident(st, a, plan, cg, words, base, k0, k0 + kResChunk));
+        RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
+        RL_HIP(queue());
+        RL_HIP(hipStreamSynchronize(st));
+        *solved = h->state_host->done != 0;
+        const int fail = h->state_host->fail;
+        if (!fail) {
+            k0 += kResChunk;
+            continue;
+        }
+        // left without a result: more slots, or the two kernels from the start
+        *solved = false;
+        hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);
+        RL_HIP(hipGetLastError());
+        if (fail == 2 && k0 == 0 && resident_larger(plan)) continue;
+        h->xchg_skip = 64;
+        break;
+    }
+    return RL_OK;
 }
 
 }  // namespace rl

@@ -724,43 +724,6 @@ static hipError_t launch_velocity(hipStream_t st, const SolveArgs &a, bool uni, 
     return hipGetLastError();
 }
 
-// iterations of one launch of a solve on chip (under 20 ms)
-constexpr long long kResChunk = 2048;
-
-// The form of a solve on chip, and its exchange words cleared of any number
-// it could take for one of its own.  groups = 0: the two kernels take it
-// (sampled timing of the loop kernels needs them too).
-static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsigned long long **words)
-{
-    *words = nullptr;
-    plan->groups = 0;
-    if (h->prm.precision != RL_FP64 || (h->prof_every > 0 && !h->arena_on)) return RL_OK;
-    *plan = resident_plan(h, a.n, a.nc, a.ordered);
-    if (plan->groups <= 1) return RL_OK;
-    if (h->xchg_skip > 0) {
-        --h->xchg_skip;
-        plan->groups = 0;
-        return RL_OK;
-    }
-    const size_t bytes = sizeof(unsigned long long) * (size_t)resident_words(*plan, a.nc);
-    if (h->arena_on && h->arena_used + bytes + 512 > kScratchBytes) {
-        plan->groups = 0;  // the list itself fits, the exchange does not
-        return RL_OK;
-    }
-    int err = 0;
-    *words = (unsigned long long *)ws_get(h, kWsXchg, bytes, &err);
-    if (err) return err;
-    // a new buffer, the scratch array (anybody's) or numbers about to run out
-    const bool arena = h->arena_on;
-    if (arena || h->xchg_buf != *words || h->xchg_cap != h->cap[kWsXchg] || h->xchg_num > 0xf0000000u) {
-        RL_HIP(hipMemsetAsync(*words, 0, arena ? bytes : h->cap[kWsXchg], h->stream));
-        h->xchg_buf = arena ? nullptr : *words;
-        h->xchg_cap = arena ? 0 : h->cap[kWsXchg];
-        h->xchg_num = 0;
-    }
-    return RL_OK;
-}
-
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
                const int *perm)
 {
@@ -771,44 +734,17 @@ int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamm
     RL_HIP(hipGetLastError());
     long long iters = 0, refreshes = 0;
     bool vel_queued = false, solved = false;
-    ResPlan plan{0, 0, 1};
-    unsigned long long *words = nullptr;
     if (a.nc > 0) {
-        const int rc = resident_prepare(h, a, &plan, &words);
+        const int rc = resident_run(
+            h, a, nullptr, p.tol,
+            [&]() {
+                hipError_t e = gamma_out ? launch_unpack_gamma(st, a, gamma_out) : hipSuccess;
+                if (e == hipSuccess && U && a.n > 0) e = launch_velocity(st, a, uni, F, perm, U);
+                return e;
+            },
+            &solved);
         if (rc) return rc;
-    }
-    // On chip: a long solve is cut into launches so that each ends soon, and
-    // whatever reads the result is queued behind the launch that is expected
-    // to be the last.
-    for (long long k0 = 0; plan.groups > 0 && !solved;) {
-        if (words && h->xchg_num > 0xf8000000u) {
-            RL_HIP(hipMemsetAsync(words, 0, sizeof(*words) * (size_t)resident_words(plan, a.nc), st));
-            h->xchg_num = 0;
-        }
-        const unsigned base = h->xchg_num;
-        h->xchg_num += (unsigned)kResChunk + 8;
-        RL_HIP(launch_resident(st, a, plan, words, base, k0, k0 + kResChunk));
-        RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
-        if (gamma_out) RL_HIP(launch_unpack_gamma(st, a, gamma_out));
-        if (U && a.n > 0) {
-            RL_HIP(launch_velocity(st, a, uni, F, perm, U));
-            vel_queued = true;
-        }
-        RL_HIP(hipStreamSynchronize(st));
-        solved = h->state_host->done != 0;
-        const int fail = h->state_host->fail;
-        if (!fail) {
-            k0 += kResChunk;
-            continue;
-        }
-        // Left without a result (gamma_out, which may be the start, received
-        // that start again): more slots, or the two kernels from the start.
-        vel_queued = solved = false;
-        hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, p.tol, (long long)p.max_iter);
-        RL_HIP(hipGetLastError());
-        if (fail == 2 && k0 == 0 && resident_larger(plan)) continue;
-        h->xchg_skip = 64;
-        break;
+        vel_queued = solved && U && a.n > 0;
     }
     if (solved) {
         iters = h->state_host->iter;

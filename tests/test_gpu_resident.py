@@ -123,3 +123,50 @@ def test_solve_over_several_launches(gpu_lib):
     assert info.status == gpu_lib.OK
     w = oracle.apply_Mc(d, 1.0, s.diam, s.eta, pr, cs, g.cpu().numpy())
     assert np.abs(np.minimum(g.cpu().numpy(), w)).max() <= 1e-8 * 1.01
+
+
+def _rates(d, L, s, pr, cs, V):
+    """D^T V of per-rod velocities."""
+    def at(r, arm):
+        return V[r, :3] + np.cross(V[r, 3:], arm[:, None] * d[r])
+    return np.einsum("ij,ij->i", cs.e, at(pr.pi, cs.arm[:, 0]) - at(pr.pj, cs.arm[:, 1]))
+
+
+@pytest.mark.parametrize("n,nc,lengths", [e for e in EDGES if e[1] in (1, 1023, 1535, 3071, 4000, 17000, 33000)])
+def test_adjoint_at_the_edges(gpu_lib, n, nc, lengths):
+    """lambda solves Mc_AA lambda = D_A^T M U_bar by the oracle's operator: the
+    recurrence stops at 1e-10, and rounding adds at most as much again."""
+    s, d, L, pr, cs = _problem(n, nc, lengths)
+    Ub = np.random.default_rng(n).standard_normal((n, 6))
+    with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-10) as slv:
+        args = (_t(d), _t(L) if lengths else L, _t(pr.pi, torch.int32), _t(pr.pj, torch.int32), _t(cs.e), _t(cs.arm),
+                _t(cs.q))
+        g, _, info = slv.solve_lcp(*args, F=_t(s.force))
+        assert info.status == gpu_lib.OK
+        qb, _, _, _, _, ai = slv.solve_lcp_adjoint(*args, g, _t(Ub), F=_t(s.force), cg_tol=1e-10)
+    assert ai.status == gpu_lib.OK and ai.cg_residual <= 1e-10
+    g, lam = g.cpu().numpy(), -qb.cpu().numpy()
+    act = g > oracle.apply_Mc(d, L, s.diam, s.eta, pr, cs, g)  # Mc g + q
+    b = _rates(d, L, s, pr, cs, oracle.velocity(d, L, s.diam, s.eta, pr, cs, np.zeros(nc), Ub))
+    assert ai.n_active == act.sum() and not lam[~act].any()
+    r = (b - (oracle.apply_Mc(d, L, s.diam, s.eta, pr, cs, lam) - cs.q))[act]
+    assert np.linalg.norm(r) <= 2e-10 * np.linalg.norm(b[act])
+
+
+def test_adjoint_over_several_launches(gpu_lib):
+    """The iteration cap holds exactly on both sides of a launch's end (no
+    residual is small enough to stop before)."""
+    s = rodsynth.make_system(300, seed=3, phi=0.05)
+    d = oracle.directors(s.quat)
+    pr = oracle.pairs(s.x, d, 1.0, s.box, s.diam, s.cutoff)
+    cs = oracle.assemble(s.x, d, 1.0, s.box, s.diam, s.eta, s.dt, pr, s.force)
+    args = (_t(d), 1.0, _t(pr.pi, torch.int32), _t(pr.pj, torch.int32), _t(cs.e), _t(cs.arm), _t(cs.q))
+    Ub = np.random.default_rng(0).standard_normal((300, 6))
+    with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-10) as slv:
+        g, _, info = slv.solve_lcp(*args)
+        assert info.status == gpu_lib.OK
+    for cap in (1, 2047, 2048, 2049):
+        with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-10,
+                            max_iter=cap) as slv:
+            *_, ai = slv.solve_lcp_adjoint(*args, g, _t(Ub), cg_tol=1e-300)
+        assert ai.status == gpu_lib.NOT_CONVERGED and ai.cg_iterations == cap

@@ -184,21 +184,16 @@ static int step_general(rl_ctx *h, int64_t n, double *x, double *quat, const dou
     int64_t np = 0;
     const int *perm = nullptr;
     const double *xs = nullptr, *ds = nullptr, *ls = nullptr;
-    rc = build_pairs_sorted(h, n, x, dir, len, len0, &np, &perm, &xs, &ds, &ls);
+    PairIndex ix;
+    double *Unc = (double *)ws_get(h, kWsStepUnc, sizeof(double) * 6 * n, &err);
+    if (err) return err;
+    rc = build_pairs_sorted(h, n, x, dir, len, len0, F, Unc, &np, &perm, &xs, &ds, &ls, &ix);
     if (rc) return rc;
     if (n_pairs) *n_pairs = np;
     const double *lsv = len ? ls : nullptr;
-    double *Fs = F ? (double *)ws_get(h, kWsFs, sizeof(double) * 6 * n, &err) : nullptr;
-    double *Unc = (double *)ws_get(h, kWsStepUnc, sizeof(double) * 6 * n, &err);
     int *inv = (int *)ws_get(h, kWsInvPerm, sizeof(int) * n, &err);
     double *Uw = U ? U : (double *)ws_get(h, kWsStepU, sizeof(double) * 6 * n, &err);
     if (err) return err;
-    if (F) {
-        RL_HIP(launch_gather6(st, n, perm, F, Fs));
-        RL_HIP(launch_unc(st, n, ds, lsv, len0, p.diam, p.eta, Fs, Unc));
-    } else {
-        RL_HIP(hipMemsetAsync(Unc, 0, sizeof(double) * 6 * n, st));
-    }
     // wall contacts: count first (sizes the concatenated list)
     int64_t nw = 0;
     rc = walls_impl(h, n, xs, ds, lsv, len0, Unc, W, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, &nw);
@@ -224,10 +219,9 @@ static int step_general(rl_ctx *h, int64_t n, double *x, double *quat, const dou
     if (np > 0) {
         RL_HIP(hipMemcpyAsync(cpi, h->buf[kWsStepPi], sizeof(int32_t) * np, hipMemcpyDeviceToDevice, st));
         RL_HIP(hipMemcpyAsync(cpj, h->buf[kWsStepPj], sizeof(int32_t) * np, hipMemcpyDeviceToDevice, st));
-        rc = assemble_impl(h, n, xs, ds, lsv, len0, np, (const int32_t *)h->buf[kWsStepPi],
-                           (const int32_t *)h->buf[kWsStepPj], (const int32_t *)h->buf[kWsStepImg], Fs, phi, ce, carm,
-                           cq);
-        if (rc) return rc;
+        RL_HIP(launch_assemble(st, p, n, xs, ds, lsv, len0, np, (const int32_t *)h->buf[kWsStepPi],
+                               (const int32_t *)h->buf[kWsStepPj], (const int32_t *)h->buf[kWsStepImg], Unc, phi, ce,
+                               carm, cq, h->flag_dev, nullptr));
         RL_HIP(hipMemsetAsync(ckind, 0, (size_t)np, st));
     }
     if (nl > 0) {
@@ -429,11 +423,11 @@ int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs)
         {kWsQidx, sizeof(int) * nc},       {kWsQcnt, sizeof(int) * n},         {kWsG, sizeof(double) * nc},
         {kWsPartial, sizeof(double) * 8 * kConGridMax},
         {kWsCellOf, sizeof(int) * n},      {kWsSorted, sizeof(int) * n},       {kWsXs, sizeof(double) * 3 * n},
-        {kWsDs, sizeof(double) * 3 * n},   {kWsLs, sizeof(double) * n},        {kWsPcnt, sizeof(int) * n},
+        {kWsDs, sizeof(double) * 3 * n},   {kWsLs, sizeof(double) * n},        {kWsStepUnc, sizeof(double) * 6 * n},
         {kWsPoff, sizeof(int) * (n + 1)},  {kWsStepPi, sizeof(int) * nc},      {kWsStepPj, sizeof(int) * nc},
-        {kWsStepImg, sizeof(int) * nc},    {kWsStepFlags, (size_t)nc},                 {kWsStepPhi, sizeof(double) * nc},
-        {kWsStepE, sizeof(double) * 3 * nc}, {kWsStepArm, sizeof(double) * 2 * nc},
-        {kWsStepQ, sizeof(double) * nc},   {kWsStepGamma, sizeof(double) * nc}, {kWsStepU, sizeof(double) * 6 * n},
+        {kWsStepImg, sizeof(int) * nc},    {kWsQrank, sizeof(int) * nc},       {kWsEmit, (size_t)kEmitBytes * nc},
+        {kWsStepGamma, sizeof(double) * nc}, {kWsStepU, sizeof(double) * 6 * n}, {kWsQv, sizeof(double) * nc},
+        {kWsUP, sizeof(double) * nc},      {kWsUQ, sizeof(double) * nc},
         {kWsPP, sizeof(int) * 2 * nc},     {kWsGeo, sizeof(double) * 4 * nc}, {kWsGeo2, sizeof(double) * 2 * nc},  {kWsSt, sizeof(double) * 2 * nc},
         {kWsAlpha, sizeof(double) * 2},    {kWsQpos, sizeof(int) * nc},        {kWsQgeo, sizeof(double) * 4 * nc},
         {kWsStq, sizeof(double) * 2 * nc},
@@ -574,7 +568,10 @@ int rl_step(rl_handle h, int64_t n, double *x, double *quat, const double *len, 
     int64_t np = 0;
     const int *perm = nullptr;
     const double *xs = nullptr, *ds = nullptr, *ls = nullptr;
-    int rc = build_pairs_sorted(h, n, x, dir, len, len0, &np, &perm, &xs, &ds, &ls);
+    PairIndex ix;
+    double *Unc = (double *)ws_get(h, kWsStepUnc, sizeof(double) * 6 * n, &err);
+    if (err) return err;
+    int rc = build_pairs_sorted(h, n, x, dir, len, len0, F, Unc, &np, &perm, &xs, &ds, &ls, &ix);
     if (rc) return rc;
     if (n_pairs) *n_pairs = np;
     if (tape_mode == RL_TAPE_RECORD && np > tape_len) {
@@ -589,31 +586,24 @@ int rl_step(rl_handle h, int64_t n, double *x, double *quat, const double *len, 
     }
     RL_REQUIRE(tape_mode == RL_TAPE_NONE || np == 0 || gamma_tape, "rl_step: NULL gamma_tape");
     const int64_t nb = np > 0 ? np : 1;
-    double *phi = (double *)ws_get(h, kWsStepPhi, sizeof(double) * nb, &err);
-    double *e = (double *)ws_get(h, kWsStepE, sizeof(double) * 3 * nb, &err);
-    double *arm = (double *)ws_get(h, kWsStepArm, sizeof(double) * 2 * nb, &err);
-    double *q = (double *)ws_get(h, kWsStepQ, sizeof(double) * nb, &err);
+    // the geometry goes straight into the solve's records; the warm start and
+    // the stress read it too
+    const bool geom = warm || (extra && extra->stress);
+    double *phi = geom ? (double *)ws_get(h, kWsStepPhi, sizeof(double) * nb, &err) : nullptr;
+    double *e = geom ? (double *)ws_get(h, kWsStepE, sizeof(double) * 3 * nb, &err) : nullptr;
+    double *arm = geom ? (double *)ws_get(h, kWsStepArm, sizeof(double) * 2 * nb, &err) : nullptr;
     double *gamma = (double *)ws_get(h, kWsStepGamma, sizeof(double) * nb, &err);
-    double *Fs = F ? (double *)ws_get(h, kWsFs, sizeof(double) * 6 * n, &err) : nullptr;
     double *Uw = U ? U : (double *)ws_get(h, kWsStepU, sizeof(double) * 6 * n, &err);
     if (err) return err;
-    if (F) RL_HIP(launch_gather6(h->stream, n, perm, F, Fs));
     const double *lsv = len ? ls : nullptr;
     const int32_t *pi = (const int32_t *)h->buf[kWsStepPi], *pj = (const int32_t *)h->buf[kWsStepPj];
     const int32_t *img = (const int32_t *)h->buf[kWsStepImg];
-    rc = assemble_impl(h, n, xs, ds, lsv, len0, np, pi, pj, img, Fs, phi, e, arm, q);
-    if (rc) return rc;
     const StepList L{n, np, 0, np, perm, pi, pj, img, ds, e, arm, phi, nullptr, nullptr};
-    if (tape_mode == RL_TAPE_REPLAY && np > 0) {
-        RL_HIP(hipMemcpyAsync(gamma, gamma_tape, sizeof(double) * np, hipMemcpyDeviceToDevice, h->stream));
-    } else if (warm) {
-        rc = warm_lookup(h, L, gamma);
-        if (rc) return rc;
-    } else {
-        RL_HIP(hipMemsetAsync(gamma, 0, sizeof(double) * nb, h->stream));
-    }
     SolveArgs a;
-    rc = prepare_solve(h, n, ds, lsv, len0, np, pi, pj, e, arm, q, gamma, &a, true);
+    rc = prepare_step(h, n, xs, ds, lsv, len0, np, pi, pj, img, Unc, ix,
+                      tape_mode == RL_TAPE_REPLAY ? gamma_tape : nullptr, phi, e, arm, &a);
+    if (!rc && warm) rc = warm_lookup(h, L, gamma);
+    if (!rc) rc = prepare_finish(h, a, warm ? gamma : nullptr);
     if (rc) return rc;
     a.ordered = true;
     rc = solve_impl(h, a, F, Uw, tape_mode != RL_TAPE_NONE && np > 0 ? gamma_tape : gamma, info, perm);
@@ -683,7 +673,10 @@ int rl_step_adjoint(rl_handle h, int64_t n, const double *x, const double *quat,
     int64_t np = 0;
     const int *perm = nullptr;
     const double *xs = nullptr, *ds = nullptr, *ls = nullptr;
-    int rc = build_pairs_sorted(h, n, x, dir, len, len0, &np, &perm, &xs, &ds, &ls);
+    PairIndex ix;
+    double *Unc = (double *)ws_get(h, kWsStepUnc, sizeof(double) * 6 * n, &err);
+    if (err) return err;
+    int rc = build_pairs_sorted(h, n, x, dir, len, len0, F, Unc, &np, &perm, &xs, &ds, &ls, &ix);
     if (rc) return rc;
     if (gamma_tape && tape_len != np) {
         set_error("rl_step_adjoint: tape of %lld values for a step with %lld constraints", (long long)tape_len,
@@ -691,12 +684,6 @@ int rl_step_adjoint(rl_handle h, int64_t n, const double *x, const double *quat,
         return RL_ERR_ARG;
     }
     const int64_t nb = np > 0 ? np : 1;
-    double *phi = (double *)ws_get(h, kWsStepPhi, sizeof(double) * nb, &err);
-    double *e = (double *)ws_get(h, kWsStepE, sizeof(double) * 3 * nb, &err);
-    double *arm = (double *)ws_get(h, kWsStepArm, sizeof(double) * 2 * nb, &err);
-    double *q = (double *)ws_get(h, kWsStepQ, sizeof(double) * nb, &err);
-    double *gamma = (double *)ws_get(h, kWsStepGamma, sizeof(double) * nb, &err);
-    double *Fs = F ? (double *)ws_get(h, kWsFs, sizeof(double) * 6 * n, &err) : nullptr;
     double *Uc = (double *)ws_get(h, kWsStepU, sizeof(double) * 6 * n, &err);
     double *Ubar = (double *)ws_get(h, kWsAdjUbar, sizeof(double) * 6 * n, &err);
     double *qbd = (double *)ws_get(h, kWsAdjQbd, sizeof(double) * 4 * n, &err);
@@ -707,18 +694,12 @@ int rl_step_adjoint(rl_handle h, int64_t n, const double *x, const double *quat,
     double *dbar = (double *)ws_get(h, kWsAdjDbar, sizeof(double) * 6 * nb, &err);
     double *gbar = (double *)ws_get(h, kWsAdjGbar, sizeof(double) * 9 * nb, &err);
     if (err) return err;
-    if (F) RL_HIP(launch_gather6(st, n, perm, F, Fs));
     const double *lsv = len ? ls : nullptr;
     const int32_t *pi = (const int32_t *)h->buf[kWsStepPi], *pj = (const int32_t *)h->buf[kWsStepPj];
     const int32_t *img = (const int32_t *)h->buf[kWsStepImg];
-    rc = assemble_impl(h, n, xs, ds, lsv, len0, np, pi, pj, img, Fs, phi, e, arm, q);
-    if (rc) return rc;
-    if (gamma_tape && np > 0)
-        RL_HIP(hipMemcpyAsync(gamma, gamma_tape, sizeof(double) * np, hipMemcpyDeviceToDevice, st));
-    else
-        RL_HIP(hipMemsetAsync(gamma, 0, sizeof(double) * nb, st));
     SolveArgs a;
-    rc = prepare_solve(h, n, ds, lsv, len0, np, pi, pj, e, arm, q, gamma, &a, true);
+    rc = prepare_step(h, n, xs, ds, lsv, len0, np, pi, pj, img, Unc, ix, gamma_tape, nullptr, nullptr, nullptr, &a);
+    if (!rc) rc = prepare_finish(h, a, nullptr);
     if (rc) return rc;
     a.ordered = true;
     rl_solve_info si{0, 0.0, 0.0, RL_OK, 0};

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
+#include <type_traits>
 
 #include "rl_vec.hpp"
 
@@ -203,24 +204,17 @@ __device__ __forceinline__ unsigned spread3(unsigned v)
     return (v & 1u) | ((v & 2u) << 2) | ((v & 4u) << 4);
 }
 
-// cell_of[i] = the rod's cell, followed by `fb` bits (0, 3, 6 or 9) of the
-// Morton code of its sub-cell (fb / 3 bits per direction) when the rods are
-// to be ordered by position inside their cells as well.
-__global__ void k_bin(int64_t n, const double *__restrict__ x, const double *__restrict__ dir, GridDev g, int fb,
-                      int *__restrict__ cell_of, int *__restrict__ cell_cnt, int *__restrict__ err)
+// The rod's cell (in id) and the same followed by `fb` bits (0, 3, 6 or 9) of
+// the Morton code of its sub-cell (fb / 3 bits per direction) for rods that
+// are to be ordered by position inside their cells as well.  A rod that is not
+// finite goes to cell 0, so that the cell counts stay consistent.
+__device__ __forceinline__ unsigned rod_bin(const V3 &xi, const V3 &di, const GridDev &g, int fb, int &id, int &err)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const V3 xi = load3(x + 3 * i), di = load3(dir + 3 * i);
     const double xs[3] = {xi.x, xi.y, xi.z};
-    bool finite = isfinite(xi.x) && isfinite(xi.y) && isfinite(xi.z) && isfinite(di.x) && isfinite(di.y) &&
-                  isfinite(di.z);
-    if (!finite) {
-        // keep the cell counts consistent with the scatter that follows
-        atomicOr(err, 1);
-        cell_of[i] = 0;
-        atomicAdd(cell_cnt, 1);
-        return;
+    id = 0;
+    if (!(isfinite(xi.x) && isfinite(xi.y) && isfinite(xi.z) && isfinite(di.x) && isfinite(di.y) && isfinite(di.z))) {
+        err = 1;
+        return 0;
     }
     int kc[3];
     unsigned sub = 0;
@@ -235,22 +229,115 @@ __global__ void k_bin(int64_t n, const double *__restrict__ x, const double *__r
             sub |= spread3((unsigned)f << (3 - per)) << a;
         }
     }
-    if (!inside) atomicOr(err, 2);
-    const int id = (kc[0] * g.nc[1] + kc[1]) * g.nc[2] + kc[2];
-    cell_of[i] = (int)(((unsigned)id << fb) | (sub >> (9 - fb)));
-    atomicAdd(cell_cnt + id, 1);
+    err = inside ? 0 : 2;
+    id = (kc[0] * g.nc[1] + kc[1]) * g.nc[2] + kc[2];
+    return ((unsigned)id << fb) | (sub >> (9 - fb));
 }
 
+// bins, cell counts, and (rank may be null) the rod's place in its cell
+__global__ void k_bin(int64_t n, const double *__restrict__ x, const double *__restrict__ dir, GridDev g, int fb,
+                      int *__restrict__ cell_of, int *__restrict__ cell_cnt, int *__restrict__ rank,
+                      int *__restrict__ err)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    int id, e;
+    const unsigned code = rod_bin(load3(x + 3 * i), load3(dir + 3 * i), g, fb, id, e);
+    if (e) atomicOr(err, e);
+    cell_of[i] = (int)code;
+    const int r = atomicAdd(cell_cnt + id, 1);
+    if (rank) rank[i] = r;
+}
+
+// counts of a search, zero when it starts: pairs by rod on either side,
+// pairs emitted, errors
+struct PairCounts {
+    int *p, *q;
+    unsigned long long *emitted;
+    int *err;
+};
+
+// Small systems in cell order by one workgroup: bins, cell offsets and the
+// order (by bin, then index) in one launch, with the counts of the search
+// cleared on the way.  Bound by latency: of 12 launches (bins, scan, radix
+// sort, clears) each takes 1.2 to 5.5 us however little it does.  Up to 4,096
+// rods and cells, the LDS of one workgroup; the sort is a bitonic network of
+// 78 steps there, and the library's radix sort takes over above.
+constexpr int kCellsOne = 4096, kCellsBlock = 1024;
+
+__global__ void __launch_bounds__(kCellsBlock)
+    k_cells_one(int n, const double *__restrict__ x, const double *__restrict__ dir, GridDev g, int fb, int ncell,
+                int *__restrict__ cell_start, int *__restrict__ sorted, PairCounts c)
+{
+    __shared__ unsigned long long key[kCellsOne];
+    __shared__ int cnt[kCellsOne], part[kCellsBlock / 64], bad;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int m = 2 * kCellsBlock;
+    while (m < n) m *= 2;
+    for (int i = tid; i < kCellsOne; i += kCellsBlock) cnt[i] = 0;
+    if (tid == 0) bad = 0;
+    __syncthreads();
+    int err = 0;
+    for (int i = tid; i < m; i += kCellsBlock) {
+        unsigned long long k = ~0ull;
+        if (i < n) {
+            int id, e;
+            const unsigned code = rod_bin(load3(x + 3 * i), load3(dir + 3 * i), g, fb, id, e);
+            err |= e;
+            atomicAdd(cnt + id, 1);
+            k = ((unsigned long long)code << 32) | (unsigned)i;
+            c.p[i] = 0;
+            c.q[i] = 0;
+        }
+        key[i] = k;
+    }
+    if (err) atomicOr(&bad, err);
+    __syncthreads();
+    int v[4], incl;
+    for (int u = 0; u < 4; ++u) v[u] = cnt[4 * tid + u];
+    incl = v[0] + v[1] + v[2] + v[3];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += t;
+    }
+    if (lane == 63) part[wave] = incl;
+    __syncthreads();
+    int run = incl - (v[0] + v[1] + v[2] + v[3]);
+    for (int w = 0; w < wave; ++w) run += part[w];
+    for (int u = 0; u < 4; ++u) {
+        if (4 * tid + u <= ncell) cell_start[4 * tid + u] = run;
+        run += v[u];
+    }
+    if (tid == kCellsBlock - 1 && ncell == kCellsOne) cell_start[ncell] = run;
+    if (tid == 0) {
+        *c.emitted = 0;
+        *c.err = bad;
+    }
+    for (int k = 2; k <= m; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = tid; t < m / 2; t += kCellsBlock) {
+                const int a = 2 * t - (t & (j - 1)), b = a + j;
+                const unsigned long long ka = key[a], kb = key[b];
+                if ((ka > kb) == ((a & k) == 0)) {
+                    key[a] = kb;
+                    key[b] = ka;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < n; i += kCellsBlock) sorted[i] = (int)(unsigned)key[i];
+}
 
 __global__ void k_scatter(int64_t n, const double *__restrict__ x, const double *__restrict__ dir,
                           const double *__restrict__ len, double len0, const int *__restrict__ cell_of,
-                          const int *__restrict__ cell_start, int *__restrict__ cell_cur, int *__restrict__ sorted,
+                          const int *__restrict__ cell_start, const int *__restrict__ rank, int *__restrict__ sorted,
                           double *__restrict__ xs, double *__restrict__ ds, double *__restrict__ ls)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int c = cell_of[i];
-    const int slot = cell_start[c] + atomicAdd(cell_cur + c, 1);
+    const int slot = cell_start[c] + rank[i];
     sorted[slot] = (int)i;
     store3(xs + 3 * (int64_t)slot, load3(x + 3 * i));
     store3(ds + 3 * (int64_t)slot, load3(dir + 3 * i));
@@ -310,8 +397,8 @@ __device__ __forceinline__ void stage_cell(CellStage &S, int q0, int m, V3 shift
 
 // Pass modes: count pairs per rod, fill the per-rod slots, or emit every
 // pair once as a key (pi, pj, shift) with its flags at a slot reserved per
-// flush (the list is put in canonical order afterwards: bucketed by pi, then
-// sorted per rod).
+// flush, counted on both rods (the list is put in canonical order afterwards:
+// bucketed by pi, then ranked in its rod's bucket).
 enum PairPass : int { kPairCount = 0, kPairFill = 1, kPairEmit = 2 };
 
 // exclusive prefix of v over the workgroup; tot = the sum (lds: 5 ints)
@@ -347,10 +434,10 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
                                                       const int *__restrict__ cell_start, int *__restrict__ pcnt,
                                                       const int *__restrict__ poff, int32_t *__restrict__ pi,
                                                       int32_t *__restrict__ pj, int32_t *__restrict__ img,
-                                                      uint8_t *__restrict__ flags, unsigned long long *ecount,
+                                                      uint8_t *__restrict__ flags, PairCounts ec,
                                                       unsigned long long *__restrict__ ekeys,
-                                                      uint8_t *__restrict__ eflags, int64_t ecap, int kshift,
-                                                      int split)
+                                                      uint8_t *__restrict__ eflags, int2 *__restrict__ erank,
+                                                      int64_t ecap, int kshift, int split)
 {
     constexpr bool FILL = PASS == kPairFill;
     __shared__ CellStage H, Nb;
@@ -463,22 +550,23 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
                             pi[o] = H.idx[a];
                             pj[o] = Nb.idx[b];
                             img[o] = packed;
-                            flags[o] = (uint8_t)fl;
+                            if (flags) flags[o] = (uint8_t)fl;
                         }
                     }
                     if (PASS == kPairEmit) {
                         int excl = 0, tot = 0;
                         block_excl_scan(mine, excl, tot, scan_lds);
-                        if (threadIdx.x == 0) ebase = tot > 0 ? atomicAdd(ecount, (unsigned long long)tot) : 0ull;
+                        if (threadIdx.x == 0) ebase = tot > 0 ? atomicAdd(ec.emitted, (unsigned long long)tot) : 0ull;
                         __syncthreads();
                         unsigned long long o = ebase + (unsigned long long)excl;
                         for (int u = threadIdx.x; u < nq; u += kPairBlock) {
                             const unsigned v = (unsigned)queue[u];
                             if (!(v >> 31)) continue;
                             if (o < (unsigned long long)ecap) {
-                                const int a = (v >> 16) & 0xff, b = v & 0xff;
-                                ekeys[o] = ((unsigned long long)(unsigned)H.idx[a] << kshift) |
-                                           ((unsigned long long)(unsigned)Nb.idx[b] << 12) | (unsigned long long)packed;
+                                const int i = H.idx[(v >> 16) & 0xff], j = Nb.idx[v & 0xff];
+                                erank[o] = make_int2(atomicAdd(ec.p + i, 1), ec.q ? atomicAdd(ec.q + j, 1) : 0);
+                                ekeys[o] = ((unsigned long long)(unsigned)i << kshift) |
+                                           ((unsigned long long)(unsigned)j << 12) | (unsigned long long)packed;
                                 eflags[o] = (uint8_t)((v >> 24) & 15u);
                             }
                             ++o;
@@ -494,47 +582,72 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
     }
 }
 
-// Emitted pair keys (pi, pj, shift) into the canonical order: bucketed by
-// pi (a histogram, its scan, a scatter), then each rod's short list sorted
-// by (pj, shift).  The keys are distinct, so the result is the order of the
-// keys whatever order the scatter's atomics took.
-__global__ void k_pair_hist(int64_t m, const unsigned long long *__restrict__ keys, int shift, int *__restrict__ cnt)
+// Emitted pair keys (pi, pj, shift) into the canonical order: bucketed by pi
+// with the ranks that the counting gave, then each pair to the place of its
+// key among its bucket's (a lane per pair reads the bucket: 4.7 pairs on
+// average at 100,000 rods, 468,000 pairs).  The keys are distinct, so the
+// result is the order of the keys whatever order the counting took.  qrank
+// (may be null): the place of the pair in the Q list of its second rod.
+__global__ void k_pair_bucket(int64_t m, const unsigned long long *__restrict__ keys, const int2 *__restrict__ rank,
+                              int kshift, const int *__restrict__ off, int *__restrict__ slot)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (t >= m) return;
-    atomicAdd(cnt + (int)(keys[t] >> shift), 1);
+    slot[off[keys[t] >> kshift] + rank[t].x] = (int)t;
 }
 
-__global__ void k_pair_scatter(int64_t m, const unsigned long long *__restrict__ keys,
-                               const uint8_t *__restrict__ kflags, int ibits, const int *__restrict__ off,
-                               int *__restrict__ cur, int32_t *__restrict__ pi, int32_t *__restrict__ pj,
-                               int32_t *__restrict__ img, uint8_t *__restrict__ flags)
+__global__ void k_pair_place(int64_t m, const unsigned long long *__restrict__ keys,
+                             const uint8_t *__restrict__ kflags, const int2 *__restrict__ rank, int kshift,
+                             const int *__restrict__ off, const int *__restrict__ slot, int32_t *__restrict__ pi,
+                             int32_t *__restrict__ pj, int32_t *__restrict__ img, uint8_t *__restrict__ flags,
+                             int *__restrict__ qrank)
 {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= m) return;
+    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (s >= m) return;
+    const int t = slot[s];
     const unsigned long long k = keys[t];
-    const int a = (int)(k >> (ibits + 12));
-    const int slot = off[a] + atomicAdd(cur + a, 1);
-    pi[slot] = a;
-    pj[slot] = (int32_t)((k >> 12) & ((1ull << ibits) - 1ull));
-    img[slot] = (int32_t)(k & 0xfffull);
-    flags[slot] = kflags[t];
+    const int a = (int)(k >> kshift), b = off[a], e = off[a + 1];
+    int c = b;
+    for (int u = b; u < e; ++u) c += keys[slot[u]] < k;
+    pi[c] = a;
+    pj[c] = (int32_t)((k >> 12) & ((1ull << (kshift - 12)) - 1ull));
+    img[c] = (int32_t)(k & 0xfffull);
+    if (flags) flags[c] = kflags[t];
+    if (qrank) qrank[c] = rank[t].y;
 }
 
-// copies of centres, directors, lengths (and forces) in cell order
+// velocity of a rod under its external force and torque alone
+__device__ __forceinline__ void rod_unc(const Mob &m, const V3 &d, const V3 &f, const V3 &tq, double *out)
+{
+    store3(out, m.aperp * f + ((m.apar - m.aperp) * dot(d, f)) * d);
+    store3(out + 3, m.rperp * tq);  // axial rotational mobility equals the normal one
+}
+
+// copies of centres, directors and lengths in cell order, and the velocities
+// of the forces (Unc null: not asked for)
 __global__ void k_gather_rods(int64_t n, const int *__restrict__ perm, const double *__restrict__ x,
                               const double *__restrict__ dir, const double *__restrict__ len, double len0,
-                              double *__restrict__ xs, double *__restrict__ ds, double *__restrict__ ls)
+                              double *__restrict__ xs, double *__restrict__ ds, double *__restrict__ ls, Mob mob,
+                              double diam, double eta, const double *__restrict__ F, double *__restrict__ Unc)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (t >= n) return;
     const int64_t i = perm[t];
+    const V3 d = load3(dir + 3 * i);
     store3(xs + 3 * t, load3(x + 3 * i));
-    store3(ds + 3 * t, load3(dir + 3 * i));
+    store3(ds + 3 * t, d);
     ls[t] = len ? len[i] : len0;
+    if (!Unc) return;
+    V3 f = v3(0, 0, 0), tq = v3(0, 0, 0);
+    if (F) {
+        f = load3(F + 6 * i);
+        tq = load3(F + 6 * i + 3);
+    }
+    rod_unc(len ? mobility_of(len[i], diam, eta) : mob, d, f, tq, Unc + 6 * t);
 }
 
-// order each rod's pairs by (pj, img).  Up to 32 pairs (every rod at the paper's densities)
+// order each rod's pairs by (pj, img) (lists from the counting and filling
+// passes).  Up to 32 pairs (every rod at the paper's densities)
 // are sorted in registers by an odd-even transposition network over keys
 // (pj, img, flags) packed into 64 bits, so the loads go out together and the
 // stores once; longer lists take an insertion sort in memory.
@@ -555,7 +668,8 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
         for (int k = 0; k < kSortRegs; ++k)
             key[k] = k < cnt ? ((unsigned long long)(unsigned)pj[b + k] << 16) |
-                                   ((unsigned long long)(unsigned)img[b + k] << 4) | (unsigned long long)flags[b + k]
+                                   ((unsigned long long)(unsigned)img[b + k] << 4) |
+                                   (unsigned long long)(flags ? flags[b + k] : 0)
                              : ~0ull;
 #pragma unroll
         for (int r = 0; r < kSortRegs; ++r)
@@ -571,24 +685,24 @@ __global__ void __launch_bounds__(256)
             if (k < cnt) {
                 pj[b + k] = (int32_t)(key[k] >> 16);
                 img[b + k] = (int32_t)((key[k] >> 4) & 0xfffull);
-                flags[b + k] = (uint8_t)(key[k] & 15ull);
+                if (flags) flags[b + k] = (uint8_t)(key[k] & 15ull);
             }
         return;
     }
     for (int k = b + 1; k < e; ++k) {
         const int32_t kj = pj[k], ki = img[k];
-        const uint8_t kf = flags[k];
+        const uint8_t kf = flags ? flags[k] : 0;
         const long long key = ((long long)kj << 12) | ki;
         int m = k - 1;
         while (m >= b && (((long long)pj[m] << 12) | img[m]) > key) {
             pj[m + 1] = pj[m];
             img[m + 1] = img[m];
-            flags[m + 1] = flags[m];
+            if (flags) flags[m + 1] = flags[m];
             --m;
         }
         pj[m + 1] = kj;
         img[m + 1] = ki;
-        flags[m + 1] = kf;
+        if (flags) flags[m + 1] = kf;
     }
 }
 
@@ -608,28 +722,14 @@ __global__ void k_len_max(int64_t n, const double *__restrict__ len, unsigned lo
 
 static inline unsigned grid_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-__global__ void k_gather6(int64_t n, const int *__restrict__ perm, const double *__restrict__ src,
-                          double *__restrict__ dst)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int64_t i = perm[t];
-    for (int a = 0; a < 6; ++a) dst[6 * t + a] = src[6 * i + a];
-}
-
-hipError_t launch_gather6(hipStream_t st, int64_t n, const int *perm, const double *src, double *dst)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather6, dim3(grid_of(n)), dim3(kBlock), 0, st, n, perm, src, dst);
-    return hipGetLastError();
-}
-
 // Shared body of the two pair searches.  internal = false: canonical list
 // in the caller's rod numbering; internal = true: rods renumbered in cell
-// order (stable by caller index), h's workspace keeps the order and copies.
+// order (stable by caller index), h's workspace keeps the order and copies,
+// Unc the velocities of the forces F, and ix where the constraints of each rod
+// are.
 static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
-                      bool internal, int64_t capacity, int32_t *pi, int32_t *pj, int32_t *img, uint8_t *flags,
-                      int64_t *n_pairs)
+                      bool internal, const double *F, double *Unc, int64_t capacity, int32_t *pi, int32_t *pj,
+                      int32_t *img, uint8_t *flags, int64_t *n_pairs, PairIndex *ix)
 {
     hipStream_t st = h->stream;
     const rl_params &p = h->prm;
@@ -638,8 +738,8 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
     if (n == 0) return RL_OK;
     // longest rod
     double Lmax = len0;
-    RL_HIP(hipMemsetAsync(h->flag_dev, 0, sizeof(int) * 4, st));
     if (len) {
+        RL_HIP(hipMemsetAsync(h->flag_dev, 0, sizeof(int) * 4, st));
         auto *lm = (unsigned long long *)ws_get(h, kWsLenMax, sizeof(unsigned long long), &werr);
         if (werr) return werr;
         RL_HIP(hipMemsetAsync(lm, 0, sizeof(unsigned long long), st));
@@ -680,18 +780,21 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         return RL_ERR_ARG;
     }
     int *cell_of = (int *)ws_get(h, kWsCellOf, sizeof(int) * n, &werr);
-    int *cell_cnt = (int *)ws_get(h, kWsCellCnt, sizeof(int) * ncell, &werr);
+    // emitted (8 bytes), errors, then the counts by cell and by rod
+    int *counts = (int *)ws_get(h, kWsPairCnt, sizeof(int) * (4 + ncell + 2 * n), &werr);
     int *cell_start = (int *)ws_get(h, kWsCellStart, sizeof(int) * (ncell + 1), &werr);
-    int *cell_cur = (int *)ws_get(h, kWsCellCur, sizeof(int) * ncell, &werr);
+    int *cell_rank = internal ? nullptr : (int *)ws_get(h, kWsCellCur, sizeof(int) * n, &werr);
     int *sorted = (int *)ws_get(h, kWsSorted, sizeof(int) * n, &werr);
     int *cell_key = internal ? (int *)ws_get(h, kWsCellKey, sizeof(int) * n, &werr) : nullptr;
     double *xs = (double *)ws_get(h, kWsXs, sizeof(double) * 3 * n, &werr);
     double *ds = (double *)ws_get(h, kWsDs, sizeof(double) * 3 * n, &werr);
     double *ls = (double *)ws_get(h, kWsLs, sizeof(double) * n, &werr);
-    int *pcnt = (int *)ws_get(h, kWsPcnt, sizeof(int) * n, &werr);
     int *poff = (int *)ws_get(h, kWsPoff, sizeof(int) * (n + 1), &werr);
+    int *qoff = internal ? (int *)ws_get(h, kWsQptr, sizeof(int) * (n + 1), &werr) : nullptr;
     int64_t *tot = (int64_t *)ws_get(h, kWsScan, sizeof(int64_t) * 2, &werr);
     if (werr) return werr;
+    int *cell_cnt = counts + 4, *pcnt = cell_cnt + ncell;
+    const PairCounts ec{pcnt, internal ? pcnt + n : nullptr, (unsigned long long *)counts, counts + 2};
 
     // internal order: by cell, then along a Morton curve of 8^3 sub-cells
     // inside the cell (fewer when the cell ids leave no room in 31 bits), so
@@ -700,27 +803,28 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
     int cbits = 1;
     while ((1LL << cbits) < ncell) ++cbits;
     const int fb = internal ? std::min(9, (31 - cbits) / 3 * 3) : 0;
-    RL_HIP(hipMemsetAsync(cell_cnt, 0, sizeof(int) * ncell, st));
-    hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, fb, cell_of, cell_cnt,
-                       h->flag_dev);
-    RL_HIP(hipGetLastError());
-    {
-        const int rc = device_scan(h, cell_cnt, ncell, cell_start, nullptr);
-        if (rc) return rc;
-    }
-    if (internal) {
-        int rc = stable_sort_by_key(h, n, cell_of, cbits + fb, cell_key, sorted);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_gather_rods, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)sorted, x, dir, len,
-                           len0, xs, ds, ls);
+    if (internal && n <= kCellsOne && ncell <= kCellsOne) {
+        hipLaunchKernelGGL(k_cells_one, dim3(1), dim3(kCellsBlock), 0, st, (int)n, x, dir, g, fb, (int)ncell,
+                           cell_start, sorted, ec);
+        RL_HIP(hipGetLastError());
     } else {
-        RL_HIP(hipMemsetAsync(cell_cur, 0, sizeof(int) * ncell, st));
-        hipLaunchKernelGGL(k_scatter, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, len, len0, cell_of,
-                           cell_start, cell_cur, sorted, xs, ds, ls);
+        RL_HIP(hipMemsetAsync(counts, 0, sizeof(int) * (4 + ncell + 2 * n), st));
+        hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, fb, cell_of, cell_cnt,
+                           cell_rank, ec.err);
+        RL_HIP(hipGetLastError());
+        int rc = device_scan(h, cell_cnt, ncell, cell_start, nullptr);
+        if (!rc && internal) rc = stable_sort_by_key(h, n, cell_of, cbits + fb, cell_key, sorted);
+        if (rc) return rc;
     }
+    if (internal)
+        hipLaunchKernelGGL(k_gather_rods, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)sorted, x, dir, len,
+                           len0, xs, ds, ls, mobility_of(len ? 1.0 : len0, p.diam, p.eta), p.diam, p.eta, F, Unc);
+    else
+        hipLaunchKernelGGL(k_scatter, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, len, len0, cell_of,
+                           cell_start, (const int *)cell_rank, sorted, xs, ds, ls);
     RL_HIP(hipGetLastError());
-    // one pass emitting keys (pi, pj, shift), then buckets by pi and a per-rod
-    // sort into the canonical order; rod counts above 2^26 do not fit the
+    // one pass emitting keys (pi, pj, shift), then buckets by pi and ranks in
+    // them for the canonical order; rod counts above 2^26 do not fit the
     // 64-bit key and take the counting and filling passes instead
     int ibits = 1;
     while ((1LL << ibits) < n) ++ibits;
@@ -733,45 +837,48 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
     // with six)
     const int split = (int)std::max<int64_t>(1, std::min<int64_t>(RL_PAIR_SPLIT, 4096 / ncell));
     const dim3 egrid((unsigned)(ncell * split));
-    auto *none_u64 = (unsigned long long *)nullptr;
-    auto *none_u8 = (uint8_t *)nullptr;
+    const bool one = n <= kScanOne;
+    const int kshift = ibits + 12;
+    unsigned long long *ekeys = nullptr;
+    uint8_t *eflags = nullptr;
+    int2 *erank = nullptr;
+    int *pslot = nullptr;
+    auto search = [&](auto pass, dim3 grid, int nsplit, int64_t ecap) {
+        constexpr int PASS = decltype(pass)::value;
+        if (internal)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<PASS, true>), grid, pblock, 0, st, g, p.diam, p.cutoff, sorted,
+                               xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags, ec, ekeys, eflags,
+                               erank, ecap, kshift, nsplit);
+        else
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<PASS, false>), grid, pblock, 0, st, g, p.diam, p.cutoff,
+                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags, ec, ekeys,
+                               eflags, erank, ecap, kshift, nsplit);
+        return hipGetLastError();
+    };
+    bool reported = false;
     if (emit) {
-        const int64_t ecap = capacity > 0 ? capacity : 0;
-        auto *ecount = (unsigned long long *)ws_get(h, kWsEmitCount, sizeof(unsigned long long), &werr);
-        auto *ekeys = (unsigned long long *)ws_get(h, kWsEmitKeys, sizeof(unsigned long long) * (ecap > 0 ? ecap : 1), &werr);
-        auto *eflags = (uint8_t *)ws_get(h, kWsEmitFlags, (size_t)(ecap > 0 ? ecap : 1), &werr);
+        const int64_t ecap = capacity > 0 ? capacity : 0, eb = ecap > 0 ? ecap : 1;
+        ekeys = (unsigned long long *)ws_get(h, kWsEmit, (size_t)kEmitBytes * eb, &werr);
         if (werr) return werr;
-        RL_HIP(hipMemsetAsync(ecount, 0, sizeof(unsigned long long), st));
-        const int kshift = ibits + 12;
-        if (internal)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<kPairEmit, true>), egrid, pblock, 0, st, g, p.diam, p.cutoff,
-                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)nullptr, (int32_t *)nullptr,
-                               (int32_t *)nullptr, (int32_t *)nullptr, none_u8, ecount, ekeys, eflags, ecap, kshift,
-                               split);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<kPairEmit, false>), egrid, pblock, 0, st, g, p.diam, p.cutoff,
-                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)nullptr, (int32_t *)nullptr,
-                               (int32_t *)nullptr, (int32_t *)nullptr, none_u8, ecount, ekeys, eflags, ecap, kshift,
-                               split);
-        RL_HIP(hipGetLastError());
-        RL_HIP(hipMemcpyAsync(h->host_scratch, ecount, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        erank = (int2 *)(ekeys + eb);
+        pslot = (int *)(erank + eb);
+        eflags = (uint8_t *)(pslot + eb);
+        RL_HIP(search(std::integral_constant<int, kPairEmit>{}, egrid, split, ecap));
+        if (one) {
+            // the offsets while the host learns the number of pairs
+            RL_HIP(launch_scan_one(st, n, pcnt, poff, ec.q, qoff, nullptr,
+                                   ScanReport{ec.emitted, ec.err, h->host_scratch}));
+            reported = true;
+        } else {
+            RL_HIP(hipMemcpyAsync(h->host_scratch, counts, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        }
     } else {
-        if (internal)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<kPairCount, true>), pgrid, pblock, 0, st, g, p.diam, p.cutoff,
-                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)nullptr, (int32_t *)nullptr,
-                               (int32_t *)nullptr, (int32_t *)nullptr, none_u8, none_u64, none_u64, none_u8,
-                               (int64_t)0, 0, 1);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<kPairCount, false>), pgrid, pblock, 0, st, g, p.diam, p.cutoff,
-                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)nullptr, (int32_t *)nullptr,
-                               (int32_t *)nullptr, (int32_t *)nullptr, none_u8, none_u64, none_u64, none_u8,
-                               (int64_t)0, 0, 1);
-        RL_HIP(hipGetLastError());
+        RL_HIP(search(std::integral_constant<int, kPairCount>{}, pgrid, 1, 0));
         const int rc = device_scan(h, pcnt, n, poff, tot);
         if (rc) return rc;
         RL_HIP(hipMemcpyAsync(h->host_scratch, tot, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        RL_HIP(hipMemcpyAsync(h->host_scratch + 1, ec.err, sizeof(int), hipMemcpyDeviceToHost, st));
     }
-    RL_HIP(hipMemcpyAsync(h->host_scratch + 1, h->flag_dev, sizeof(int), hipMemcpyDeviceToHost, st));
     RL_HIP(hipStreamSynchronize(st));
     const int64_t total = h->host_scratch[0];
     const int ferr = ((int *)(h->host_scratch + 1))[0];
@@ -794,32 +901,24 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
     }
     if (total == 0) return RL_OK;
     if (emit) {
-        auto *ekeys = (unsigned long long *)h->buf[kWsEmitKeys];
-        auto *eflags = (uint8_t *)h->buf[kWsEmitFlags];
-        RL_HIP(hipMemsetAsync(pcnt, 0, sizeof(int) * n, st));
-        hipLaunchKernelGGL(k_pair_hist, dim3(grid_of(total)), dim3(kBlock), 0, st, total,
-                           (const unsigned long long *)ekeys, ibits + 12, pcnt);
+        if (!reported) {
+            int rc = device_scan(h, pcnt, n, poff, nullptr);
+            if (!rc && internal) rc = device_scan(h, ec.q, n, qoff, nullptr);
+            if (rc) return rc;
+        }
+        int *qrank = internal ? (int *)ws_get(h, kWsQrank, sizeof(int) * total, &werr) : nullptr;
+        if (werr) return werr;
+        hipLaunchKernelGGL(k_pair_bucket, dim3(grid_of(total)), dim3(kBlock), 0, st, total,
+                           (const unsigned long long *)ekeys, (const int2 *)erank, kshift, (const int *)poff, pslot);
         RL_HIP(hipGetLastError());
-        const int rc = device_scan(h, pcnt, n, poff, nullptr);
-        if (rc) return rc;
-        RL_HIP(hipMemsetAsync(pcnt, 0, sizeof(int) * n, st));
-        hipLaunchKernelGGL(k_pair_scatter, dim3(grid_of(total)), dim3(kBlock), 0, st, total,
-                           (const unsigned long long *)ekeys, (const uint8_t *)eflags, ibits, (const int *)poff, pcnt,
-                           pi, pj, img, flags);
+        hipLaunchKernelGGL(k_pair_place, dim3(grid_of(total)), dim3(kBlock), 0, st, total,
+                           (const unsigned long long *)ekeys, (const uint8_t *)eflags, (const int2 *)erank, kshift,
+                           (const int *)poff, (const int *)pslot, pi, pj, img, flags, qrank);
         RL_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_sort_pairs, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)poff, pj, img, flags);
-        RL_HIP(hipGetLastError());
+        if (ix) *ix = PairIndex{poff, qoff, qrank};
         return RL_OK;
     }
-    if (internal)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<kPairFill, true>), pgrid, pblock, 0, st, g, p.diam, p.cutoff, sorted,
-                           xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags, none_u64, none_u64,
-                           none_u8, (int64_t)0, 0, 1);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<kPairFill, false>), pgrid, pblock, 0, st, g, p.diam, p.cutoff,
-                           sorted, xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags, none_u64,
-                           none_u64, none_u8, (int64_t)0, 0, 1);
-    RL_HIP(hipGetLastError());
+    RL_HIP(search(std::integral_constant<int, kPairFill>{}, pgrid, 1, 0));
     hipLaunchKernelGGL(k_sort_pairs, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)poff, pj, img, flags);
     RL_HIP(hipGetLastError());
     return RL_OK;
@@ -887,7 +986,7 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
     RL_HIP(hipMemsetAsync(cell_cnt, 0, sizeof(int) * ncell, st));
     if (n > 0) {
         hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, 0, cell_of, cell_cnt,
-                           h->flag_dev);
+                           (int *)nullptr, h->flag_dev);
         RL_HIP(hipGetLastError());
     }
     {
@@ -900,7 +999,7 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
         const int rc = stable_sort_by_key(h, n, cell_of, cbits, cell_key, sorted);
         if (rc) return rc;
         hipLaunchKernelGGL(k_gather_rods, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)sorted, x, dir, len,
-                           len0, xs, ds, ls);
+                           len0, xs, ds, ls, Mob{}, 0.0, 0.0, (const double *)nullptr, (double *)nullptr);
         RL_HIP(hipGetLastError());
     }
     RL_HIP(hipMemcpyAsync(h->host_scratch + 1, h->flag_dev, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -930,31 +1029,32 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
 int build_pairs_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
                      int64_t capacity, int32_t *pi, int32_t *pj, int32_t *img, uint8_t *flags, int64_t *n_pairs)
 {
-    return pairs_core(h, n, x, dir, len, len0, false, capacity, pi, pj, img, flags, n_pairs);
+    return pairs_core(h, n, x, dir, len, len0, false, nullptr, nullptr, capacity, pi, pj, img, flags, n_pairs,
+                      nullptr);
 }
 
 int build_pairs_sorted(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
-                       int64_t *n_pairs, const int **perm, const double **xs, const double **ds, const double **ls)
+                       const double *F, double *Unc, int64_t *n_pairs, const int **perm, const double **xs,
+                       const double **ds, const double **ls, PairIndex *ix)
 {
     int err = 0;
-    int64_t cap = (int64_t)(h->cap[kWsStepPi] / sizeof(int32_t));
+    // pairs that all three lists hold
+    auto held = [&]() {
+        return (int64_t)(std::min(h->cap[kWsStepPi], std::min(h->cap[kWsStepPj], h->cap[kWsStepImg])) /
+                         sizeof(int32_t));
+    };
     int64_t np = 0;
     int rc = RL_ERR_CAPACITY;
+    *ix = PairIndex{nullptr, nullptr, nullptr};
     for (int attempt = 0; attempt < 2 && rc == RL_ERR_CAPACITY; ++attempt) {
-        if (cap > 0 && (h->cap[kWsStepPj] < sizeof(int32_t) * cap || h->cap[kWsStepImg] < sizeof(int32_t) * cap ||
-                        h->cap[kWsStepFlags] < (size_t)cap))
-            cap = 0;
-        rc = pairs_core(h, n, x, dir, len, len0, true, cap, (int32_t *)h->buf[kWsStepPi],
-                        (int32_t *)h->buf[kWsStepPj], (int32_t *)h->buf[kWsStepImg], (uint8_t *)h->buf[kWsStepFlags],
-                        &np);
+        rc = pairs_core(h, n, x, dir, len, len0, true, F, Unc, held(), (int32_t *)h->buf[kWsStepPi],
+                        (int32_t *)h->buf[kWsStepPj], (int32_t *)h->buf[kWsStepImg], nullptr, &np, ix);
         if (rc == RL_ERR_CAPACITY && np <= 0x7fffffffLL) {
-            cap = np + np / 4 + 64;
+            const int64_t cap = np + np / 4 + 64;
             ws_get(h, kWsStepPi, sizeof(int32_t) * cap, &err);
             ws_get(h, kWsStepPj, sizeof(int32_t) * cap, &err);
             ws_get(h, kWsStepImg, sizeof(int32_t) * cap, &err);
-            ws_get(h, kWsStepFlags, (size_t)cap, &err);
             if (err) return err;
-            cap = (int64_t)(h->cap[kWsStepPi] / sizeof(int32_t));
         }
     }
     if (rc) return rc;
@@ -982,23 +1082,21 @@ __global__ void k_unc(int64_t n, const double *__restrict__ dir, const double *_
         f = load3(F + 6 * i);
         tq = load3(F + 6 * i + 3);
     }
-    const V3 u = m.aperp * f + ((m.apar - m.aperp) * dot(d, f)) * d;
-    const V3 w = m.rperp * tq;  // axial rotational mobility equals the normal one
-    store3(Unc + 6 * i, u);
-    store3(Unc + 6 * i + 3, w);
+    rod_unc(m, d, f, tq, Unc + 6 * i);
 }
 
+template <bool PACK>
 __global__ void k_assemble(int64_t nc, const double *__restrict__ x, const double *__restrict__ dir,
                            const double *__restrict__ len, double len0, GridDev g, double diam, double dt,
                            const int32_t *__restrict__ pi, const int32_t *__restrict__ pj,
                            const int32_t *__restrict__ img, const double *__restrict__ Unc, double *__restrict__ phi,
                            double *__restrict__ e, double *__restrict__ arm, double *__restrict__ q, int64_t n,
-                           int *__restrict__ err)
+                           int *__restrict__ err, PackOut pk)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (c >= nc) return;
     const int i = pi[c], j = pj[c], im = img[c];
-    if (i < 0 || j < 0 || i >= n || j >= n) {
+    if (!PACK && (i < 0 || j < 0 || i >= n || j >= n)) {
         atomicOr(err, 8);
         phi[c] = q[c] = arm[2 * c] = arm[2 * c + 1] = NAN;
         store3(e + 3 * c, v3(NAN, NAN, NAN));
@@ -1011,16 +1109,47 @@ __global__ void k_assemble(int64_t nc, const double *__restrict__ x, const doubl
     const double Li = len ? len[i] : len0, Lj = len ? len[j] : len0;
     const Contact ct = closest_point(xi, di, 0.5 * Li, xj, dj, 0.5 * Lj);
     const double ph = ct.dist - diam;
-    phi[c] = ph;
-    store3(e + 3 * c, ct.e);
-    arm[2 * c] = ct.s;
-    arm[2 * c + 1] = ct.t;
     // D^T U_nc: e.U_i + (s_i d_i x e).Omega_i - e.U_j - (t d_j x e).Omega_j
     const V3 ui = load3(Unc + 6 * (int64_t)i), wi = load3(Unc + 6 * (int64_t)i + 3);
     const V3 uj = load3(Unc + 6 * (int64_t)j), wj = load3(Unc + 6 * (int64_t)j + 3);
     const double rate = dot(ct.e, ui) + dot(cross(ct.s * di, ct.e), wi) - dot(ct.e, uj) -
                         dot(cross(ct.t * dj, ct.e), wj);
-    q[c] = ph / dt + rate;
+    const double qc = ph / dt + rate;
+    if (!PACK || phi) {
+        phi[c] = ph;
+        store3(e + 3 * c, ct.e);
+        arm[2 * c] = ct.s;
+        arm[2 * c + 1] = ct.t;
+    }
+    if (!PACK) {
+        q[c] = qc;
+        return;
+    }
+    pk.pp[c] = make_int2(i, j);
+    double2 *gd = reinterpret_cast<double2 *>(pk.geo + 4 * c);
+    gd[0] = make_double2(ct.e.x, ct.e.y);
+    gd[1] = make_double2(ct.e.z, ct.s);
+    pk.geo2[c] = make_double2(ct.t, qc);
+    pk.qv[c] = qc;
+    pk.st[c] = make_double2(pk.gamma ? pk.gamma[c] : 0.0, 0.0);
+    pk.qtmp[pk.qptr[j] + pk.qrank[c]] = (int32_t)c;
+}
+
+hipError_t launch_assemble(hipStream_t st, const rl_params &p, int64_t n, const double *x, const double *dir,
+                           const double *len, double len0, int64_t nc, const int32_t *pi, const int32_t *pj,
+                           const int32_t *img, const double *Unc, double *phi, double *e, double *arm, double *q,
+                           int *err, const PackOut *pk)
+{
+    if (nc <= 0) return hipSuccess;
+    GridDev g{};
+    for (int a = 0; a < 3; ++a) g.box[a] = p.box[a];
+    if (pk)
+        hipLaunchKernelGGL(k_assemble<true>, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, x, dir, len, len0, g, p.diam,
+                           p.dt, pi, pj, img, Unc, phi, e, arm, q, n, err, *pk);
+    else
+        hipLaunchKernelGGL(k_assemble<false>, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, x, dir, len, len0, g,
+                           p.diam, p.dt, pi, pj, img, Unc, phi, e, arm, q, n, err, PackOut{});
+    return hipGetLastError();
 }
 
 hipError_t launch_unc(hipStream_t st, int64_t n, const double *dir, const double *len, double len0, double diam,
@@ -1242,20 +1371,9 @@ int assemble_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, cons
     if (nc == 0) return RL_OK;
     double *Unc = (double *)ws_get(h, kWsUnc, sizeof(double) * 6 * (n > 0 ? n : 1), &werr);
     if (werr) return werr;
-    const Mob mob = mobility_of(len ? 1.0 : len0, p.diam, p.eta);
-    if (len)
-        hipLaunchKernelGGL(k_unc<false>, dim3(grid_of(n)), dim3(kBlock), 0, st, n, dir, len, mob, p.diam, p.eta, F,
-                           Unc);
-    else
-        hipLaunchKernelGGL(k_unc<true>, dim3(grid_of(n)), dim3(kBlock), 0, st, n, dir, len, mob, p.diam, p.eta, F,
-                           Unc);
-    RL_HIP(hipGetLastError());
-    GridDev g{};
-    for (int a = 0; a < 3; ++a) g.box[a] = p.box[a];
+    RL_HIP(launch_unc(st, n, dir, len, len0, p.diam, p.eta, F, Unc));
     RL_HIP(hipMemsetAsync(h->flag_dev, 0, sizeof(int), st));
-    hipLaunchKernelGGL(k_assemble, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, x, dir, len, len0, g, p.diam, p.dt,
-                       pi, pj, img, (const double *)Unc, phi, e, arm, q, n, h->flag_dev);
-    RL_HIP(hipGetLastError());
+    RL_HIP(launch_assemble(st, p, n, x, dir, len, len0, nc, pi, pj, img, Unc, phi, e, arm, q, h->flag_dev, nullptr));
     RL_HIP(hipMemcpyAsync(h->host_scratch, h->flag_dev, sizeof(int), hipMemcpyDeviceToHost, st));
     RL_HIP(hipStreamSynchronize(st));
     if (((int *)h->host_scratch)[0] & 8) {

@@ -210,12 +210,12 @@ namespace rl {
 
 enum Slot : int {
     kWsDir = 0, kWsCoef, kWsV, kWsUnc, kWsPptr, kWsQptr, kWsQidx, kWsQcnt, kWsG, kWsPartial,
-    kWsCellOf, kWsCellCnt, kWsCellStart, kWsCellCur, kWsSorted, kWsXs, kWsDs, kWsLs, kWsPcnt, kWsPoff,
-    kWsStepPi, kWsStepPj, kWsStepImg, kWsStepFlags, kWsStepPhi, kWsStepE, kWsStepArm, kWsStepQ, kWsStepGamma,
+    kWsCellOf, kWsCellCnt, kWsCellStart, kWsCellCur, kWsSorted, kWsXs, kWsDs, kWsLs, kWsPoff,
+    kWsStepPi, kWsStepPj, kWsStepImg, kWsStepPhi, kWsStepE, kWsStepArm, kWsStepQ, kWsStepGamma,
     kWsStepU, kWsScan, kWsLenMax, kWsPP, kWsGeo, kWsSt, kWsAlpha, kWsQpos, kWsQgeo, kWsStq, kWsSortIdx, kWsSortTmp, kWsCellKey, kWsFs,
     kWsSt32, kWsStq32, kWsGeo32, kWsUP32, kWsQgeo32, kWsUQ32,
     kWsBatchTab, kWsBatchOff, kWsBatchState, kWsBatchAlpha, kWsBatchCtr, kWsBatchPartial,
-    kWsBatchPartial2, kWsBatchDone, kWsBatchMap, kWsGeo2, kWsPairCache, kWsScanTmp, kWsEmitCount, kWsEmitKeys, kWsEmitFlags,
+    kWsBatchPartial2, kWsBatchDone, kWsBatchMap, kWsGeo2, kWsPairCache, kWsScanTmp, kWsEmit, kWsPairCnt, kWsQrank,
     kWsAdjG, kWsAdjUbar, kWsAdjQbd, kWsAdjCs, kWsAdjCr, kWsAdjCq, kWsAdjSc, kWsAdjPQ, kWsAdjDmob,
     kWsAdjEbar, kWsAdjArmbar, kWsAdjQbar, kWsAdjDbar, kWsAdjGbar, kWsAdjFs, kWsQv, kWsUP, kWsUQ,
     kWsGenKey, kWsGenKeyOut, kWsGenOrd, kWsGenPi, kWsGenPj, kWsGenE, kWsGenArm, kWsGenQ, kWsGenCmp, kWsGenGamma,
@@ -237,7 +237,6 @@ void set_error(const char *fmt, ...);
 // Internal building blocks used by the C-ABI layer.
 int build_pairs_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
                      int64_t capacity, int32_t *pi, int32_t *pj, int32_t *img, uint8_t *flags, int64_t *n_pairs);
-hipError_t launch_gather6(hipStream_t st, int64_t n, const int *perm, const double *src, double *dst);
 int stable_sort_by_key(rl_ctx *h, int64_t n, const int *keys, int bits, int *keys_out, int *perm);
 
 // Filaments binned by centre into periodic cells of edge >= L_max/2 +
@@ -255,7 +254,18 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
               double radius, RodCells *out);
 // out[0..m] = exclusive prefix sums of in[0..m-1] (out[m] = the total, also
 // written to *total when given), on the handle's stream.  tmp (may be null:
-// taken from the workspace) holds scan_tmp_bytes(m) bytes.
+// taken from the workspace) holds scan_tmp_bytes(m) bytes, 0 up to kScanOne,
+// where one workgroup takes an array.
+constexpr int64_t kScanOne = 16384;
+// written to pinned host memory when the sums are there: host[0] = *count (or
+// the first total), host[1] = *flag (host null: nothing)
+struct ScanReport {
+    const unsigned long long *count;
+    const int *flag;
+    int64_t *host;
+};
+hipError_t launch_scan_one(hipStream_t st, int64_t m, const int *in0, int *out0, const int *in1, int *out1,
+                           int64_t *total, const ScanReport &rep);
 int device_scan(rl_ctx *h, const int *in, int64_t m, int *out, int64_t *total, void *tmp = nullptr);
 int scan_tmp_bytes(int64_t m, size_t *bytes);
 // bytes of the allocation-free scratch array on each device
@@ -263,19 +273,53 @@ constexpr size_t kScratchBytes = (size_t)RL_NOALLOC_SCRATCH_BYTES;
 // sorts m (key, value) pairs by key (the warm start's constraint keys)
 int sort_key_values(rl_ctx *h, int64_t m, const unsigned long long *keys, const double *vals,
                     unsigned long long *keys_out, double *vals_out);
+// bytes the search keeps per pair it finds: key, places on both rods, bucket
+// slot and flags
+constexpr int kEmitBytes = 21;
+// Where the constraints of each rod are found, as the pair search leaves it
+// (all null: it does not): P lists as offsets, Q lists as offsets and the
+// place of each constraint in its list, in no particular order.
+struct PairIndex {
+    const int32_t *pptr, *qptr;
+    const int *qrank;
+};
 // Pair list in the solver's own rod order (cell order).  On return *perm
-// (device, n) maps solver rod -> caller rod and xs/ds/ls hold the rods'
-// centres, directors and lengths in solver order (handle workspace).
+// (device, n) maps solver rod -> caller rod, xs/ds/ls hold the rods' centres,
+// directors and lengths in solver order (handle workspace), and Unc the
+// velocities of the forces F (caller order, may be null) in solver order.
 int build_pairs_sorted(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
-                       int64_t *n_pairs, const int **perm, const double **xs, const double **ds, const double **ls);
+                       const double *F, double *Unc, int64_t *n_pairs, const int **perm, const double **xs,
+                       const double **ds, const double **ls, PairIndex *ix);
 int assemble_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
                   int64_t nc, const int32_t *pi, const int32_t *pj, const int32_t *img, const double *F,
                   double *phi, double *e, double *arm, double *q);
-// trusted: the pair list was built by the library itself (rl_step), so the
-// index checks and their host sync are skipped
+// the constraint records of a solve (see SolveArgs), and the Q lists unsorted
+struct PackOut {
+    const double *gamma;  // start, null: zeros
+    int2 *pp;
+    double *geo;
+    double2 *geo2;
+    double *qv;
+    double2 *st;
+    const int32_t *qptr;
+    const int *qrank;
+    int32_t *qtmp;
+};
+// geometry of the library's own pairs; each of phi, e, arm, q and pk may be null
+hipError_t launch_assemble(hipStream_t st, const rl_params &p, int64_t n, const double *x, const double *dir,
+                           const double *len, double len0, int64_t nc, const int32_t *pi, const int32_t *pj,
+                           const int32_t *img, const double *Unc, double *phi, double *e, double *arm, double *q,
+                           int *err, const PackOut *pk);
+// The same for a step's own pairs: their geometry goes straight into the
+// records (and to phi, e, arm where given); prepare_finish orders the Q lists,
+// from the start `gamma` if given, else from the one of prepare_step.
+int prepare_step(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0, int64_t nc,
+                 const int32_t *pi, const int32_t *pj, const int32_t *img, const double *Unc, const PairIndex &ix,
+                 const double *gamma0, double *phi, double *e, double *arm, SolveArgs *a);
+int prepare_finish(rl_ctx *h, const SolveArgs &a, const double *gamma);
 int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, double len0, int64_t nc,
                   const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
-                  double *gamma, SolveArgs *a, bool trusted = false);
+                  double *gamma, SolveArgs *a);
 int apply_impl(rl_ctx *h, SolveArgs &a, double *w);
 // Solves that stay on chip (rl_resident.hip).
 // What the conjugate gradients of the adjoint read and leave, in the layout of

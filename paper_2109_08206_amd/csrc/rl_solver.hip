@@ -53,9 +53,11 @@ static inline unsigned grid_of(int64_t n) { return grid_of(n, kBlock); }
 // incidence structure and packing
 // ---------------------------------------------------------------------------
 // Checks 0 <= pi <= pj < n and pi non-decreasing; writes pptr[r] = first c
-// with pi[c] >= r (pptr[n] = nc).
+// with pi[c] >= r (pptr[n] = nc), counts the Q sides and takes each
+// constraint's place among those of its second rod.
 __global__ void k_check_pairs(int64_t n, int64_t nc, const int32_t *__restrict__ pi, const int32_t *__restrict__ pj,
-                              int32_t *__restrict__ pptr, int *__restrict__ err)
+                              int32_t *__restrict__ pptr, int *__restrict__ qcnt, int *__restrict__ qrank,
+                              int *__restrict__ err)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (c > nc) return;
@@ -78,77 +80,59 @@ __global__ void k_check_pairs(int64_t n, int64_t nc, const int32_t *__restrict__
     }
     if (prev < -1) prev = -1;
     for (int64_t r = prev + 1; r <= a; ++r) pptr[r] = (int32_t)c;
+    qrank[c] = atomicAdd(qcnt + b, 1);
 }
 
-__global__ void k_qcount(int64_t nc, const int32_t *__restrict__ pj, int *__restrict__ qcnt)
-{
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c >= nc) return;
-    atomicAdd(qcnt + pj[c], 1);
-}
-
-__global__ void k_qfill(int64_t nc, const int32_t *__restrict__ pj, const int32_t *__restrict__ qptr,
-                        int *__restrict__ qcur, int32_t *__restrict__ qidx)
+// constraint records: (pi, pj), (ex, ey, ez, s_i) and (s_j, q), q alone,
+// (gamma, g = 0), and its place in the Q lists, not yet in order
+__global__ void k_pack(int64_t nc, const int32_t *__restrict__ pi, const int32_t *__restrict__ pj,
+                       const double *__restrict__ e, const double *__restrict__ arm, const double *__restrict__ q,
+                       PackOut o)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (c >= nc) return;
     const int r = pj[c];
-    qidx[qptr[r] + atomicAdd(qcur + r, 1)] = (int32_t)c;
-}
-
-// ascending constraint order inside each rod's Q-side list (fixes the
-// summation order of the rod kernel)
-__global__ void k_qsort(int64_t n, const int32_t *__restrict__ qptr, int32_t *__restrict__ qidx)
-{
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int b = qptr[r], e = qptr[r + 1];
-    for (int k = b + 1; k < e; ++k) {
-        const int32_t v = qidx[k];
-        int m = k - 1;
-        while (m >= b && qidx[m] > v) {
-            qidx[m + 1] = qidx[m];
-            --m;
-        }
-        qidx[m + 1] = v;
-    }
-}
-
-// constraint records: (pi, pj), (ex, ey, ez, s_i) and (s_j, q), q alone,
-// (gamma, g = 0)
-__global__ void k_pack(int64_t nc, const int32_t *__restrict__ pi, const int32_t *__restrict__ pj,
-                       const double *__restrict__ e, const double *__restrict__ arm, const double *__restrict__ q,
-                       const double *__restrict__ gamma, int2 *__restrict__ pp, double *__restrict__ geo,
-                       double2 *__restrict__ geo2, double *__restrict__ qv, double2 *__restrict__ st)
-{
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c >= nc) return;
-    pp[c] = make_int2(pi[c], pj[c]);
-    double2 *gd = reinterpret_cast<double2 *>(geo + 4 * c);
+    o.pp[c] = make_int2(pi[c], r);
+    double2 *gd = reinterpret_cast<double2 *>(o.geo + 4 * c);
     gd[0] = make_double2(e[3 * c], e[3 * c + 1]);
     gd[1] = make_double2(e[3 * c + 2], arm[2 * c]);
     const double qc = q ? q[c] : 0.0;
-    geo2[c] = make_double2(arm[2 * c + 1], qc);
-    qv[c] = qc;
-    st[c] = make_double2(gamma[c], 0.0);
+    o.geo2[c] = make_double2(arm[2 * c + 1], qc);
+    o.qv[c] = qc;
+    o.st[c] = make_double2(o.gamma[c], 0.0);
+    o.qtmp[o.qptr[r] + o.qrank[c]] = (int32_t)c;
 }
 
-// Q-side copies: qpos (inverse of qidx), the geometry a rod needs on its Q
-// side in list order, and the start iterate in list order
-__global__ void k_pack_q(int64_t nc, const int32_t *__restrict__ qidx, const double *__restrict__ geo,
-                         const double2 *__restrict__ geo2, const double2 *__restrict__ st, int32_t *__restrict__ qpos,
-                         double *__restrict__ qgeo, double2 *__restrict__ stq)
+// The Q lists in ascending constraint order (which fixes the summation order
+// of the rod kernel): each entry to its rank among its rod's, with qpos (the
+// inverse), the geometry a rod needs on its Q side and the start iterate.  A
+// lane per entry reads its rod's list: 4.7 entries on average at 100,000 rods,
+// 468,000 constraints.
+__global__ void k_pack_q(int64_t nc, const int32_t *__restrict__ qtmp, const int32_t *__restrict__ qptr,
+                         const int2 *__restrict__ pp, const double *__restrict__ geo,
+                         const double2 *__restrict__ geo2, const double2 *__restrict__ st, int32_t *__restrict__ qidx,
+                         int32_t *__restrict__ qpos, double *__restrict__ qgeo, double2 *__restrict__ stq)
 {
-    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k >= nc) return;
-    const int c = qidx[k];
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t >= nc) return;
+    const int c = qtmp[t], r = pp[c].y, b = qptr[r], e = qptr[r + 1];
+    int k = b;
+    for (int u = b; u < e; ++u) k += qtmp[u] < c;
+    qidx[k] = c;
     qpos[c] = (int32_t)k;
     const double2 *gd = reinterpret_cast<const double2 *>(geo + 4 * (int64_t)c);
     const double2 g0 = gd[0], g1 = gd[1];
-    double2 *qd = reinterpret_cast<double2 *>(qgeo + 4 * k);
+    double2 *qd = reinterpret_cast<double2 *>(qgeo + 4 * (int64_t)k);
     qd[0] = g0;
     qd[1] = make_double2(g1.x, geo2[c].x);
     stq[k] = st[c];
+}
+
+// a start that came after the records
+__global__ void k_set_start(int64_t nc, const double *__restrict__ gamma, double2 *__restrict__ st)
+{
+    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (c < nc) st[c] = make_double2(gamma[c], 0.0);
 }
 
 __global__ void k_unpack_gamma(int64_t nc, const double2 *__restrict__ st, double *__restrict__ gamma)
@@ -480,11 +464,18 @@ __global__ void k_integrate(int64_t n, const double *__restrict__ U, double *__r
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, double len0, int64_t nc,
-                  const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
-                  double *gamma, SolveArgs *out, bool trusted)
+// Sizes, mobility and workspace of a contact solve, all of it taken before
+// anything is launched.  own: the index of the lists is made here, else it
+// comes from the pair search.
+struct PrepWork {
+    int32_t *pptr, *qptr;
+    int *qcnt, *flag;
+    void *scan_tmp;
+};
+
+static int solve_args(rl_ctx *h, int64_t n, const double *dir, const double *len, double len0, int64_t nc, bool own,
+                      SolveArgs *out, PrepWork *w)
 {
-    hipStream_t st = h->stream;
     const rl_params &p = h->prm;
     int werr = 0;
     SolveArgs s{};
@@ -504,10 +495,14 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
     if (p.precision == RL_FP32_MIXED) gc = std::min<int64_t>(gc, kConGridMixed);
     s.gcon = (int)((gc + 7) / 8 * 8);
     const int64_t nb = nc > 0 ? nc : 1, rb = n > 0 ? n : 1;
-    int32_t *pptr = (int32_t *)ws_get(h, kWsPptr, sizeof(int32_t) * (n + 1), &werr);
-    int32_t *qptr = (int32_t *)ws_get(h, kWsQptr, sizeof(int32_t) * (n + 1), &werr);
+    // the error flag follows the counts where one workgroup scans them, so
+    // that one clear does (the scan's own scratch, larger, is not needed there)
+    const bool one = n <= kScanOne;
+    w->pptr = own ? (int32_t *)ws_get(h, kWsPptr, sizeof(int32_t) * (n + 1), &werr) : nullptr;
+    w->qptr = own ? (int32_t *)ws_get(h, kWsQptr, sizeof(int32_t) * (n + 1), &werr) : nullptr;
     int32_t *qidx = (int32_t *)ws_get(h, kWsQidx, sizeof(int32_t) * nb, &werr);
-    int *qcnt = (int *)ws_get(h, kWsQcnt, sizeof(int) * rb, &werr);
+    w->qcnt = own ? (int *)ws_get(h, kWsQcnt, sizeof(int) * (one ? n + 1 : rb), &werr) : nullptr;
+    w->flag = one && w->qcnt ? w->qcnt + n : h->flag_dev;
     int2 *pp = (int2 *)ws_get(h, kWsPP, sizeof(int2) * nb, &werr);
     double *geo = (double *)ws_get(h, kWsGeo, sizeof(double) * 4 * nb, &werr);
     double2 *geo2 = (double2 *)ws_get(h, kWsGeo2, sizeof(double2) * nb, &werr);
@@ -521,16 +516,17 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
     s.partial = (double *)ws_get(h, kWsPartial, sizeof(double) * 8 * s.gcon, &werr);
     s.alpha_buf = (double *)ws_get(h, kWsAlpha, sizeof(double) * 2, &werr);
     double *coef = len ? (double *)ws_get(h, kWsCoef, sizeof(double) * 3 * rb, &werr) : nullptr;
-    size_t scan_bytes = 0;
-    {
+    w->scan_tmp = nullptr;
+    if (own && !one) {
+        size_t scan_bytes = 0;
         const int rc = scan_tmp_bytes(n, &scan_bytes);
         if (rc) return rc;
+        w->scan_tmp = ws_get(h, kWsScanTmp, scan_bytes, &werr);
     }
-    void *scan_tmp = n > 0 ? ws_get(h, kWsScanTmp, scan_bytes, &werr) : nullptr;
     if (werr) return werr;
     s.coef = coef;
-    s.pptr = pptr;
-    s.qptr = qptr;
+    s.pptr = w->pptr;
+    s.qptr = w->qptr;
     s.qidx = qidx;
     s.pp = pp;
     s.geo = geo;
@@ -539,46 +535,99 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
     s.qpos = qpos;
     s.qgeo = qgeo;
     s.state = h->state;
-    if (len) RL_HIP(launch_mobility_coeffs(st, n, len, p.diam, p.eta, coef));
-    RL_HIP(hipMemsetAsync(h->flag_dev, 0, sizeof(int), st));
-    hipLaunchKernelGGL(k_check_pairs, dim3(grid_of(nc + 1)), dim3(kBlock), 0, st, n, nc, pi, pj, pptr, h->flag_dev);
-    RL_HIP(hipGetLastError());
-    if (!trusted) {
-        // a caller's list: its indices must be valid before k_qcount scatters through pj
-        RL_HIP(hipMemcpyAsync(h->host_scratch, h->flag_dev, sizeof(int), hipMemcpyDeviceToHost, st));
-        RL_HIP(hipStreamSynchronize(st));
-        const int ferr = ((int *)h->host_scratch)[0];
-        if (ferr) {
-            set_error(ferr & 1 ? "pair indices must satisfy 0 <= pi <= pj < n" : "pi must be non-decreasing");
-            return RL_ERR_ARG;
-        }
-    }
-    if (n > 0) {
-        RL_HIP(hipMemsetAsync(qcnt, 0, sizeof(int) * n, st));
-        if (nc > 0) {
-            hipLaunchKernelGGL(k_qcount, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, pj, qcnt);
-            RL_HIP(hipGetLastError());
-        }
-        const int rc = device_scan(h, qcnt, n, qptr, nullptr, scan_tmp);
-        if (rc) return rc;
-        if (nc > 0) {
-            RL_HIP(hipMemsetAsync(qcnt, 0, sizeof(int) * n, st));
-            hipLaunchKernelGGL(k_qfill, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, pj, (const int32_t *)qptr, qcnt,
-                               qidx);
-            RL_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_qsort, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int32_t *)qptr, qidx);
-            RL_HIP(hipGetLastError());
-        }
-    }
-    if (nc > 0) {
-        hipLaunchKernelGGL(k_pack, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, pi, pj, e, arm, q,
-                           (const double *)gamma, pp, geo, geo2, qv, s.st);
-        RL_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_pack_q, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, (const int32_t *)qidx,
-                           (const double *)geo, (const double2 *)geo2, (const double2 *)s.st, qpos, qgeo, s.stq);
-        RL_HIP(hipGetLastError());
-    }
+    if (len) RL_HIP(launch_mobility_coeffs(h->stream, n, len, p.diam, p.eta, coef));
     *out = s;
+    return RL_OK;
+}
+
+// the unsorted Q lists and the places in them, in what the loop writes first
+static int32_t *unsorted_q(const SolveArgs &s) { return (int32_t *)s.uP; }
+static int *places_q(const SolveArgs &s) { return (int *)s.uQ; }
+
+// pptr, qptr and the places in the Q lists of a list of pairs; trusted: the
+// library's own
+static int index_pairs(rl_ctx *h, const SolveArgs &s, const PrepWork &w, const int32_t *pi, const int32_t *pj,
+                       bool trusted)
+{
+    hipStream_t st = h->stream;
+    const int64_t n = s.n, nc = s.nc;
+    const bool one = n <= kScanOne;
+    RL_HIP(hipMemsetAsync(w.qcnt, 0, sizeof(int) * (one ? n + 1 : n), st));
+    if (!one) RL_HIP(hipMemsetAsync(w.flag, 0, sizeof(int), st));
+    hipLaunchKernelGGL(k_check_pairs, dim3(grid_of(nc + 1)), dim3(kBlock), 0, st, n, nc, pi, pj, w.pptr, w.qcnt,
+                       places_q(s), w.flag);
+    RL_HIP(hipGetLastError());
+    if (one) {
+        RL_HIP(launch_scan_one(st, n, w.qcnt, w.qptr, nullptr, nullptr, nullptr,
+                               ScanReport{nullptr, w.flag, trusted ? nullptr : h->host_scratch}));
+    } else {
+        if (!trusted)
+            RL_HIP(hipMemcpyAsync(h->host_scratch + 1, w.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+        const int rc = device_scan(h, w.qcnt, n, w.qptr, nullptr, w.scan_tmp);
+        if (rc) return rc;
+    }
+    if (trusted) return RL_OK;
+    // a caller's list: its indices must be valid before the records scatter through pj
+    RL_HIP(hipStreamSynchronize(st));
+    const int ferr = ((int *)(h->host_scratch + 1))[0];
+    if (ferr) {
+        set_error(ferr & 1 ? "pair indices must satisfy 0 <= pi <= pj < n" : "pi must be non-decreasing");
+        return RL_ERR_ARG;
+    }
+    return RL_OK;
+}
+
+static PackOut pack_out(const SolveArgs &s, const double *gamma, const int *qrank)
+{
+    return PackOut{gamma, const_cast<int2 *>(s.pp), const_cast<double *>(s.geo), const_cast<double2 *>(s.geo2),
+                   const_cast<double *>(s.qv), s.st, s.qptr, qrank, unsorted_q(s)};
+}
+
+int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, double len0, int64_t nc,
+                  const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
+                  double *gamma, SolveArgs *out)
+{
+    PrepWork w;
+    int rc = solve_args(h, n, dir, len, len0, nc, true, out, &w);
+    if (!rc) rc = index_pairs(h, *out, w, pi, pj, false);
+    if (rc || nc == 0) return rc;
+    hipLaunchKernelGGL(k_pack, dim3(grid_of(nc)), dim3(kBlock), 0, h->stream, nc, pi, pj, e, arm, q,
+                       pack_out(*out, gamma, places_q(*out)));
+    RL_HIP(hipGetLastError());
+    return prepare_finish(h, *out, nullptr);
+}
+
+int prepare_step(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0, int64_t nc,
+                 const int32_t *pi, const int32_t *pj, const int32_t *img, const double *Unc, const PairIndex &ix,
+                 const double *gamma0, double *phi, double *e, double *arm, SolveArgs *out)
+{
+    PrepWork w;
+    const bool own = ix.pptr == nullptr;
+    int rc = solve_args(h, n, dir, len, len0, nc, own, out, &w);
+    if (!rc && own) rc = index_pairs(h, *out, w, pi, pj, true);
+    if (rc) return rc;
+    if (!own) {
+        out->pptr = ix.pptr;
+        out->qptr = ix.qptr;
+    }
+    const PackOut pk = pack_out(*out, gamma0, own ? places_q(*out) : ix.qrank);
+    RL_HIP(launch_assemble(h->stream, h->prm, n, x, dir, len, len0, nc, pi, pj, img, Unc, phi, e, arm, nullptr,
+                           nullptr, &pk));
+    return RL_OK;
+}
+
+int prepare_finish(rl_ctx *h, const SolveArgs &a, const double *gamma)
+{
+    if (a.nc == 0) return RL_OK;
+    if (gamma) {
+        hipLaunchKernelGGL(k_set_start, dim3(grid_of(a.nc)), dim3(kBlock), 0, h->stream, a.nc, gamma, a.st);
+        RL_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_pack_q, dim3(grid_of(a.nc)), dim3(kBlock), 0, h->stream, a.nc,
+                       (const int32_t *)unsorted_q(a), a.qptr, a.pp, a.geo, a.geo2, (const double2 *)a.st,
+                       const_cast<int32_t *>(a.qidx), const_cast<int32_t *>(a.qpos), const_cast<double *>(a.qgeo),
+                       a.stq);
+    RL_HIP(hipGetLastError());
     return RL_OK;
 }
 

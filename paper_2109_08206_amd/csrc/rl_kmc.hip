@@ -170,13 +170,21 @@ __global__ void __launch_bounds__(kKmcBlock) k_kmc_check(KmcArgs A, int *__restr
 }
 
 // Processing order: crosslinkers with one head bound first, then unbound,
-// then doubly bound (the three cost very differently), each class by the
-// cell of its query point.  heavy[0] counts the first two classes.
-__global__ void k_kmc_keys(KmcArgs A, int *__restrict__ key, int *__restrict__ heavy)
+// then doubly bound (the three cost very differently), the first two by the
+// cell of their query point (by 2^drop cells), so that neighbours read the same
+// filaments.  Only the classes and the locality matter, so the order is a
+// counting sort by bins: nbc of either class, then one per workgroup of the
+// third.  (The stable sort by these keys took 20 launches and 100 us at 400,000
+// crosslinkers, and counting two of the classes on one word another 65.)
+__global__ void __launch_bounds__(kKmcBlock)
+    k_kmc_bins(KmcArgs A, int drop, int nbc, int *__restrict__ bin, int *__restrict__ rank, int *__restrict__ cnt)
 {
+    __shared__ int doubly;
+    if (threadIdx.x == 0) doubly = 0;
+    __syncthreads();
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c >= A.m) return;
-    const int s = A.state[c];
+    const bool live = c < A.m;
+    const int s = live ? A.state[c] : -1;
     int cls = 2;
     double p[3] = {0.0, 0.0, 0.0};
     if (s == RL_XL_SA || s == RL_XL_SB) {
@@ -194,10 +202,23 @@ __global__ void k_kmc_keys(KmcArgs A, int *__restrict__ key, int *__restrict__ h
             int v = (int)floor(p[a] / A.cell[a]);
             k[a] = v < 0 ? 0 : (v >= A.nc[a] ? A.nc[a] - 1 : v);
         }
-        id = (k[0] * A.nc[1] + k[1]) * A.nc[2] + k[2];
-        atomicAdd(heavy, 1);
+        id = cls * nbc + (((k[0] * A.nc[1] + k[1]) * A.nc[2] + k[2]) >> drop);
+        rank[c] = atomicAdd(cnt + id, 1);
+    } else {
+        id = 2 * nbc + (int)blockIdx.x;
+        if (live) rank[c] = atomicAdd(&doubly, 1);
     }
-    key[c] = (cls << 26) | id;
+    if (live) bin[c] = id;
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[2 * nbc + (int)blockIdx.x] = doubly;
+}
+
+__global__ void __launch_bounds__(kKmcBlock)
+    k_kmc_order(int64_t m, const int *__restrict__ bin, const int *__restrict__ rank, const int *__restrict__ off,
+                int *__restrict__ perm)
+{
+    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (c < m) perm[off[bin[c]] + rank[c]] = (int)c;
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -250,28 +271,32 @@ __global__ void __launch_bounds__(64) k_kmc_heavy(KmcArgs A, const int *__restri
         cnt[a] = A.nc[a] >= 3 ? 3 : A.nc[a];
     }
     const int ncl = cnt[0] * cnt[1] * cnt[2];
+    int held = 0;
     if (lane < ncl) {
         const int ix = lane / (cnt[1] * cnt[2]), iy = (lane / cnt[2]) % cnt[1], iz = lane % cnt[2];
         const int wx = (lo[0] + ix + A.nc[0]) % A.nc[0], wy = (lo[1] + iy + A.nc[1]) % A.nc[1],
                   wz = (lo[2] + iz + A.nc[2]) % A.nc[2];
         const int w = (wx * A.nc[1] + wy) * A.nc[2] + wz;
         cstart[lane] = A.start[w];
-        cpre[lane + 1] = A.start[w + 1] - A.start[w];
+        held = A.start[w + 1] - A.start[w];
     }
-    if (lane == 0) nnear = 0;
-    __syncthreads();
-    if (lane == 0) {
-        cpre[0] = 0;
-        for (int k = 0; k < ncl; ++k) cpre[k + 1] += cpre[k];
+#pragma unroll
+    for (int d = 1; d < 32; d <<= 1) {
+        const int v = __shfl_up(held, d, 64);
+        if (lane >= d) held += v;
     }
+    if (lane < ncl) cpre[lane + 1] = held;
+    if (lane == 0) cpre[0] = nnear = 0;
     __syncthreads();
     const int T = cpre[ncl];
     // candidate pass: a cheap centre-distance test (nearest image, reach
     // L/2 + r with a margin), then the exact captured interval
     const double inv[3] = {1.0 / A.box[0], 1.0 / A.box[1], 1.0 / A.box[2]};
     for (int t = lane; t < T; t += 64) {
-        int k = 0;
-        while (cpre[k + 1] <= t) ++k;
+        int k = 0;  // the last cell that starts at or before t
+#pragma unroll
+        for (int d = 16; d > 0; d >>= 1)
+            if (k + d < ncl && cpre[k + d] <= t) k += d;
         const int q = cstart[k] + (t - cpre[k]);
         const double *xq = A.xs + 3 * (int64_t)q, *dq = A.ds + 3 * (int64_t)q;
         const double Lq = A.ls[q];
@@ -617,16 +642,27 @@ int rl_kmc_step(rl_handle h, int64_t n, const double *x, const double *dir, cons
     A.xs = cells.xs;
     A.ds = cells.ds;
     A.ls = cells.ls;
-    int *key = (int *)ws_get(h, kWsKmcKey, sizeof(int) * m, &werr);
-    int *key_out = (int *)ws_get(h, kWsKmcKeyOut, sizeof(int) * m, &werr);
+    const int64_t ncell = (int64_t)A.nc[0] * A.nc[1] * A.nc[2];
+    int drop = 0;
+    while (((ncell - 1) >> drop) >= (1 << 17)) ++drop;
+    const int nbc = (int)((ncell - 1) >> drop) + 1;
+    const int64_t nbin = 2 * (int64_t)nbc + grid_of(m, kKmcBlock);
+    int *bin = (int *)ws_get(h, kWsKmcKey, sizeof(int) * m, &werr);
+    int *rank = (int *)ws_get(h, kWsKmcKeyOut, sizeof(int) * m, &werr);
     int *perm = (int *)ws_get(h, kWsKmcPerm, sizeof(int) * m, &werr);
+    int *bins = (int *)ws_get(h, kWsKmcBins, sizeof(int) * nbin, &werr);
+    int *off = (int *)ws_get(h, kWsKmcOff, sizeof(int) * (nbin + 1), &werr);
     if (werr) return werr;
     RL_HIP(hipMemsetAsync(flag, 0, sizeof(int) * 4, st));
-    hipLaunchKernelGGL(k_kmc_keys, dim3(grid_of(m, 256)), dim3(256), 0, st, A, key, flag + 1);
+    RL_HIP(hipMemsetAsync(bins, 0, sizeof(int) * nbin, st));
+    hipLaunchKernelGGL(k_kmc_bins, dim3(grid_of(m, kKmcBlock)), dim3(kKmcBlock), 0, st, A, drop, nbc, bin, rank, bins);
     RL_HIP(hipGetLastError());
-    rc = stable_sort_by_key(h, m, key, 28, key_out, perm);
+    rc = device_scan(h, bins, nbin, off, nullptr);
     if (rc) return rc;
-    RL_HIP(hipMemcpyAsync(h->host_scratch + 4, flag + 1, sizeof(int), hipMemcpyDeviceToHost, st));
+    hipLaunchKernelGGL(k_kmc_order, dim3(grid_of(m, kKmcBlock)), dim3(kKmcBlock), 0, st, m, (const int *)bin,
+                       (const int *)rank, (const int *)off, perm);
+    RL_HIP(hipGetLastError());
+    RL_HIP(hipMemcpyAsync(h->host_scratch + 4, off + 2 * (int64_t)nbc, sizeof(int), hipMemcpyDeviceToHost, st));
     RL_HIP(hipStreamSynchronize(st));
     const int nheavy = ((int *)(h->host_scratch + 4))[0];
     RL_HIP(hipMemsetAsync(cnt, 0, sizeof(unsigned long long) * 8, st));

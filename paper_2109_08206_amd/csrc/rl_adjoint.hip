@@ -621,8 +621,6 @@ int adjoint_core(rl_ctx *h, SolveArgs &a, bool step, const double *Ubar, const d
                                Ubar);
         RL_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, cg_tol, (long long)p.max_iter);
-    RL_HIP(hipGetLastError());
     long long iters = 0, nact = 0;
     double res = 0.0;
     int status = RL_OK;
@@ -634,8 +632,12 @@ int adjoint_core(rl_ctx *h, SolveArgs &a, bool step, const double *Ubar, const d
             return hipGetLastError();
         };
         RL_HIP(start());
-        if ((rc = resident_run(h, a, &cg, cg_tol, [] { return hipSuccess; }, &solved))) return rc;
-        if (!solved) RL_HIP(start());
+        if ((rc = resident_run(h, a, &cg, cg_tol, [] { return hipSuccess; }, false, &solved))) return rc;
+        if (!solved) {
+            RL_HIP(start());
+            hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, cg_tol, (long long)p.max_iter);
+            RL_HIP(hipGetLastError());
+        }
         const int every = p.check_every > 0 ? p.check_every : 32;
         const dim3 rgrid(rod_grid8(n > 0 ? n : 1));
         long long launched = 0;

@@ -358,6 +358,12 @@ int rl_create(rl_handle *out, const rl_params *prm)
         return rc;
     }
     memset(h->state_host, 0, sizeof(SolverState));
+    // a solve on chip starts from a state without a failure
+    if (hipMemset(h->state, 0, sizeof(SolverState)) != hipSuccess) {
+        rl_destroy(h);
+        set_error("rl_create: clearing the solver's state failed");
+        return RL_ERR_HIP;
+    }
     *out = h;
     return RL_OK;
 }
@@ -606,7 +612,10 @@ int rl_step(rl_handle h, int64_t n, double *x, double *quat, const double *len, 
     if (!rc) rc = prepare_finish(h, a, warm ? gamma : nullptr);
     if (rc) return rc;
     a.ordered = true;
-    rc = solve_impl(h, a, F, Uw, tape_mode != RL_TAPE_NONE && np > 0 ? gamma_tape : gamma, info, perm);
+    // the update may follow the solve at once where nothing after it can fail
+    StepEnd end{x, quat, extra ? extra->x_unwrapped : nullptr, false};
+    rc = solve_impl(h, a, F, Uw, tape_mode != RL_TAPE_NONE && np > 0 ? gamma_tape : gamma, info, perm,
+                    geom ? nullptr : &end);
     if (rc < 0) return rc;
     // gamma (or the tape) holds the forces in the step's constraint order
     const double *gsol = tape_mode != RL_TAPE_NONE && np > 0 ? gamma_tape : gamma;
@@ -618,6 +627,7 @@ int rl_step(rl_handle h, int64_t n, double *x, double *quat, const double *len, 
         const int rcs = step_stress(h, L, gsol, extra->stress);
         if (rcs) return rcs;
     }
+    if (end.done) return rc;  // waited for with the solve
     const int rc2 = integrate_impl(h, n, Uw, x, quat, extra ? extra->x_unwrapped : nullptr);
     if (rc2) return rc2;
     RL_HIP(hipStreamSynchronize(h->stream));

@@ -329,13 +329,18 @@ struct ResCg {
     double *cs, *cr, *cq;
 };
 // Runs a prepared solve (or cg) on chip if a form takes it.  `queue` queues
-// what reads the result, after each launch.  solved: state_host holds the
-// stop.  Else nothing was solved: the state is as k_state_init(tol) leaves it,
-// the iterate (and what cg holds) may be any of the solve.
+// what reads the result, after each launch; copies: among it the copy of the
+// state to state_host.  solved: state_host holds the stop.  Else nothing was
+// solved, and the iterate (and what cg holds) may be any of the solve.
 int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, const std::function<hipError_t()> &queue,
-                 bool *solved);
+                 bool copies, bool *solved);
+// the Euler update that ends a step, queued behind the solve where it can be
+struct StepEnd {
+    double *x, *quat, *xu;
+    bool done;
+};
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
-               const int *perm = nullptr);
+               const int *perm = nullptr, StepEnd *end = nullptr);
 // xu (may be null): unwrapped centres, += h U_t without wrapping
 int integrate_impl(rl_ctx *h, int64_t n, const double *U, double *x, double *quat, double *xu = nullptr);
 // mixed precision: FP32 copies of the geometry, then the refinement loop

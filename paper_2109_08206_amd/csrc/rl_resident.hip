@@ -373,7 +373,7 @@ enum ResKind { kResContacts, kResGeneral, kResCg };
 
 template <int T, int NC, int R1, int R2, bool HELD, ResKind KIND, bool MANY>
 __global__ void __launch_bounds__(T, 2)
-    k_resident(SolveArgs a, Exchange x, ResCg io, int ln, long long k0, long long kend)
+    k_resident(SolveArgs a, Exchange x, ResCg io, int ln, double tol, long long max_iter, long long k0, long long kend)
 {
     constexpr bool BIL = KIND == kResGeneral, CG = KIND == kResCg;
     constexpr int NW = T / 64, J = NC / T, kBins = 64;
@@ -689,8 +689,6 @@ __global__ void __launch_bounds__(T, 2)
     // its sums are over the constraints: a second slot does not enter them
     auto ours = [&](int j) { return !MANY || tid + j * T < own; };
 
-    const double tol = S->tol;
-    const long long max_iter = S->max_iter;
     double alpha = 0.0, alpha0 = 0.0, amin = 0.0, amax = 0.0, rmax = 0.0;
     if (k0 > 0) {
         alpha = S->alpha;
@@ -939,12 +937,12 @@ constexpr int kResSlots[kResForms] = {1024, 1536, 2048, 2560, 3072};
 
 template <int T, int NC, int R1, int R2, bool HELD, bool MANY>
 static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, const ResCg *cg, const ResPlan &p,
-                              long long k0, long long kend)
+                              double tol, long long max_iter, long long k0, long long kend)
 {
     SolveArgs aa = a;
     ResCg io = cg ? *cg : ResCg{nullptr, nullptr, nullptr};
     int ln = p.ln;
-    void *args[] = {&aa, &x, &io, &ln, &k0, &kend};
+    void *args[] = {&aa, &x, &io, &ln, &tol, &max_iter, &k0, &kend};
     const void *f = cg ? (const void *)k_resident<T, NC, R1, R2, HELD, kResCg, MANY>
                     : a.gen ? (const void *)k_resident<T, NC, R1, R2, HELD, kResGeneral, MANY>
                             : (const void *)k_resident<T, NC, R1, R2, HELD, kResContacts, MANY>;
@@ -980,7 +978,10 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
         int g = (int)std::min<int64_t>((nc + kResPer - 1) / kResPer, kFlat);
         g = std::max(g, 2);
         if (!fits(g, 0)) g = 2 * kFlat;
-        if (!fits(g, 0)) g = most;
+        // past 550 a workgroup the exchange between 256 costs less (50,000
+        // rods, 78,000 constraints: 7.7 us per iteration with 128, 7.0; 20,000
+        // and 62,000: 6.4 and 6.6)
+        if (!fits(g, 0) || (ordered && nc > 550 * 2 * kFlat)) g = most;
         if (g > most) return p;
         while (p.form < forms && !fits(g, p.form)) ++p.form;
         if (p.form == forms) return p;
@@ -1005,20 +1006,21 @@ static int64_t resident_words(const ResPlan &p, int64_t nc)
 }
 
 static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, const ResCg *cg,
-                           unsigned long long *words, unsigned base, long long k0, long long kend)
+                           unsigned long long *words, unsigned base, double tol, long long max_iter, long long k0,
+                           long long kend)
 {
     u64 *at = words ? words + 2 * (int64_t)p.groups * kResSlots[p.form] : nullptr;
     const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail};
     if (p.groups == 1) {
-        if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, cg, p, k0, kend);
-        return launch_form<512, 2048, 8, 4, true, false>(st, a, x, cg, p, k0, kend);
+        if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
+        return launch_form<512, 2048, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
     }
     switch (p.form) {
-    case 0: return launch_form<512, 1024, 8, 0, true, true>(st, a, x, cg, p, k0, kend);
-    case 1: return launch_form<512, 1536, 12, 0, true, true>(st, a, x, cg, p, k0, kend);
-    case 2: return launch_form<512, 2048, 8, 0, true, true>(st, a, x, cg, p, k0, kend);
-    case 3: return launch_form<512, 2560, 16, 0, false, true>(st, a, x, cg, p, k0, kend);
-    default: return launch_form<512, 3072, 12, 0, false, true>(st, a, x, cg, p, k0, kend);
+    case 0: return launch_form<512, 1024, 8, 0, true, true>(st, a, x, cg, p, tol, max_iter, k0, kend);
+    case 1: return launch_form<512, 1536, 12, 0, true, true>(st, a, x, cg, p, tol, max_iter, k0, kend);
+    case 2: return launch_form<512, 2048, 8, 0, true, true>(st, a, x, cg, p, tol, max_iter, k0, kend);
+    case 3: return launch_form<512, 2560, 16, 0, false, true>(st, a, x, cg, p, tol, max_iter, k0, kend);
+    default: return launch_form<512, 3072, 12, 0, false, true>(st, a, x, cg, p, tol, max_iter, k0, kend);
     }
 }
 
@@ -1060,7 +1062,7 @@ static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsign
 }
 
 int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, const std::function<hipError_t()> &queue,
-                 bool *solved)
+                 bool copies, bool *solved)
 {
     hipStream_t st = h->stream;
     *solved = false;
@@ -1076,8 +1078,9 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         }
         const unsigned base = h->xchg_num;
         h->xchg_num += (unsigned)kResChunk + 8;
-        RL_HIP(launch_resident(st, a, plan, cg, words, base, k0, k0 + kResChunk));
-        RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
+        RL_HIP(launch_resident(st, a, plan, cg, words, base, tol, (long long)h->prm.max_iter, k0, k0 + kResChunk));
+        if (!copies)
+            RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
         RL_HIP(queue());
         RL_HIP(hipStreamSynchronize(st));
         *solved = h->state_host->done != 0;
@@ -1089,7 +1092,7 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         // left without a result: more slots, or the two kernels from the start
         *solved = false;
         hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);
-        RL_HIP(hipGetLastError());
+        RL_HIP(hipGetLastError());  // (clears the failure)
         if (fail == 2 && k0 == 0 && resident_larger(plan)) continue;
         h->xchg_skip = 64;
         break;

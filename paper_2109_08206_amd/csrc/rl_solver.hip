@@ -359,16 +359,21 @@ __global__ void __launch_bounds__(kRodBlock) k_fin(SolveArgs a)
 
 // U = M (D gamma + F) per rod, with the full 6x6 block (external torques may
 // have an axial part; the axial rotational mobility equals the normal one).
-// `perm` (may be null) maps the solver's rod order to the caller's.
+// `perm` (may be null) maps the solver's rod order to the caller's.  gamma
+// (may be null) receives the forces, host (may be null) the solver's state.
 template <bool UNI>
-__global__ void __launch_bounds__(kRodBlock) k_velocity(SolveArgs a, const double *__restrict__ F,
-                                                        const int *__restrict__ perm, double *__restrict__ U)
+__global__ void __launch_bounds__(kRodBlock)
+    k_velocity(SolveArgs a, const double *__restrict__ F, const int *__restrict__ perm, double *__restrict__ U,
+               double *__restrict__ gamma, SolverState *__restrict__ host)
 {
+    if (host && blockIdx.x == 0 && threadIdx.x == 0) *host = *a.state;
     const int sub = threadIdx.x & (kRodLanes - 1);
     const int64_t r = (int64_t)blockIdx.x * (kRodBlock / kRodLanes) + (threadIdx.x / kRodLanes);
     const bool active = r < a.n;
     RodLoads<> L;
     rod_load(a, r, active, sub, L);
+    if (gamma && active)
+        for (int c = a.pptr[r] + sub; c < a.pptr[r + 1]; c += kRodLanes) gamma[c] = a.st[c].x;
     double f[3], m[3];
     rod_accumulate<kModeApply>(a, L, 0.0, f, m);
     if (!active || sub != 0) return;
@@ -428,12 +433,14 @@ __global__ void k_mix_accum(int64_t nc, const float4 *__restrict__ st32, const i
 }
 
 // x += h U_t wrapped into [0, box); theta += h Psi(theta) Omega, renormalised;
-// xu (may be null) += h U_t without wrapping.
+// xu (may be null) += h U_t without wrapping.  gate (may be null): nothing
+// unless the solve has ended with velocities.
 __global__ void k_integrate(int64_t n, const double *__restrict__ U, double *__restrict__ x, double *__restrict__ quat,
-                            double *__restrict__ xu, double dt, double b0, double b1, double b2)
+                            double *__restrict__ xu, double dt, double b0, double b1, double b2,
+                            const SolverState *__restrict__ gate)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || (gate && (!gate->done || gate->fail || gate->status < 0))) return;
     const double box[3] = {b0, b1, b2};
     for (int a = 0; a < 3; ++a) {
         const double dx = dt * U[6 * i + a];
@@ -763,37 +770,53 @@ static hipError_t record_sample(rl_ctx *h, int v, long long it, const SolveArgs 
 
 // U = M (D gamma + F) in the caller's order (perm may be null)
 static hipError_t launch_velocity(hipStream_t st, const SolveArgs &a, bool uni, const double *F, const int *perm,
-                                  double *U)
+                                  double *U, double *gamma = nullptr, SolverState *host = nullptr)
 {
     const dim3 grid(grid_of(a.n, kRodBlock / kRodLanes));
     if (uni)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_velocity<true>), grid, dim3(kRodBlock), 0, st, a, F, perm, U);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_velocity<true>), grid, dim3(kRodBlock), 0, st, a, F, perm, U, gamma,
+                           host);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_velocity<false>), grid, dim3(kRodBlock), 0, st, a, F, perm, U);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_velocity<false>), grid, dim3(kRodBlock), 0, st, a, F, perm, U, gamma,
+                           host);
+    return hipGetLastError();
+}
+
+static hipError_t launch_integrate(rl_ctx *h, int64_t n, const double *U, double *x, double *quat, double *xu,
+                                   const SolverState *gate)
+{
+    const rl_params &p = h->prm;
+    hipLaunchKernelGGL(k_integrate, dim3(grid_of(n)), dim3(kBlock), 0, h->stream, n, U, x, quat, xu, p.dt, p.box[0],
+                       p.box[1], p.box[2], gate);
     return hipGetLastError();
 }
 
 int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamma_out, rl_solve_info *info,
-               const int *perm)
+               const int *perm, StepEnd *end)
 {
     hipStream_t st = h->stream;
     const rl_params &p = h->prm;
     const bool uni = a.coef == nullptr;
-    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, p.tol, (long long)p.max_iter);
-    RL_HIP(hipGetLastError());
     long long iters = 0, refreshes = 0;
     bool vel_queued = false, solved = false;
     if (a.nc > 0) {
+        const bool vel = U && a.n > 0;
         const int rc = resident_run(
             h, a, nullptr, p.tol,
             [&]() {
-                hipError_t e = gamma_out ? launch_unpack_gamma(st, a, gamma_out) : hipSuccess;
-                if (e == hipSuccess && U && a.n > 0) e = launch_velocity(st, a, uni, F, perm, U);
+                if (!vel) return gamma_out ? launch_unpack_gamma(st, a, gamma_out) : hipSuccess;
+                hipError_t e = launch_velocity(st, a, uni, F, perm, U, gamma_out, h->state_host);
+                if (e == hipSuccess && end) e = launch_integrate(h, a.n, U, end->x, end->quat, end->xu, h->state);
                 return e;
             },
-            &solved);
+            vel, &solved);
         if (rc) return rc;
-        vel_queued = solved && U && a.n > 0;
+        vel_queued = solved && vel;
+        if (end) end->done = vel_queued && h->state_host->status >= 0;
+    }
+    if (!solved) {
+        hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, p.tol, (long long)p.max_iter);
+        RL_HIP(hipGetLastError());
     }
     if (solved) {
         iters = h->state_host->iter;
@@ -928,7 +951,7 @@ int solve_impl(rl_ctx *h, SolveArgs &a, const double *F, double *U, double *gamm
         RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
     }
     if (U && a.n > 0 && !vel_queued) RL_HIP(launch_velocity(st, a, uni, F, perm, U));
-    RL_HIP(hipStreamSynchronize(st));
+    if (!solved) RL_HIP(hipStreamSynchronize(st));  // a solve on chip has been waited for, with its velocities
     const SolverState &s = *h->state_host;
     const int status = a.nc > 0 ? s.status : RL_OK;
     if (info) {
@@ -971,13 +994,7 @@ hipError_t launch_alpha0_64(rl_ctx *h, const SolveArgs &a)
 
 hipError_t launch_velocity_on(hipStream_t st, const SolveArgs &a, const double *F, const int *perm, double *U)
 {
-    if (a.n <= 0) return hipSuccess;
-    const dim3 grid(grid_of(a.n, kRodBlock / kRodLanes));
-    if (a.coef == nullptr)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_velocity<true>), grid, dim3(kRodBlock), 0, st, a, F, perm, U);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_velocity<false>), grid, dim3(kRodBlock), 0, st, a, F, perm, U);
-    return hipGetLastError();
+    return a.n > 0 ? launch_velocity(st, a, a.coef == nullptr, F, perm, U) : hipSuccess;
 }
 
 hipError_t launch_velocity64(rl_ctx *h, const SolveArgs &a, const double *F, const int *perm, double *U)
@@ -1005,11 +1022,7 @@ __global__ void k_restore_start(int64_t nc, const double *__restrict__ gamma_in,
 
 int integrate_impl(rl_ctx *h, int64_t n, const double *U, double *x, double *quat, double *xu)
 {
-    if (n <= 0) return RL_OK;
-    const rl_params &p = h->prm;
-    hipLaunchKernelGGL(k_integrate, dim3(grid_of(n)), dim3(kBlock), 0, h->stream, n, U, x, quat, xu, p.dt,
-                       p.box[0], p.box[1], p.box[2]);
-    RL_HIP(hipGetLastError());
+    if (n > 0) RL_HIP(launch_integrate(h, n, U, x, quat, xu, nullptr));
     return RL_OK;
 }
 

@@ -39,6 +39,7 @@
 // as long as its longest list, and a random 64 rods nearly always hold one
 // two or three times the average).
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 #include "rl_device.hpp"
@@ -378,7 +379,7 @@ __global__ void __launch_bounds__(T, 2)
     constexpr bool BIL = KIND == kResGeneral, CG = KIND == kResCg;
     constexpr int NW = T / 64, J = NC / T, kBins = 64;
     static_assert(NC % T == 0 && J <= 16 && NC <= 0xffff && R1 % kGroup == 0 && R2 % kGroup == 0, "");
-    __shared__ double E[3][NC], G[NC], U[2 * NC];
+    __shared__ __align__(16) double E[3][NC], G[NC], U[2 * NC];
     __shared__ double sP[HELD ? NC : 1], sQ[HELD ? NC : 1];
     __shared__ unsigned short qslot[NC];
     __shared__ __align__(16) double red[MANY ? 2 : 1][4][4 * NW];
@@ -522,17 +523,27 @@ __global__ void __launch_bounds__(T, 2)
     if (MANY) {
         // the second slots in the order of their constraints (by rank), so
         // that neighbouring lanes send and receive neighbouring words
+        // (four of them a read: at 250 second slots one by one took 13 us)
         int *moved = reinterpret_cast<int *>(U) + (R2 ? 2 : 1) * T;
         static_assert(!MANY || (R2 ? 2 : 1) * T + NC <= 2 * NC, "order and moved slots fit in half of U");
+        const int first = own & ~3, last = (slots + 3) & ~3;
+        if (tid < 4) {
+            if (first + tid < own) away[first + tid] = INT_MAX;
+            if (slots + tid < last) away[slots + tid] = INT_MAX;
+        }
+        __syncthreads();
         int c[J], rank[J];
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int s = own + tid + j * T;
+            c[j] = s < slots ? away[s] : 0;
             rank[j] = 0;
-            if (s < slots) {
-                c[j] = away[s];
-                for (int k = own; k < slots; ++k) rank[j] += away[k] < c[j];
-            }
+        }
+        for (int k = first; k < last; k += 4) {
+            const int4 v = *reinterpret_cast<const int4 *>(away + k);
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                rank[j] += (v.x < c[j]) + (v.y < c[j]) + (v.z < c[j]) + (v.w < c[j]);
         }
         __syncthreads();
 #pragma unroll

@@ -221,28 +221,43 @@ __global__ void __launch_bounds__(kKmcBlock)
     if (c < m) perm[off[bin[c]] + rank[c]] = (int)c;
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+__device__ __forceinline__ double lane_of(double v, int lane)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+__device__ __forceinline__ int64_t lane_of(int64_t v, int lane)
+{
+    return __double_as_longlong(lane_of(__longlong_as_double(v), lane));
 }
 
 // Crosslinkers without both heads bound: one wave each (a 64-thread
 // workgroup), its lanes sharing the candidate filaments of the 27 cells
 // around the query point.  A candidate is kept when its axis passes within
-// the query radius; the kept ones go to an LDS list, sorted by filament
+// the query radius: 580 candidates of the benchmark's suspension come to 75
+// whose centre is near enough, which wait in a queue for the exact test 64 at
+// a time (on the lanes that found them it ran nine times with one lane in
+// eight).  Bound by the latency of its chain of loads and by the sites' sums:
+// 82,500 crosslinkers among 100,000 filaments 345 us, 430 with the cells walked,
+// the exact test where it was found and each filament looked up by all lanes.
+// (Two, four or eight waves per workgroup were slower, 510 to 615 us against
+// 505 for the whole step: a workgroup waits for its slowest.)
+// The kept ones go to an LDS list, sorted by filament
 // index, over which the rate is summed and the binding walks, in the order
 // the method defines.  The S -> D weight of a kept filament is summed over
 // its sites by all lanes.
 constexpr int kNearCap = 128;
+
+// what lanes of a wave left in LDS, for its other lanes
+__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 __global__ void __launch_bounds__(64) k_kmc_heavy(KmcArgs A, const int *__restrict__ perm, int nheavy,
                                                   int *__restrict__ err)
 {
     __shared__ int cstart[27], cpre[28];
     __shared__ int nnear;
-    __shared__ int nidx[kNearCap], sidx[kNearCap];
+    __shared__ int nidx[kNearCap], sidx[kNearCap], queue[128];
     __shared__ double nw[kNearCap], sw[kNearCap];
     const int lane = threadIdx.x;
     if ((int)blockIdx.x >= nheavy) return;
@@ -287,39 +302,53 @@ __global__ void __launch_bounds__(64) k_kmc_heavy(KmcArgs A, const int *__restri
     }
     if (lane < ncl) cpre[lane + 1] = held;
     if (lane == 0) cpre[0] = nnear = 0;
-    __syncthreads();
+    wave_sync();
     const int T = cpre[ncl];
     // candidate pass: a cheap centre-distance test (nearest image, reach
     // L/2 + r with a margin), then the exact captured interval
     const double inv[3] = {1.0 / A.box[0], 1.0 / A.box[1], 1.0 / A.box[2]};
-    for (int t = lane; t < T; t += 64) {
-        int k = 0;  // the last cell that starts at or before t
-#pragma unroll
-        for (int d = 16; d > 0; d >>= 1)
-            if (k + d < ncl && cpre[k + d] <= t) k += d;
-        const int q = cstart[k] + (t - cpre[k]);
-        const double *xq = A.xs + 3 * (int64_t)q, *dq = A.ds + 3 * (int64_t)q;
-        const double Lq = A.ls[q];
-        double d2 = 0.0;
-        for (int a = 0; a < 3; ++a) {
-            double d = xq[a] - p[a];
-            d -= A.box[a] * rint(d * inv[a]);
-            d2 += d * d;
-        }
-        const double reach = 0.5 * Lq + r;
-        if (d2 > reach * reach * (1.0 + 1e-9) + 1e-24) continue;
+    int qn = 0;  // entries in the queue
+    auto exact = [&](int cnt) {
+        wave_sync();
+        qn -= cnt;
+        if (lane >= cnt) return;
+        const int64_t q = queue[qn + lane];
         const int j = A.order[q];
-        if (j == own) continue;
+        if (j == own) return;
         double a0, a1;
-        inside_interval(xq, dq, Lq, A.box, p, unb ? r : r * (1.0 + 1e-9), a0, a1);
-        if (!(a1 > a0)) continue;
+        inside_interval(A.xs + 3 * q, A.ds + 3 * q, A.ls[q], A.box, p, unb ? r : r * (1.0 + 1e-9), a0, a1);
+        if (!(a1 > a0)) return;
         const int slot = atomicAdd(&nnear, 1);
         if (slot < kNearCap) {
             nidx[slot] = j;
             nw[slot] = a1 - a0;
         }
+    };
+    int k = 0;  // the last cell that starts at or before the lane's candidate
+    for (int t0 = 0; t0 < T; t0 += 64) {
+        const int t = t0 + lane;
+        bool in = false;
+        int q = 0;
+        if (t < T) {
+            while (cpre[k + 1] <= t) ++k;
+            q = cstart[k] + (t - cpre[k]);
+            const double *xq = A.xs + 3 * (int64_t)q;
+            double d2 = 0.0;
+            for (int a = 0; a < 3; ++a) {
+                double d = xq[a] - p[a];
+                d -= A.box[a] * rint(d * inv[a]);
+                d2 += d * d;
+            }
+            const double reach = 0.5 * A.ls[q] + r;
+            in = !(d2 > reach * reach * (1.0 + 1e-9) + 1e-24);
+        }
+        const unsigned long long m = __ballot(in);
+        if (in) queue[qn + __popcll(m & ((1ull << lane) - 1ull))] = q;
+        qn += __popcll(m);
+        if (qn >= 64) exact(64);
     }
-    __syncthreads();
+    if (qn > 0) exact(qn);
+    wave_sync();
     const int K = nnear;
     if (K > kNearCap) {
         if (lane == 0) atomicOr(err, 2);
@@ -333,34 +362,59 @@ __global__ void __launch_bounds__(64) k_kmc_heavy(KmcArgs A, const int *__restri
         sidx[rank] = me;
         sw[rank] = nw[k];
     }
-    __syncthreads();
-    // S -> D weights of the kept filaments, sites spread over the lanes
+    wave_sync();
+    // S -> D weights of the kept filaments: a lane looks its filament up, then
+    // the sites of one filament after the other are spread over the lanes, two
+    // filaments at a time (their sums are chains of shuffles)
     if (!unb) {
-        for (int k = 0; k < K; ++k) {
-            const int j = sidx[k];
-            const double L = rlen(A, j);
-            const int64_t m = sites_of(A, L);
-            const double *xj = A.x + 3 * (int64_t)j, *dj = A.dir + 3 * (int64_t)j;
-            double a0, a1;
-            inside_interval(xj, dj, L, A.box, p, P.rcd * (1.0 + 1e-9), a0, a1);
-            const double step = L / m;
-            int64_t k0 = (int64_t)floor((a0 + 0.5 * L) / step - 0.5) - 1;
-            int64_t k1 = (int64_t)ceil((a1 + 0.5 * L) / step - 0.5) + 1;
-            if (k0 < 0) k0 = 0;
-            if (k1 > m - 1) k1 = m - 1;
-            double cc[3];
-            centre_rel(xj, A.box, p, cc);
-            double part = 0.0;
-            for (int64_t ks = k0 + lane; ks <= k1; ks += 64) {
-                const double sa = site_arc(L, m, ks);
-                const double v0 = cc[0] + sa * dj[0], v1 = cc[1] + sa * dj[1], v2 = cc[2] + sa * dj[2];
-                const double l = sqrt(v0 * v0 + v1 * v1 + v2 * v2);
-                if (l <= P.rcd) part += cross_weight(A, l);
+        for (int kb = 0; kb < K; kb += 64) {
+            double L = 1.0, cc[3] = {0.0, 0.0, 0.0}, dj[3] = {0.0, 0.0, 0.0};
+            int64_t k0 = 0, k1 = -1;
+            if (kb + lane < K) {
+                const int64_t j = sidx[kb + lane];
+                L = rlen(A, j);
+                const int64_t m = sites_of(A, L);
+                const double *xj = A.x + 3 * j;
+                for (int a = 0; a < 3; ++a) dj[a] = A.dir[3 * j + a];
+                double a0, a1;
+                inside_interval(xj, dj, L, A.box, p, P.rcd * (1.0 + 1e-9), a0, a1);
+                const double step = L / m;
+                k0 = (int64_t)floor((a0 + 0.5 * L) / step - 0.5) - 1;
+                k1 = (int64_t)ceil((a1 + 0.5 * L) / step - 0.5) + 1;
+                if (k0 < 0) k0 = 0;
+                if (k1 > m - 1) k1 = m - 1;
+                centre_rel(xj, A.box, p, cc);
             }
-            const double wj = wave_sum(part);
-            if (lane == 0) sw[k] = wj;
+            // sum over the sites of kept filament k of this batch
+            auto weight = [&](int k) {
+                const double Lk = lane_of(L, k), c0 = lane_of(cc[0], k), c1 = lane_of(cc[1], k), c2 = lane_of(cc[2], k),
+                             d0 = lane_of(dj[0], k), d1 = lane_of(dj[1], k), d2 = lane_of(dj[2], k);
+                const int64_t m = sites_of(A, Lk);
+                const int64_t last = lane_of(k1, k);
+                double part = 0.0;
+                for (int64_t ks = lane_of(k0, k) + lane; ks <= last; ks += 64) {
+                    const double sa = site_arc(Lk, m, ks);
+                    const double v0 = c0 + sa * d0, v1 = c1 + sa * d1, v2 = c2 + sa * d2;
+                    const double l = sqrt(v0 * v0 + v1 * v1 + v2 * v2);
+                    if (l <= P.rcd) part += cross_weight(A, l);
+                }
+                return part;
+            };
+            const int held = min(64, K - kb);
+            for (int k = 0; k < held; k += 2) {
+                double u = weight(k), v = k + 1 < held ? weight(k + 1) : 0.0;
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) {
+                    u += __shfl_xor(u, o, 64);
+                    v += __shfl_xor(v, o, 64);
+                }
+                if (lane == 0) {
+                    sw[kb + k] = u;
+                    if (k + 1 < held) sw[kb + k + 1] = v;
+                }
+            }
         }
-        __syncthreads();
+        wave_sync();
     }
     if (lane != 0) return;
     // the total over the kept filaments in index order

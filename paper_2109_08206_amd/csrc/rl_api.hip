@@ -358,12 +358,6 @@ int rl_create(rl_handle *out, const rl_params *prm)
         return rc;
     }
     memset(h->state_host, 0, sizeof(SolverState));
-    // a solve on chip starts from a state without a failure
-    if (hipMemset(h->state, 0, sizeof(SolverState)) != hipSuccess) {
-        rl_destroy(h);
-        set_error("rl_create: clearing the solver's state failed");
-        return RL_ERR_HIP;
-    }
     *out = h;
     return RL_OK;
 }

@@ -177,6 +177,7 @@ struct rl_ctx {
     rl::SolverState *state = nullptr;       // device
     rl::SolverState *state_host = nullptr;  // pinned
     int *flag_dev = nullptr;                // device error flags
+    bool state_ready = false;               // the state holds what a solve left
     int64_t *host_scratch = nullptr;        // pinned, for small readbacks
     unsigned long long *progress_host = nullptr;  // pinned coherent word written by the loop (SolveArgs::progress)
     unsigned long long *progress_dev = nullptr;   // its device address

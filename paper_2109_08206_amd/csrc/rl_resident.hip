@@ -1081,6 +1081,12 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
     unsigned long long *words = nullptr;
     const int rc = resident_prepare(h, a, &plan, &words);
     if (rc) return rc;
+    // the launches start from a state without a failure, which they leave so
+    if (plan.groups > 0 && !h->state_ready) {
+        hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);
+        RL_HIP(hipGetLastError());
+        h->state_ready = true;
+    }
     // a long solve is cut into launches so that each ends soon
     for (long long k0 = 0; plan.groups > 0 && !*solved;) {
         if (words && h->xchg_num > 0xf8000000u) {

@@ -425,7 +425,7 @@ int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs)
         {kWsCellOf, sizeof(int) * n},      {kWsSorted, sizeof(int) * n},       {kWsXs, sizeof(double) * 3 * n},
         {kWsDs, sizeof(double) * 3 * n},   {kWsLs, sizeof(double) * n},        {kWsStepUnc, sizeof(double) * 6 * n},
         {kWsPoff, sizeof(int) * (n + 1)},  {kWsStepPi, sizeof(int) * nc},      {kWsStepPj, sizeof(int) * nc},
-        {kWsStepImg, sizeof(int) * nc},    {kWsQrank, sizeof(int) * nc},       {kWsEmit, (size_t)kEmitBytes * nc},
+        {kWsStepImg, sizeof(int) * nc},    {kWsQtmp, sizeof(int) * nc},        {kWsEmit, (size_t)kEmitBytes * nc},
         {kWsStepGamma, sizeof(double) * nc}, {kWsStepU, sizeof(double) * 6 * n}, {kWsQv, sizeof(double) * nc},
         {kWsUP, sizeof(double) * nc},      {kWsUQ, sizeof(double) * nc},
         {kWsPP, sizeof(int) * 2 * nc},     {kWsGeo, sizeof(double) * 4 * nc}, {kWsGeo2, sizeof(double) * 2 * nc},  {kWsSt, sizeof(double) * 2 * nc},
@@ -603,7 +603,7 @@ int rl_step(rl_handle h, int64_t n, double *x, double *quat, const double *len, 
     rc = prepare_step(h, n, xs, ds, lsv, len0, np, pi, pj, img, Unc, ix,
                       tape_mode == RL_TAPE_REPLAY ? gamma_tape : nullptr, phi, e, arm, &a);
     if (!rc && warm) rc = warm_lookup(h, L, gamma);
-    if (!rc) rc = prepare_finish(h, a, warm ? gamma : nullptr);
+    if (!rc && warm) rc = set_start(h, a, gamma);
     if (rc) return rc;
     a.ordered = true;
     // the update may follow the solve at once where nothing after it can fail
@@ -703,7 +703,6 @@ int rl_step_adjoint(rl_handle h, int64_t n, const double *x, const double *quat,
     const int32_t *img = (const int32_t *)h->buf[kWsStepImg];
     SolveArgs a;
     rc = prepare_step(h, n, xs, ds, lsv, len0, np, pi, pj, img, Unc, ix, gamma_tape, nullptr, nullptr, nullptr, &a);
-    if (!rc) rc = prepare_finish(h, a, nullptr);
     if (rc) return rc;
     a.ordered = true;
     rl_solve_info si{0, 0.0, 0.0, RL_OK, 0};

@@ -644,4 +644,30 @@ __device__ __forceinline__ void con_update_gen(const SolveArgs &a, int64_t c, co
     con_apply_gen<MODE>(a, c, L.up - L.uq, L.q, L.sg, L.qp, L.cm, alpha, p);
 }
 
+// The records of constraint c between rods i and j: the P side in its own
+// order, the Q side at the rank of c among its rod's entries (ascending
+// constraint order fixes the summation order of the rods).  A lane reads its
+// rod's list: 4.7 entries on average at 100,000 rods, 468,000 constraints.
+__device__ __forceinline__ void pack_record(const PackOut &o, int64_t c, int i, int j, double ex, double ey, double ez,
+                                            double s, double t, double q)
+{
+    const int b = o.qptr[j], e = o.qptr[j + 1];
+    const double2 start = make_double2(o.gamma ? o.gamma[c] : 0.0, 0.0);
+    int k = b;
+    for (int u = b; u < e; ++u) k += o.qtmp[u] < (int)c;
+    o.pp[c] = make_int2(i, j);
+    double2 *g = reinterpret_cast<double2 *>(o.geo + 4 * c);
+    g[0] = make_double2(ex, ey);
+    g[1] = make_double2(ez, s);
+    o.geo2[c] = make_double2(t, q);
+    o.qv[c] = q;
+    o.st[c] = start;
+    o.qpos[c] = k;
+    o.qidx[k] = (int32_t)c;
+    double2 *h = reinterpret_cast<double2 *>(o.qgeo + 4 * (int64_t)k);
+    h[0] = make_double2(ex, ey);
+    h[1] = make_double2(ez, t);
+    o.stq[k] = start;
+}
+
 }  // namespace rl

@@ -13,6 +13,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "rl_device.hpp"
 #include "rl_vec.hpp"
 
 namespace rl {
@@ -765,8 +766,8 @@ __global__ void __launch_bounds__(kPairBlock)
 // with the ranks that the counting gave, then each pair to the place of its
 // key among its bucket's (a lane per pair reads the bucket: 4.7 pairs on
 // average at 100,000 rods, 468,000 pairs).  The keys are distinct, so the
-// result is the order of the keys whatever order the counting took.  qrank
-// (may be null): the place of the pair in the Q list of its second rod.
+// result is the order of the keys whatever order the counting took.  qtmp
+// (may be null): the pairs of each second rod, at the offsets qoff.
 __global__ void k_pair_bucket(int64_t m, const unsigned long long *__restrict__ keys, const int2 *__restrict__ rank,
                               int kshift, const int *__restrict__ off, int *__restrict__ slot)
 {
@@ -779,7 +780,7 @@ __global__ void k_pair_place(int64_t m, const unsigned long long *__restrict__ k
                              const uint8_t *__restrict__ kflags, const int2 *__restrict__ rank, int kshift,
                              const int *__restrict__ off, const int *__restrict__ slot, int32_t *__restrict__ pi,
                              int32_t *__restrict__ pj, int32_t *__restrict__ img, uint8_t *__restrict__ flags,
-                             int *__restrict__ qrank)
+                             const int *__restrict__ qoff, int32_t *__restrict__ qtmp)
 {
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (s >= m) return;
@@ -789,10 +790,11 @@ __global__ void k_pair_place(int64_t m, const unsigned long long *__restrict__ k
     int c = b;
     for (int u = b; u < e; ++u) c += keys[slot[u]] < k;
     pi[c] = a;
-    pj[c] = (int32_t)((k >> 12) & ((1ull << (kshift - 12)) - 1ull));
+    const int j = (int)((k >> 12) & ((1ull << (kshift - 12)) - 1ull));
+    pj[c] = j;
     img[c] = (int32_t)(k & 0xfffull);
     if (flags) flags[c] = kflags[t];
-    if (qrank) qrank[c] = rank[t].y;
+    if (qtmp) qtmp[qoff[j] + rank[t].y] = c;
 }
 
 // velocity of a rod under its external force and torque alone
@@ -1094,16 +1096,16 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
             if (!rc && internal) rc = device_scan(h, ec.q, n, qoff, nullptr);
             if (rc) return rc;
         }
-        int *qrank = internal ? (int *)ws_get(h, kWsQrank, sizeof(int) * total, &werr) : nullptr;
+        int32_t *qtmp = internal ? (int32_t *)ws_get(h, kWsQtmp, sizeof(int32_t) * total, &werr) : nullptr;
         if (werr) return werr;
         hipLaunchKernelGGL(k_pair_bucket, dim3(grid_of(total)), dim3(kBlock), 0, st, total,
                            (const unsigned long long *)ekeys, (const int2 *)erank, kshift, (const int *)poff, pslot);
         RL_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_pair_place, dim3(grid_of(total)), dim3(kBlock), 0, st, total,
                            (const unsigned long long *)ekeys, (const uint8_t *)eflags, (const int2 *)erank, kshift,
-                           (const int *)poff, (const int *)pslot, pi, pj, img, flags, qrank);
+                           (const int *)poff, (const int *)pslot, pi, pj, img, flags, (const int *)qoff, qtmp);
         RL_HIP(hipGetLastError());
-        if (ix) *ix = PairIndex{poff, qoff, qrank};
+        if (ix) *ix = PairIndex{poff, qoff, qtmp};
         return RL_OK;
     }
     RL_HIP(search(std::integral_constant<int, kPairFill>{}));
@@ -1309,14 +1311,7 @@ __global__ void k_assemble(int64_t nc, const double *__restrict__ x, const doubl
         q[c] = qc;
         return;
     }
-    pk.pp[c] = make_int2(i, j);
-    double2 *gd = reinterpret_cast<double2 *>(pk.geo + 4 * c);
-    gd[0] = make_double2(ct.e.x, ct.e.y);
-    gd[1] = make_double2(ct.e.z, ct.s);
-    pk.geo2[c] = make_double2(ct.t, qc);
-    pk.qv[c] = qc;
-    pk.st[c] = make_double2(pk.gamma ? pk.gamma[c] : 0.0, 0.0);
-    pk.qtmp[pk.qptr[j] + pk.qrank[c]] = (int32_t)c;
+    pack_record(pk, c, i, j, ct.e.x, ct.e.y, ct.e.z, ct.s, ct.t, qc);
 }
 
 hipError_t launch_assemble(hipStream_t st, const rl_params &p, int64_t n, const double *x, const double *dir,

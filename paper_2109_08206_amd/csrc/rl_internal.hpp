@@ -212,13 +212,13 @@ namespace rl {
 enum Slot : int {
     kWsDir = 0, kWsCoef, kWsV, kWsUnc, kWsPptr, kWsQptr, kWsQidx, kWsQcnt, kWsG, kWsPartial,
     kWsCellOf, kWsCellCnt, kWsCellStart, kWsCellCur, kWsSorted, kWsXs, kWsDs, kWsLs, kWsPoff,
-    kWsStepPi, kWsStepPj, kWsStepImg, kWsStepPhi, kWsStepE, kWsStepArm, kWsStepQ, kWsStepGamma,
-    kWsStepU, kWsScan, kWsLenMax, kWsPP, kWsGeo, kWsSt, kWsAlpha, kWsQpos, kWsQgeo, kWsStq, kWsSortIdx, kWsSortTmp, kWsCellKey, kWsFs,
+    kWsStepPi, kWsStepPj, kWsStepImg, kWsStepPhi, kWsStepE, kWsStepArm, kWsStepGamma,
+    kWsStepU, kWsScan, kWsLenMax, kWsPP, kWsGeo, kWsSt, kWsAlpha, kWsQpos, kWsQgeo, kWsStq, kWsSortIdx, kWsSortTmp, kWsCellKey,
     kWsSt32, kWsStq32, kWsGeo32, kWsUP32, kWsQgeo32, kWsUQ32,
     kWsBatchTab, kWsBatchOff, kWsBatchState, kWsBatchAlpha, kWsBatchCtr, kWsBatchPartial,
-    kWsBatchPartial2, kWsBatchDone, kWsBatchMap, kWsGeo2, kWsPairCache, kWsScanTmp, kWsEmit, kWsPairCnt, kWsQrank,
+    kWsBatchPartial2, kWsBatchDone, kWsBatchMap, kWsGeo2, kWsPairCache, kWsScanTmp, kWsEmit, kWsPairCnt, kWsQtmp,
     kWsAdjG, kWsAdjUbar, kWsAdjQbd, kWsAdjCs, kWsAdjCr, kWsAdjCq, kWsAdjSc, kWsAdjPQ, kWsAdjDmob,
-    kWsAdjEbar, kWsAdjArmbar, kWsAdjQbar, kWsAdjDbar, kWsAdjGbar, kWsAdjFs, kWsQv, kWsUP, kWsUQ,
+    kWsAdjEbar, kWsAdjArmbar, kWsAdjQbar, kWsAdjDbar, kWsAdjGbar, kWsQv, kWsUP, kWsUQ,
     kWsGenKey, kWsGenKeyOut, kWsGenOrd, kWsGenPi, kWsGenPj, kWsGenE, kWsGenArm, kWsGenQ, kWsGenCmp, kWsGenGamma,
     kWsGenPsplit, kWsGenQsplit, kWsLinkLen, kWsLinkFlags, kWsInvPerm, kWsWallCnt, kWsWallOff,
     kWsCatPi, kWsCatPj, kWsCatE, kWsCatArm, kWsCatQ, kWsCatKind, kWsCatCmp, kWsCatLen, kWsStepUnc,
@@ -278,11 +278,10 @@ int sort_key_values(rl_ctx *h, int64_t m, const unsigned long long *keys, const 
 // slot and flags
 constexpr int kEmitBytes = 21;
 // Where the constraints of each rod are found, as the pair search leaves it
-// (all null: it does not): P lists as offsets, Q lists as offsets and the
-// place of each constraint in its list, in no particular order.
+// (all null: it does not): P lists as offsets, Q lists as offsets and entries
+// in no order inside a list.
 struct PairIndex {
-    const int32_t *pptr, *qptr;
-    const int *qrank;
+    const int32_t *pptr, *qptr, *qtmp;
 };
 // Pair list in the solver's own rod order (cell order).  On return *perm
 // (device, n) maps solver rod -> caller rod, xs/ds/ls hold the rods' centres,
@@ -294,17 +293,18 @@ int build_pairs_sorted(rl_ctx *h, int64_t n, const double *x, const double *dir,
 int assemble_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
                   int64_t nc, const int32_t *pi, const int32_t *pj, const int32_t *img, const double *F,
                   double *phi, double *e, double *arm, double *q);
-// the constraint records of a solve (see SolveArgs), and the Q lists unsorted
+// the constraint records of a solve (see SolveArgs), from the unsorted Q lists
 struct PackOut {
     const double *gamma;  // start, null: zeros
+    const int32_t *qptr, *qtmp;
     int2 *pp;
     double *geo;
     double2 *geo2;
     double *qv;
     double2 *st;
-    const int32_t *qptr;
-    const int *qrank;
-    int32_t *qtmp;
+    int32_t *qidx, *qpos;
+    double *qgeo;
+    double2 *stq;
 };
 // geometry of the library's own pairs; each of phi, e, arm, q and pk may be null
 hipError_t launch_assemble(hipStream_t st, const rl_params &p, int64_t n, const double *x, const double *dir,
@@ -312,12 +312,12 @@ hipError_t launch_assemble(hipStream_t st, const rl_params &p, int64_t n, const 
                            const int32_t *img, const double *Unc, double *phi, double *e, double *arm, double *q,
                            int *err, const PackOut *pk);
 // The same for a step's own pairs: their geometry goes straight into the
-// records (and to phi, e, arm where given); prepare_finish orders the Q lists,
-// from the start `gamma` if given, else from the one of prepare_step.
+// records (and to phi, e, arm where given), the start from gamma0 (null: zeros)
+// or, once it is known, from set_start.
 int prepare_step(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0, int64_t nc,
                  const int32_t *pi, const int32_t *pj, const int32_t *img, const double *Unc, const PairIndex &ix,
                  const double *gamma0, double *phi, double *e, double *arm, SolveArgs *a);
-int prepare_finish(rl_ctx *h, const SolveArgs &a, const double *gamma);
+int set_start(rl_ctx *h, const SolveArgs &a, const double *gamma);
 int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, double len0, int64_t nc,
                   const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
                   double *gamma, SolveArgs *a);

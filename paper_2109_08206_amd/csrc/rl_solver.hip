@@ -83,56 +83,38 @@ __global__ void k_check_pairs(int64_t n, int64_t nc, const int32_t *__restrict__
     qrank[c] = atomicAdd(qcnt + b, 1);
 }
 
-// constraint records: (pi, pj), (ex, ey, ez, s_i) and (s_j, q), q alone,
-// (gamma, g = 0), and its place in the Q lists, not yet in order
+// the Q lists, in no order inside a list
+__global__ void k_qbucket(int64_t nc, const int32_t *__restrict__ pj, const int32_t *__restrict__ qptr,
+                          const int *__restrict__ qrank, int32_t *__restrict__ qtmp)
+{
+    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (c < nc) qtmp[qptr[pj[c]] + qrank[c]] = (int32_t)c;
+}
+
+// constraint records on both sides, each constraint read once (see
+// pack_record).  Bound by the scattered Q side: 100,000 rods and 469,000 pairs
+// in the caller's order 41.6 us and 8.3 for the lists; packing the P side and
+// then gathering the Q side from it took 18 and 39, and a launch more in a step.
 __global__ void k_pack(int64_t nc, const int32_t *__restrict__ pi, const int32_t *__restrict__ pj,
                        const double *__restrict__ e, const double *__restrict__ arm, const double *__restrict__ q,
                        PackOut o)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (c >= nc) return;
-    const int r = pj[c];
-    o.pp[c] = make_int2(pi[c], r);
-    double2 *gd = reinterpret_cast<double2 *>(o.geo + 4 * c);
-    gd[0] = make_double2(e[3 * c], e[3 * c + 1]);
-    gd[1] = make_double2(e[3 * c + 2], arm[2 * c]);
-    const double qc = q ? q[c] : 0.0;
-    o.geo2[c] = make_double2(arm[2 * c + 1], qc);
-    o.qv[c] = qc;
-    o.st[c] = make_double2(o.gamma[c], 0.0);
-    o.qtmp[o.qptr[r] + o.qrank[c]] = (int32_t)c;
+    pack_record(o, c, pi[c], pj[c], e[3 * c], e[3 * c + 1], e[3 * c + 2], arm[2 * c], arm[2 * c + 1],
+                q ? q[c] : 0.0);
 }
 
-// The Q lists in ascending constraint order (which fixes the summation order
-// of the rod kernel): each entry to its rank among its rod's, with qpos (the
-// inverse), the geometry a rod needs on its Q side and the start iterate.  A
-// lane per entry reads its rod's list: 4.7 entries on average at 100,000 rods,
-// 468,000 constraints.
-__global__ void k_pack_q(int64_t nc, const int32_t *__restrict__ qtmp, const int32_t *__restrict__ qptr,
-                         const int2 *__restrict__ pp, const double *__restrict__ geo,
-                         const double2 *__restrict__ geo2, const double2 *__restrict__ st, int32_t *__restrict__ qidx,
-                         int32_t *__restrict__ qpos, double *__restrict__ qgeo, double2 *__restrict__ stq)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= nc) return;
-    const int c = qtmp[t], r = pp[c].y, b = qptr[r], e = qptr[r + 1];
-    int k = b;
-    for (int u = b; u < e; ++u) k += qtmp[u] < c;
-    qidx[k] = c;
-    qpos[c] = (int32_t)k;
-    const double2 *gd = reinterpret_cast<const double2 *>(geo + 4 * (int64_t)c);
-    const double2 g0 = gd[0], g1 = gd[1];
-    double2 *qd = reinterpret_cast<double2 *>(qgeo + 4 * (int64_t)k);
-    qd[0] = g0;
-    qd[1] = make_double2(g1.x, geo2[c].x);
-    stq[k] = st[c];
-}
-
-// a start that came after the records
-__global__ void k_set_start(int64_t nc, const double *__restrict__ gamma, double2 *__restrict__ st)
+// the iterate to a start that comes after the records, or back to the caller's
+// (after trial iterations)
+__global__ void k_restore_start(int64_t nc, const double *__restrict__ gamma_in, const int32_t *__restrict__ qpos,
+                                double2 *__restrict__ st, double2 *__restrict__ stq)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c < nc) st[c] = make_double2(gamma[c], 0.0);
+    if (c >= nc) return;
+    const double2 v = make_double2(gamma_in[c], 0.0);
+    st[c] = v;
+    stq[qpos[c]] = v;
 }
 
 __global__ void k_unpack_gamma(int64_t nc, const double2 *__restrict__ st, double *__restrict__ gamma)
@@ -551,7 +533,7 @@ static int solve_args(rl_ctx *h, int64_t n, const double *dir, const double *len
 static int32_t *unsorted_q(const SolveArgs &s) { return (int32_t *)s.uP; }
 static int *places_q(const SolveArgs &s) { return (int *)s.uQ; }
 
-// pptr, qptr and the places in the Q lists of a list of pairs; trusted: the
+// pptr, qptr and the unsorted Q lists of a list of pairs; trusted: the
 // library's own
 static int index_pairs(rl_ctx *h, const SolveArgs &s, const PrepWork &w, const int32_t *pi, const int32_t *pj,
                        bool trusted)
@@ -573,21 +555,28 @@ static int index_pairs(rl_ctx *h, const SolveArgs &s, const PrepWork &w, const i
         const int rc = device_scan(h, w.qcnt, n, w.qptr, nullptr, w.scan_tmp);
         if (rc) return rc;
     }
-    if (trusted) return RL_OK;
-    // a caller's list: its indices must be valid before the records scatter through pj
-    RL_HIP(hipStreamSynchronize(st));
-    const int ferr = ((int *)(h->host_scratch + 1))[0];
-    if (ferr) {
-        set_error(ferr & 1 ? "pair indices must satisfy 0 <= pi <= pj < n" : "pi must be non-decreasing");
-        return RL_ERR_ARG;
+    if (!trusted) {
+        // a caller's list: its indices must be valid before the lists scatter through pj
+        RL_HIP(hipStreamSynchronize(st));
+        const int ferr = ((int *)(h->host_scratch + 1))[0];
+        if (ferr) {
+            set_error(ferr & 1 ? "pair indices must satisfy 0 <= pi <= pj < n" : "pi must be non-decreasing");
+            return RL_ERR_ARG;
+        }
+    }
+    if (nc > 0) {
+        hipLaunchKernelGGL(k_qbucket, dim3(grid_of(nc)), dim3(kBlock), 0, st, nc, pj, (const int32_t *)w.qptr,
+                           (const int *)places_q(s), unsorted_q(s));
+        RL_HIP(hipGetLastError());
     }
     return RL_OK;
 }
 
-static PackOut pack_out(const SolveArgs &s, const double *gamma, const int *qrank)
+static PackOut pack_out(const SolveArgs &s, const double *gamma, const int32_t *qtmp)
 {
-    return PackOut{gamma, const_cast<int2 *>(s.pp), const_cast<double *>(s.geo), const_cast<double2 *>(s.geo2),
-                   const_cast<double *>(s.qv), s.st, s.qptr, qrank, unsorted_q(s)};
+    return PackOut{gamma, s.qptr, qtmp, const_cast<int2 *>(s.pp), const_cast<double *>(s.geo),
+                   const_cast<double2 *>(s.geo2), const_cast<double *>(s.qv), s.st, const_cast<int32_t *>(s.qidx),
+                   const_cast<int32_t *>(s.qpos), const_cast<double *>(s.qgeo), s.stq};
 }
 
 int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, double len0, int64_t nc,
@@ -599,9 +588,9 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
     if (!rc) rc = index_pairs(h, *out, w, pi, pj, false);
     if (rc || nc == 0) return rc;
     hipLaunchKernelGGL(k_pack, dim3(grid_of(nc)), dim3(kBlock), 0, h->stream, nc, pi, pj, e, arm, q,
-                       pack_out(*out, gamma, places_q(*out)));
+                       pack_out(*out, gamma, unsorted_q(*out)));
     RL_HIP(hipGetLastError());
-    return prepare_finish(h, *out, nullptr);
+    return RL_OK;
 }
 
 int prepare_step(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0, int64_t nc,
@@ -617,22 +606,16 @@ int prepare_step(rl_ctx *h, int64_t n, const double *x, const double *dir, const
         out->pptr = ix.pptr;
         out->qptr = ix.qptr;
     }
-    const PackOut pk = pack_out(*out, gamma0, own ? places_q(*out) : ix.qrank);
+    const PackOut pk = pack_out(*out, gamma0, own ? unsorted_q(*out) : ix.qtmp);
     RL_HIP(launch_assemble(h->stream, h->prm, n, x, dir, len, len0, nc, pi, pj, img, Unc, phi, e, arm, nullptr,
                            nullptr, &pk));
     return RL_OK;
 }
 
-int prepare_finish(rl_ctx *h, const SolveArgs &a, const double *gamma)
+int set_start(rl_ctx *h, const SolveArgs &a, const double *gamma)
 {
     if (a.nc == 0) return RL_OK;
-    if (gamma) {
-        hipLaunchKernelGGL(k_set_start, dim3(grid_of(a.nc)), dim3(kBlock), 0, h->stream, a.nc, gamma, a.st);
-        RL_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_pack_q, dim3(grid_of(a.nc)), dim3(kBlock), 0, h->stream, a.nc,
-                       (const int32_t *)unsorted_q(a), a.qptr, a.pp, a.geo, a.geo2, (const double2 *)a.st,
-                       const_cast<int32_t *>(a.qidx), const_cast<int32_t *>(a.qpos), const_cast<double *>(a.qgeo),
+    hipLaunchKernelGGL(k_restore_start, dim3(grid_of(a.nc)), dim3(kBlock), 0, h->stream, a.nc, gamma, a.qpos, a.st,
                        a.stq);
     RL_HIP(hipGetLastError());
     return RL_OK;
@@ -1007,17 +990,6 @@ hipError_t launch_unpack_gamma(hipStream_t st, const SolveArgs &a, double *gamma
     if (a.nc <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_unpack_gamma, dim3(grid_of(a.nc)), dim3(kBlock), 0, st, a.nc, (const double2 *)a.st, gamma);
     return hipGetLastError();
-}
-
-// the iterate back to the caller's start (after trial iterations)
-__global__ void k_restore_start(int64_t nc, const double *__restrict__ gamma_in, const int32_t *__restrict__ qpos,
-                                double2 *__restrict__ st, double2 *__restrict__ stq)
-{
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c >= nc) return;
-    const double2 v = make_double2(gamma_in[c], 0.0);
-    st[c] = v;
-    stq[qpos[c]] = v;
 }
 
 int integrate_impl(rl_ctx *h, int64_t n, const double *U, double *x, double *quat, double *xu)

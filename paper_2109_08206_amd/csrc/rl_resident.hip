@@ -1095,7 +1095,14 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         }
         const unsigned base = h->xchg_num;
         h->xchg_num += (unsigned)kResChunk + 8;
-        RL_HIP(launch_resident(st, a, plan, cg, words, base, tol, (long long)h->prm.max_iter, k0, k0 + kResChunk));
+        if (launch_resident(st, a, plan, cg, words, base, tol, (long long)h->prm.max_iter, k0, k0 + kResChunk) !=
+            hipSuccess) {
+            // no room for its workgroups on this device (a part of its compute
+            // units, say): the two kernels need none
+            (void)hipGetLastError();
+            h->xchg_skip = 64;
+            break;
+        }
         if (!copies)
             RL_HIP(hipMemcpyAsync(h->state_host, h->state, sizeof(SolverState), hipMemcpyDeviceToHost, st));
         RL_HIP(queue());

@@ -800,7 +800,9 @@ __global__ void k_pair_place(int64_t m, const unsigned long long *__restrict__ k
 // velocity of a rod under its external force and torque alone
 __device__ __forceinline__ void rod_unc(const Mob &m, const V3 &d, const V3 &f, const V3 &tq, double *out)
 {
-    store3(out, m.aperp * f + ((m.apar - m.aperp) * dot(d, f)) * d);
+    // (fused by hand, so that every kernel rounds alike)
+    const double k = (m.apar - m.aperp) * fma(d.z, f.z, fma(d.x, f.x, d.y * f.y));
+    store3(out, v3(fma(m.aperp, f.x, k * d.x), fma(m.aperp, f.y, k * d.y), fma(m.aperp, f.z, k * d.z)));
     store3(out + 3, m.rperp * tq);  // axial rotational mobility equals the normal one
 }
 
@@ -1295,22 +1297,22 @@ __global__ void k_assemble(int64_t nc, const double *__restrict__ x, const doubl
     const double Li = len ? len[i] : len0, Lj = len ? len[j] : len0;
     const Contact ct = closest_point(xi, di, 0.5 * Li, xj, dj, 0.5 * Lj);
     const double ph = ct.dist - diam;
-    // D^T U_nc: e.U_i + (s_i d_i x e).Omega_i - e.U_j - (t d_j x e).Omega_j
-    const V3 ui = load3(Unc + 6 * (int64_t)i), wi = load3(Unc + 6 * (int64_t)i + 3);
-    const V3 uj = load3(Unc + 6 * (int64_t)j), wj = load3(Unc + 6 * (int64_t)j + 3);
-    const double rate = dot(ct.e, ui) + dot(cross(ct.s * di, ct.e), wi) - dot(ct.e, uj) -
-                        dot(cross(ct.t * dj, ct.e), wj);
-    const double qc = ph / dt + rate;
     if (!PACK || phi) {
         phi[c] = ph;
         store3(e + 3 * c, ct.e);
         arm[2 * c] = ct.s;
         arm[2 * c + 1] = ct.t;
     }
+    // D^T U_nc: e.U_i + (s_i d_i x e).Omega_i - e.U_j - (t d_j x e).Omega_j
+    const V3 ui = load3(Unc + 6 * (int64_t)i), wi = load3(Unc + 6 * (int64_t)i + 3);
+    const V3 uj = load3(Unc + 6 * (int64_t)j), wj = load3(Unc + 6 * (int64_t)j + 3);
+    const double rate = dot(ct.e, ui) + dot(cross(ct.s * di, ct.e), wi) - dot(ct.e, uj) -
+                        dot(cross(ct.t * dj, ct.e), wj);
     if (!PACK) {
-        q[c] = qc;
+        q[c] = ph / dt + rate;
         return;
     }
+    const double qc = ph / dt + rate;
     pack_record(pk, c, i, j, ct.e.x, ct.e.y, ct.e.z, ct.s, ct.t, qc);
 }
 

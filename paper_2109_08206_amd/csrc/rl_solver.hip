@@ -342,23 +342,26 @@ __global__ void __launch_bounds__(kRodBlock) k_fin(SolveArgs a)
 // U = M (D gamma + F) per rod, with the full 6x6 block (external torques may
 // have an axial part; the axial rotational mobility equals the normal one).
 // `perm` (may be null) maps the solver's rod order to the caller's.  gamma
-// (may be null) receives the forces, host (may be null) the solver's state.
+// (may be null) receives the forces, host (may be null) the solver's state; with
+// it, queued behind a launch that may not have ended the solve, nothing else
+// unless that has (F may be U's array: the velocities are written once).
 template <bool UNI>
 __global__ void __launch_bounds__(kRodBlock)
     k_velocity(SolveArgs a, const double *__restrict__ F, const int *__restrict__ perm, double *__restrict__ U,
                double *__restrict__ gamma, SolverState *__restrict__ host)
 {
     if (host && blockIdx.x == 0 && threadIdx.x == 0) *host = *a.state;
+    const bool ended = !host || (a.state->done && !a.state->fail);
     const int sub = threadIdx.x & (kRodLanes - 1);
     const int64_t r = (int64_t)blockIdx.x * (kRodBlock / kRodLanes) + (threadIdx.x / kRodLanes);
     const bool active = r < a.n;
     RodLoads<> L;
     rod_load(a, r, active, sub, L);
-    if (gamma && active)
+    if (gamma && active && ended)
         for (int c = a.pptr[r] + sub; c < a.pptr[r + 1]; c += kRodLanes) gamma[c] = a.st[c].x;
     double f[3], m[3];
     rod_accumulate<kModeApply>(a, L, 0.0, f, m);
-    if (!active || sub != 0) return;
+    if (!active || sub != 0 || !ended) return;
     const int64_t ro = perm ? (int64_t)perm[r] : r;
     const double dx = a.dir[3 * r], dy = a.dir[3 * r + 1], dz = a.dir[3 * r + 2];
     // torque of the contact forces: dir x m

@@ -1,0 +1,49 @@
+"""What a solve on chip must leave as it is for the caller: arrays shared
+between inputs and outputs."""
+import numpy as np
+import pytest
+
+import oracle
+import rodsynth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _t(a, dtype=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=dtype, device="cuda")
+
+
+def _suspension(n, seed, phi):
+    """Arguments of solve_lcp, and of the solver, for a suspension."""
+    s = rodsynth.make_system(n, seed=seed, phi=phi)
+    d = oracle.directors(s.quat)
+    pr = oracle.pairs(s.x, d, 1.0, s.box, s.diam, s.cutoff)
+    cs = oracle.assemble(s.x, d, 1.0, s.box, s.diam, s.eta, s.dt, pr, s.force)
+    args = (_t(d), 1.0, _t(pr.pi, torch.int32), _t(pr.pj, torch.int32), _t(cs.e), _t(cs.arm), _t(cs.q))
+    return args, dict(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-8), _t(s.force)
+
+
+def _hub(n, seed=5):
+    """One rod in n - 1 contacts with the others."""
+    nc = n - 1
+    rng = np.random.default_rng(seed)
+    d, e = rng.normal(size=(n, 3)), rng.normal(size=(nc, 3))
+    d, e = d / np.linalg.norm(d, axis=1)[:, None], e / np.linalg.norm(e, axis=1)[:, None]
+    args = (_t(d), 1.0, _t(np.zeros(nc), torch.int32), _t(np.arange(1, n), torch.int32), _t(e),
+            _t(rng.uniform(-0.5, 0.5, (nc, 2))), _t(rng.uniform(-1.0, 0.2, nc)))
+    return args, dict(box=10.0, diam=0.08, cutoff=0.1, eta=1.0, dt=1e-3, tol=1e-8), _t(rng.normal(size=(n, 6)))
+
+
+@pytest.mark.parametrize("make", [lambda: _suspension(300, 3, 0.05), lambda: _hub(5001)],
+                         ids=["several launches", "fits no workgroup"])
+def test_velocities_in_the_array_of_the_forces(gpu_lib, make):
+    """U may be F's array: the velocities are computed once, from the forces,
+    also where a solve takes several launches or leaves the chip."""
+    args, prm, F = make()
+    with gpu_lib.Solver(**prm) as slv:
+        g0, U0, i0 = slv.solve_lcp(*args, F=F)
+        V = F.clone()
+        g1, U1, i1 = slv.solve_lcp(*args, F=V, U=V)
+    assert i0.status == gpu_lib.OK and i1.iterations == i0.iterations
+    assert torch.equal(g1, g0) and torch.equal(U1, U0)

@@ -48,6 +48,9 @@ struct SolverState {
     long long refreshes;
     int refresh;  // set by the rod kernel when the inner round ends
     int fail;     // solves on chip: 1 a wait ran out, 2 the problem does not fit
+    // of a problem that does not fit, from the workgroups where it does not:
+    // the most slots and rods with records (0 in a state without a failure)
+    int need_slots, need_rods;
 };
 
 // Per-rod mobility: a_par, a_perp (translation along / normal to the axis),
@@ -165,7 +168,7 @@ struct rl_ctx {
     int cus = 0;  // compute units
     // exchange words of the solves on chip: what of the buffer holds no
     // number above `xchg_num` (0: nothing yet), and solves left to the two
-    // kernels after one that did not fit or gave up waiting
+    // kernels after one that gave up waiting
     void *xchg_buf = nullptr;
     size_t xchg_cap = 0;
     unsigned xchg_num = 0;

@@ -404,7 +404,6 @@ __global__ void __launch_bounds__(T, 2)
         r1 = share[1];
     }
     const int c0 = a.pptr[r0], q0 = a.qptr[r0], own = a.pptr[r1] - c0, nq = a.qptr[r1] - q0;
-    bool fits = own < NC && nq <= NC;
     if (tid == 0) {
         share[2] = own;  // slots in use
         share[3] = 0;    // rods with records
@@ -415,16 +414,15 @@ __global__ void __launch_bounds__(T, 2)
     // slots of the Q lists: the owner's, or a second one for a constraint
     // whose P rod is elsewhere (its constraint left in `away` for now)
     int *ord = reinterpret_cast<int *>(U), *away = reinterpret_cast<int *>(U + NC);
-    if (fits)
-        for (int k = tid; k < nq; k += T) {
-            const int c = a.qidx[q0 + k];
-            int s = c - c0;
-            if (s < 0 || s >= own) {
-                s = atomicAdd(&share[2], 1);
-                if (s < NC) away[s] = c;
-            }
-            qslot[k] = (unsigned short)min(s, NC - 1);
+    for (int k = tid; k < nq; k += T) {
+        const int c = a.qidx[q0 + k];
+        int s = c - c0;
+        if (s < 0 || s >= own) {
+            s = atomicAdd(&share[2], 1);
+            if (s < NC) away[s] = c;
         }
+        if (k < NC) qslot[k] = (unsigned short)min(s, NC - 1);
+    }
     // the rods with records, by descending number of them: slot t of the
     // order goes to lanes ln t ... of the workgroup (which rod a thread holds
     // does not enter any sum)
@@ -447,7 +445,11 @@ __global__ void __launch_bounds__(T, 2)
     }
     __syncthreads();
     const int nrod = share[3];  // share[3] counts the velocities to send from here on
-    fits = fits && slots < NC && nrod <= cap;
+    const bool fits = slots < NC && nrod <= cap;  // (slots: of own constraints and of every Q record)
+    if (!fits && tid == 0) {
+        atomicMax(&S->need_slots, slots);
+        atomicMax(&S->need_rods, nrod);
+    }
     static_assert((R2 ? 2 : 1) * T <= 2 * NC, "the order fits in half of U");
     if (fits)
         for (int r = r0 + tid; r < r1; r += T) {
@@ -945,6 +947,7 @@ constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64
 // whether with their normals.
 constexpr int kResForms = 5;
 constexpr int kResSlots[kResForms] = {1024, 1536, 2048, 2560, 3072};
+constexpr int kResThreads = 512;  // threads of all but the smallest
 
 template <int T, int NC, int R1, int R2, bool HELD, bool MANY>
 static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, const ResCg *cg, const ResPlan &p,
@@ -979,7 +982,7 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
         // rods are in no spatial order: there the largest forms lose (100,000
         // rods, 281,000 constraints: 23.5 us per iteration, two kernels 20.8;
         // 50,000 and 90,000: 14.3 and 16.8).  A problem that does not fit
-        // after all is tried again with more slots.
+        // after all is tried again with as many slots as it asks for.
         const double reach = ordered ? 1.30 : 2.05;
         const int forms = ordered ? kResForms : 3;
         const int most = std::min(h->cus, kResMost);
@@ -1001,15 +1004,20 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
     // several lanes per rod while that leaves one rod per thread (the single
     // workgroup has two, and takes them for long lists)
     const bool two = p.groups == 1;
-    const int T = two && p.form == 0 ? 256 : 512;
+    const int T = two && p.form == 0 ? 256 : kResThreads;
     const double rods = two ? (double)n : 1.15 * (double)n / p.groups + 8.0;
     while (p.ln < 4 && (2 * p.ln * rods <= T || (two && 2 * p.ln * rods <= 2 * T && 2.0 * nc > 6.0 * p.ln * n)))
         p.ln *= 2;
     return p;
 }
 
-// the next larger form; false: there is none
-static bool resident_larger(ResPlan &p) { return p.groups > 1 && ++p.form < kResForms; }
+// The form that holds what the refused one did not; false: there is none.  (All
+// several-workgroup forms have the same threads.)
+static bool resident_larger(ResPlan &p, int slots, int rods)
+{
+    while (p.form < kResForms && kResSlots[p.form] <= slots) ++p.form;
+    return p.groups > 1 && p.form < kResForms && rods * p.ln <= kResThreads;
+}
 
 static int64_t resident_words(const ResPlan &p, int64_t nc)
 {
@@ -1100,7 +1108,6 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
             // no room for its workgroups on this device (a part of its compute
             // units, say): the two kernels need none
             (void)hipGetLastError();
-            h->xchg_skip = 64;
             break;
         }
         if (!copies)
@@ -1113,12 +1120,16 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
             k0 += kResChunk;
             continue;
         }
-        // left without a result: more slots, or the two kernels from the start
+        // left without a result: more slots, or the two kernels from the start.
+        // What does not fit is found again by each solve that does not (a
+        // launch of 20 to 30 us), so that the loop a problem takes, and with it
+        // the last bits of its solution, depends on the problem alone.
         *solved = false;
+        const int slots = h->state_host->need_slots, rods = h->state_host->need_rods;
         hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);
         RL_HIP(hipGetLastError());  // (clears the failure)
-        if (fail == 2 && k0 == 0 && resident_larger(plan)) continue;
-        h->xchg_skip = 64;
+        if (fail == 2 && k0 == 0 && resident_larger(plan, slots, rods)) continue;
+        if (fail != 2) h->xchg_skip = 64;
         break;
     }
     return RL_OK;

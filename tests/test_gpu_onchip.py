@@ -1,5 +1,6 @@
 """What a solve on chip must leave as it is for the caller: arrays shared
-between inputs and outputs."""
+between inputs and outputs, and the bits of a result whatever the handle
+solved before."""
 import numpy as np
 import pytest
 
@@ -47,3 +48,28 @@ def test_velocities_in_the_array_of_the_forces(gpu_lib, make):
         g1, U1, i1 = slv.solve_lcp(*args, F=V, U=V)
     assert i0.status == gpu_lib.OK and i1.iterations == i0.iterations
     assert torch.equal(g1, g0) and torch.equal(U1, U0)
+
+
+def test_results_do_not_depend_on_earlier_calls(gpu_lib):
+    """A problem that fits no workgroup sends no other one elsewhere: solution,
+    velocities and gradients have the bits of a fresh handle's."""
+    args, prm, F = _suspension(2500, 11, 0.02)
+    assert args[2].shape[0] >= 1536  # several workgroups
+    hub, hprm, hF = _hub(5001)
+    Ub = _t(np.random.default_rng(1).standard_normal((2500, 6)))
+
+    def run(slv):
+        slv.set_params(**prm)
+        g, U, info = slv.solve_lcp(*args, F=F)
+        *bars, ai = slv.solve_lcp_adjoint(*args, g, Ub, F=F)
+        return (g, U, *bars), (info.iterations, ai.cg_iterations)
+
+    with gpu_lib.Solver(**prm) as slv:
+        want, iters = run(slv)
+    with gpu_lib.Solver(**hprm) as slv:
+        h0, V0, _ = slv.solve_lcp(*hub, F=hF)
+        got, again = run(slv)
+        slv.set_params(**hprm)
+        h1, V1, _ = slv.solve_lcp(*hub, F=hF)
+    assert again == iters and all(torch.equal(a, b) for a, b in zip(got, want))
+    assert torch.equal(h0, h1) and torch.equal(V0, V1)

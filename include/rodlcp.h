@@ -561,6 +561,34 @@ int rl_kmc_links(rl_handle h, const rl_kmc_params *kp, const rl_crosslinkers *xl
 int rl_profile_enable(rl_handle h, int every);
 int rl_profile_read(rl_handle h, double *out);
 
+/* Solves on chip, for tests and measurement.  FP64 solves of contacts and
+ * general sets and the adjoint's conjugate gradients run in one launch where
+ * a form takes them, else as a loop of two kernels per iteration; which one
+ * is a rule on the problem alone.  rl_onchip_control replaces the rule or
+ * makes the handle meet what the rule cannot (c NULL: back to the rule):
+ *   groups > 0: this many workgroups (at most the device's compute units and
+ *     256), form `form` (0 to 4: 1,024, 1,536, 2,048, 2,560 or 3,072 slots per
+ *     workgroup; with groups = 1 form 0 or 1) and `lanes` (1, 2 or 4) lanes
+ *     per rod.  A problem that does not fit is refused as ever;
+ *   refuse: RL_ONCHIP_NO_MEMORY, _NO_ROOM: as if there were no memory for the
+ *     exchange, or no room for the workgroups on the device;
+ *   patience >= 0: polls before a wait between workgroups runs out, from the
+ *     launch's exchange number `patient` + 1 on (1: the one that finds out
+ *     whether the problem fits, then one per product and one that ends a solve
+ *     of contacts or a general set).
+ * rl_onchip_read writes to out[8] (host): solves on chip, launches refused
+ * because the problem did not fit, waits that ran out, solves without the
+ * memory or the room, and form, workgroups and lanes of the last launch (0
+ * workgroups: the two kernels); out[7] counts the handle's workspace
+ * allocations. */
+#define RL_ONCHIP_NO_MEMORY 1
+#define RL_ONCHIP_NO_ROOM 2
+typedef struct {
+    int32_t form, groups, lanes, refuse;
+    int64_t patience, patient;
+} rl_onchip;
+int rl_onchip_control(rl_handle h, const rl_onchip *c);
+int rl_onchip_read(rl_handle h, int64_t *out);
 
 #ifdef __cplusplus
 }

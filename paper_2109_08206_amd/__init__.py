@@ -99,6 +99,11 @@ XL_U, XL_SA, XL_SB, XL_D = 0, 1, 2, 3
 EV_NONE, EV_BIND, EV_UNBIND, EV_CROSS, EV_RELEASE = 0, 1, 2, 3, 4
 
 
+class OnChip(C.Structure):
+    _fields_ = [("form", C.c_int32), ("groups", C.c_int32), ("lanes", C.c_int32), ("refuse", C.c_int32),
+                ("patience", C.c_int64), ("patient", C.c_int64)]
+
+
 class AdjointInfo(C.Structure):
     _fields_ = [("cg_iterations", C.c_int64), ("cg_residual", C.c_double), ("n_active", C.c_int64),
                 ("status", C.c_int32), ("solve_status", C.c_int32), ("solve_iterations", C.c_int64),
@@ -110,7 +115,7 @@ SYMBOLS = ("rl_create", "rl_destroy", "rl_set_params", "rl_get_params", "rl_set_
            "rl_solve_lcp", "rl_step", "rl_profile_enable", "rl_profile_read", "rl_solve_lcp_batched",
            "rl_batch_tuning", "rl_solve_lcp_adjoint", "rl_step_adjoint", "rl_solve_lcp_noalloc",
            "rl_assemble_links", "rl_solve_general", "rl_assemble_walls", "rl_kmc_effective_volume", "rl_kmc_step",
-           "rl_kmc_links")
+           "rl_kmc_links", "rl_onchip_control", "rl_onchip_read")
 
 
 def load(path: Optional[str] = None) -> C.CDLL:
@@ -160,6 +165,8 @@ def load(path: Optional[str] = None) -> C.CDLL:
                              C.POINTER(C.c_int64)], C.c_int),
             "rl_kmc_links": ([H, C.POINTER(KmcParams), C.POINTER(RLCrosslinkers), I64, P, P, P, P, P, P,
                               C.POINTER(C.c_int64)], C.c_int),
+            "rl_onchip_control": ([H, C.POINTER(OnChip)], C.c_int),
+            "rl_onchip_read": ([H, C.POINTER(C.c_int64)], C.c_int),
         }
         for name, (args, res) in sig.items():
             fn = getattr(lib, name)
@@ -286,6 +293,19 @@ class Solver:
         out = (C.c_double * 4)()
         self._check(self.lib.rl_profile_read(self._h, out), "rl_profile_read")
         return {"rod_ms": out[0], "rod_launches": int(out[1]), "con_ms": out[2], "con_launches": int(out[3])}
+
+    def onchip_control(self, form=0, groups=0, lanes=1, refuse=0, patience=-1, patient=0):
+        """For tests and measurement: form, workgroups and lanes of solves on
+        chip, or what they have to do without (no arguments: the rule)."""
+        c = OnChip(form, groups, lanes, refuse, patience, patient)
+        self._check(self.lib.rl_onchip_control(self._h, C.byref(c)), "rl_onchip_control")
+
+    def onchip_read(self):
+        """Counts since the handle was made, and the last launch's form."""
+        out = (C.c_int64 * 8)()
+        self._check(self.lib.rl_onchip_read(self._h, out), "rl_onchip_read")
+        names = ("solves", "misfits", "timeouts", "refused", "form", "groups", "lanes", "allocations")
+        return dict(zip(names, (int(v) for v in out)))
 
     def reserve(self, max_rods, max_pairs):
         self._check(self.lib.rl_reserve(self._h, int(max_rods), int(max_pairs)), "rl_reserve")

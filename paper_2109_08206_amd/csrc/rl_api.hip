@@ -90,6 +90,7 @@ void *ws_get(rl_ctx *h, int s, size_t bytes, int *err)
     }
     h->buf[s] = p;
     h->cap[s] = want;
+    ++h->onchip_out[7];
     return p;
 }
 
@@ -781,6 +782,30 @@ int rl_profile_read(rl_handle h, double *out)
     out[3] = h->prof_cnt[1];
     h->prof_ms[0] = h->prof_ms[1] = 0.0;
     h->prof_cnt[0] = h->prof_cnt[1] = 0.0;
+    return RL_OK;
+}
+
+int rl_onchip_control(rl_handle h, const rl_onchip *c)
+{
+    RL_CHECK_HANDLE(h);
+    const rl_onchip rule{0, 0, 0, 0, -1, 0};
+    if (!c) c = &rule;
+    RL_REQUIRE(c->groups >= 0 && c->groups <= std::min(h->cus, kResMost), "rl_onchip_control: bad groups");
+    RL_REQUIRE(c->groups == 0 || ((c->lanes == 1 || c->lanes == 2 || c->lanes == 4) && c->form >= 0 &&
+                                  c->form < (c->groups == 1 ? 2 : kResForms)),
+               "rl_onchip_control: bad form or lanes");
+    RL_REQUIRE(c->refuse >= 0 && c->refuse <= RL_ONCHIP_NO_ROOM, "rl_onchip_control: bad refuse");
+    RL_REQUIRE(c->patience <= INT32_MAX && c->patient >= 0 && c->patient <= INT32_MAX,
+               "rl_onchip_control: bad patience");
+    h->onchip = *c;
+    return RL_OK;
+}
+
+int rl_onchip_read(rl_handle h, int64_t *out)
+{
+    RL_CHECK_HANDLE(h);
+    RL_REQUIRE(out != nullptr, "rl_onchip_read: NULL out");
+    for (int k = 0; k < 8; ++k) out[k] = h->onchip_out[k];
     return RL_OK;
 }
 

@@ -173,6 +173,8 @@ struct rl_ctx {
     size_t xchg_cap = 0;
     unsigned xchg_num = 0;
     int xchg_skip = 0;
+    rl_onchip onchip{0, 0, 0, 0, -1, 0};  // groups 0, patience below 0: the rule, the usual bound
+    int64_t onchip_out[8] = {};           // see rl_onchip_read
     // grow-only workspace slots
     static constexpr int kSlots = 128;
     void *buf[kSlots] = {};
@@ -326,6 +328,8 @@ int prepare_solve(rl_ctx *h, int64_t n, const double *dir, const double *len, do
                   double *gamma, SolveArgs *a);
 int apply_impl(rl_ctx *h, SolveArgs &a, double *w);
 // Solves that stay on chip (rl_resident.hip).
+constexpr int kResMost = 256;  // workgroups of a solve
+constexpr int kResForms = 5;   // forms of several workgroups
 // What the conjugate gradients of the adjoint read and leave, in the layout of
 // their two-kernel form: (lambda, p, mask, .), (r, s, ., .) and, in the order
 // of the Q lists, (., ., ., lambda).

@@ -57,9 +57,11 @@ struct Exchange {
                     // the workgroups, and of the groups of kTeam workgroups
     unsigned base;  // numbers base + 1, ... belong to this launch
     int *fail;      // set when a wait ran out (1) or the problem does not fit (2)
+    // polls of one word before the wait is given up, at numbers above base + patient
+    int patience;
+    unsigned patient;
 };
 
-constexpr int kResMost = 256;  // workgroups of a solve
 constexpr int kSlot = 32;      // words from one workgroup's sums to the next (256 bytes)
 // Above 64 workgroups their sums meet in two steps, teams of 16 and then the
 // teams: every workgroup polling 128 or 256 others takes 1.4 or 2.2 us, the
@@ -92,23 +94,24 @@ __device__ __forceinline__ double pair_value(u64 lo, u64 hi)
     return __hiloint2double((int)(hi >> 32), (int)(lo >> 32));
 }
 
-// whether poll number `spin` was one too many, or somebody else gave up
-__device__ __forceinline__ bool give_up(int spin, int *fail, int *bad)
+// whether poll number `spin` for number `num` was one too many, or somebody
+// else gave up
+__device__ __forceinline__ bool give_up(int spin, const Exchange &x, unsigned num, int *bad)
 {
-    if (spin < kSpin && ((spin & 1023) != 1023 ||
-                         __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
+    if (spin < (num - x.base > x.patient ? x.patience : kSpin) &&
+        ((spin & 1023) != 1023 || __hip_atomic_load(x.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
         return false;
-    __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(x.fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *bad = 1;
     return true;
 }
 
 // the two words of a number, polled until both carry `num`
-__device__ __forceinline__ double pair_wait(const u64 *p, unsigned num, int *fail, int *bad)
+__device__ __forceinline__ double pair_wait(const u64 *p, const Exchange &x, unsigned num, int *bad)
 {
     for (int spin = 0;; ++spin) {
         const u64 lo = word_get(p), hi = word_get(p + 1);
-        if (((unsigned)lo == num && (unsigned)hi == num) || give_up(spin, fail, bad)) return pair_value(lo, hi);
+        if (((unsigned)lo == num && (unsigned)hi == num) || give_up(spin, x, num, bad)) return pair_value(lo, hi);
     }
 }
 
@@ -470,7 +473,7 @@ __global__ void __launch_bounds__(T, 2)
         double c = 0.0;
         for (int i = tid; i < 4 * cnt; i += T) {
             const u64 *u = buf + (i >> 2) * kSlot + 2 * (i & 3);
-            c += pair_wait(u, num, x.fail, &bad);
+            c += pair_wait(u, x, num, &bad);
         }
         return c;
     };
@@ -502,7 +505,7 @@ __global__ void __launch_bounds__(T, 2)
             double c = 0.0;
             for (int i = tid; i < groups; i += T) {
                 const u64 *u = buf + i * kSlot;
-                c = fmax(c, pair_wait(u, num, x.fail, &bad));
+                c = fmax(c, pair_wait(u, x, num, &bad));
             }
             v = res_max<NW>(c, &red[0][0][0]);
         }
@@ -639,7 +642,7 @@ __global__ void __launch_bounds__(T, 2)
                 u64 v = 0;
                 for (int spin = 0;; ++spin) {
                     v = word_get(x.at + in[j]);
-                    if ((unsigned)v == num || give_up(spin, x.fail, &bad)) break;
+                    if ((unsigned)v == num || give_up(spin, x, num, &bad)) break;
                 }
                 in[j] = (unsigned)v == num ? 8u * (unsigned)(v >> 32) : 0u;
             }
@@ -691,7 +694,7 @@ __global__ void __launch_bounds__(T, 2)
                         else up[j] = v;
                         left &= ~(1u << j);
                     }
-                if (left && give_up(spin, x.fail, &bad)) break;
+                if (left && give_up(spin, x, num, &bad)) break;
             }
         }
 #pragma unroll
@@ -945,7 +948,6 @@ constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64
 
 // The forms: threads, slots, records held by a thread's first and second rod,
 // whether with their normals.
-constexpr int kResForms = 5;
 constexpr int kResSlots[kResForms] = {1024, 1536, 2048, 2560, 3072};
 constexpr int kResThreads = 512;  // threads of all but the smallest
 
@@ -970,6 +972,7 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
 {
     ResPlan p{0, 0, 1};
     if (nc <= 0 || nc >= (1 << 29)) return p;
+    if (h->onchip.groups > 0) return ResPlan{h->onchip.form, h->onchip.groups, h->onchip.lanes};
     if (n <= 512 && nc < 1024) {
         p.groups = 1;
     } else if (n <= 1024 && nc < kResSolo) {
@@ -1025,11 +1028,13 @@ static int64_t resident_words(const ResPlan &p, int64_t nc)
 }
 
 static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, const ResCg *cg,
-                           unsigned long long *words, unsigned base, double tol, long long max_iter, long long k0,
-                           long long kend)
+                                  const rl_onchip &ctl, unsigned long long *words, unsigned base, double tol,
+                                  long long max_iter, long long k0, long long kend)
 {
+    if (ctl.refuse == RL_ONCHIP_NO_ROOM) return hipErrorCooperativeLaunchTooLarge;
     u64 *at = words ? words + 2 * (int64_t)p.groups * kResSlots[p.form] : nullptr;
-    const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail};
+    const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail,
+                     ctl.patience < 0 ? kSpin : (int)ctl.patience, (unsigned)ctl.patient};
     if (p.groups == 1) {
         if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
         return launch_form<512, 2048, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
@@ -1089,6 +1094,7 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
     unsigned long long *words = nullptr;
     const int rc = resident_prepare(h, a, &plan, &words);
     if (rc) return rc;
+    h->onchip_out[5] = 0;
     // the launches start from a state without a failure, which they leave so
     if (plan.groups > 0 && !h->state_ready) {
         hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);
@@ -1103,11 +1109,16 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         }
         const unsigned base = h->xchg_num;
         h->xchg_num += (unsigned)kResChunk + 8;
-        if (launch_resident(st, a, plan, cg, words, base, tol, (long long)h->prm.max_iter, k0, k0 + kResChunk) !=
-            hipSuccess) {
+        int64_t *out = h->onchip_out;
+        out[4] = plan.form;
+        out[5] = plan.groups;
+        out[6] = plan.ln;
+        if (launch_resident(st, a, plan, cg, h->onchip, words, base, tol, (long long)h->prm.max_iter, k0,
+                            k0 + kResChunk) != hipSuccess) {
             // no room for its workgroups on this device (a part of its compute
             // units, say): the two kernels need none
             (void)hipGetLastError();
+            ++out[3];
             break;
         }
         if (!copies)
@@ -1118,8 +1129,10 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         const int fail = h->state_host->fail;
         if (!fail) {
             k0 += kResChunk;
+            out[0] += *solved;
             continue;
         }
+        ++out[fail == 2 ? 1 : 2];
         // left without a result: more slots, or the two kernels from the start.
         // What does not fit is found again by each solve that does not (a
         // launch of 20 to 30 us), so that the loop a problem takes, and with it
@@ -1132,6 +1145,7 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         if (fail != 2) h->xchg_skip = 64;
         break;
     }
+    if (!*solved) h->onchip_out[5] = 0;
     return RL_OK;
 }
 

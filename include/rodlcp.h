@@ -573,9 +573,10 @@ int rl_profile_read(rl_handle h, double *out);
  *   refuse: RL_ONCHIP_NO_MEMORY, _NO_ROOM: as if there were no memory for the
  *     exchange, or no room for the workgroups on the device;
  *   patience >= 0: polls before a wait between workgroups runs out, from the
- *     launch's exchange number `patient` + 1 on (1: the one that finds out
- *     whether the problem fits, then one per product and one that ends a solve
- *     of contacts or a general set).
+ *     solve's exchange number `patient` + 1 on (each launch of up to 2,048
+ *     iterations has 2,056 numbers: 1 finds out whether the problem fits, then
+ *     come one per product, after one for the conjugate gradients' start, and
+ *     one that ends a solve of contacts or a general set).
  * rl_onchip_read writes to out[8] (host): solves on chip, launches refused
  * because the problem did not fit, waits that ran out, solves without the
  * memory or the room, and form, workgroups and lanes of the last launch (0

@@ -51,6 +51,8 @@ struct SolverState {
     // of a problem that does not fit, from the workgroups where it does not:
     // the most slots and rods with records (0 in a state without a failure)
     int need_slots, need_rods;
+    // base + 1 of the last launch in which a workgroup left its results
+    unsigned left;
 };
 
 // Per-rod mobility: a_par, a_perp (translation along / normal to the axis),
@@ -339,7 +341,8 @@ struct ResCg {
 // Runs a prepared solve (or cg) on chip if a form takes it.  `queue` queues
 // what reads the result, after each launch; copies: among it the copy of the
 // state to state_host.  solved: state_host holds the stop.  Else nothing was
-// solved, and the iterate (and what cg holds) may be any of the solve.
+// solved, and the iterate is the caller's start (what cg holds may be any of
+// the solve).
 int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, const std::function<hipError_t()> &queue,
                  bool copies, bool *solved);
 // the Euler update that ends a step, queued behind the solve where it can be

@@ -57,8 +57,8 @@ struct Exchange {
                     // the workgroups, and of the groups of kTeam workgroups
     unsigned base;  // numbers base + 1, ... belong to this launch
     int *fail;      // set when a wait ran out (1) or the problem does not fit (2)
-    // polls of one word before the wait is given up, at numbers above base + patient
-    int patience;
+    // what the count of polls starts from at numbers above base + patient
+    int spent;
     unsigned patient;
 };
 
@@ -94,24 +94,29 @@ __device__ __forceinline__ double pair_value(u64 lo, u64 hi)
     return __hiloint2double((int)(hi >> 32), (int)(lo >> 32));
 }
 
-// whether poll number `spin` for number `num` was one too many, or somebody
-// else gave up
-__device__ __forceinline__ bool give_up(int spin, const Exchange &x, unsigned num, int *bad)
+// whether poll number `spin` was one too many, or somebody else gave up
+__device__ __forceinline__ bool give_up(int spin, int *fail, int *bad)
 {
-    if (spin < (num - x.base > x.patient ? x.patience : kSpin) &&
-        ((spin & 1023) != 1023 || __hip_atomic_load(x.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
+    if (spin < kSpin && ((spin & 1023) != 1023 ||
+                         __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
         return false;
-    __hip_atomic_store(x.fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *bad = 1;
     return true;
+}
+
+// the count of polls of a wait for number `num` before the first
+__device__ __forceinline__ int spent(const Exchange &x, unsigned num)
+{
+    return num - x.base > x.patient ? x.spent : 0;
 }
 
 // the two words of a number, polled until both carry `num`
 __device__ __forceinline__ double pair_wait(const u64 *p, const Exchange &x, unsigned num, int *bad)
 {
-    for (int spin = 0;; ++spin) {
+    for (int spin = spent(x, num);; ++spin) {
         const u64 lo = word_get(p), hi = word_get(p + 1);
-        if (((unsigned)lo == num && (unsigned)hi == num) || give_up(spin, x, num, bad)) return pair_value(lo, hi);
+        if (((unsigned)lo == num && (unsigned)hi == num) || give_up(spin, x.fail, bad)) return pair_value(lo, hi);
     }
 }
 
@@ -600,6 +605,9 @@ __global__ void __launch_bounds__(T, 2)
                 g[j] = st.y;
                 q[j] = a.qv[c];
                 if (BIL) cm[j] = a.cmpv[c];
+                // the start, for when a wait runs out after somebody's results
+                // are out (the two kernels' product is not in use here)
+                if (MANY && k0 == 0 && s < own) a.uP[c] = st.x;
             }
             if (MANY) {
                 const int r = a.pp[c].y;  // the Q rod (below 0: a fixed body)
@@ -640,9 +648,9 @@ __global__ void __launch_bounds__(T, 2)
         for (int j = 0; j < J; ++j)
             if ((cross >> j) & 1u) {
                 u64 v = 0;
-                for (int spin = 0;; ++spin) {
+                for (int spin = spent(x, num);; ++spin) {
                     v = word_get(x.at + in[j]);
-                    if ((unsigned)v == num || give_up(spin, x, num, &bad)) break;
+                    if ((unsigned)v == num || give_up(spin, x.fail, &bad)) break;
                 }
                 in[j] = (unsigned)v == num ? 8u * (unsigned)(v >> 32) : 0u;
             }
@@ -678,7 +686,7 @@ __global__ void __launch_bounds__(T, 2)
                     word_put(word(out[j] + high), half_word(__double2hiint(v), num));
                 }
             unsigned left = cross;
-            for (int spin = 0; left; ++spin) {
+            for (int spin = spent(x, num); left; ++spin) {
                 u64 lo[J], hi[J];
 #pragma unroll
                 for (int j = 0; j < J; ++j)
@@ -694,7 +702,7 @@ __global__ void __launch_bounds__(T, 2)
                         else up[j] = v;
                         left &= ~(1u << j);
                     }
-                if (left && give_up(spin, x, num, &bad)) break;
+                if (left && give_up(spin, x.fail, &bad)) break;
             }
         }
 #pragma unroll
@@ -913,6 +921,7 @@ __global__ void __launch_bounds__(T, 2)
     if (MANY) {
         __syncthreads();
         if (bad) return;  // the flag is set
+        if (tid == 0) __hip_atomic_store(&S->left, x.base + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -934,6 +943,18 @@ __global__ void __launch_bounds__(T, 2)
         S->status = status;
         S->done = done ? 1 : 0;
     }
+}
+
+// The start of a solve of contacts or a general set back from where the first
+// launch left it.
+__global__ void k_resident_start(SolveArgs a)
+{
+    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (c >= a.nc) return;
+    const double2 v = make_double2(a.uP[c], 0.0);
+    const int k = a.qpos[c];
+    a.st[c] = v;
+    if (k >= 0) a.stq[k] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1027,14 +1048,20 @@ static int64_t resident_words(const ResPlan &p, int64_t nc)
     return p.groups > 1 ? 2 * (int64_t)p.groups * kResSlots[kResForms - 1] + 2 * nc + 4 * (int64_t)kResMost * kSlot : 0;
 }
 
+// iterations of one launch of a solve on chip (under 20 ms), and the numbers
+// that its exchanges may take
+constexpr long long kResChunk = 2048, kResNumbers = kResChunk + 8;
+
 static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, const ResCg *cg,
                                   const rl_onchip &ctl, unsigned long long *words, unsigned base, double tol,
                                   long long max_iter, long long k0, long long kend)
 {
+    const long long patient = ctl.patient - k0 / kResChunk * kResNumbers;  // of this launch's exchanges
     if (ctl.refuse == RL_ONCHIP_NO_ROOM) return hipErrorCooperativeLaunchTooLarge;
     u64 *at = words ? words + 2 * (int64_t)p.groups * kResSlots[p.form] : nullptr;
     const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail,
-                     ctl.patience < 0 ? kSpin : (int)ctl.patience, (unsigned)ctl.patient};
+                     ctl.patience < 0 ? 0 : kSpin - (int)std::min<int64_t>(ctl.patience, kSpin),
+                     (unsigned)std::max(0ll, patient)};
     if (p.groups == 1) {
         if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
         return launch_form<512, 2048, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
@@ -1047,9 +1074,6 @@ static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResP
     default: return launch_form<512, 3072, 12, 0, false, true>(st, a, x, cg, p, tol, max_iter, k0, kend);
     }
 }
-
-// iterations of one launch of a solve on chip (under 20 ms)
-constexpr long long kResChunk = 2048;
 
 // The form of a solve on chip, and its exchange words cleared of any number
 // it could take for one of its own.  groups = 0: the two kernels take it
@@ -1075,12 +1099,16 @@ static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsign
     *words = (unsigned long long *)ws_get(h, kWsXchg, bytes, &err);
     if (err) return err;
     // a new buffer, the scratch array (anybody's) or numbers about to run out
-    const bool arena = h->arena_on;
-    if (arena || h->xchg_buf != *words || h->xchg_cap != h->cap[kWsXchg] || h->xchg_num > 0xf0000000u) {
+    // (the state, which holds one of them, begins anew with them)
+    const bool arena = h->arena_on, over = h->xchg_num > 0xf0000000u;
+    if (arena || h->xchg_buf != *words || h->xchg_cap != h->cap[kWsXchg] || over) {
         RL_HIP(hipMemsetAsync(*words, 0, arena ? bytes : h->cap[kWsXchg], h->stream));
         h->xchg_buf = arena ? nullptr : *words;
         h->xchg_cap = arena ? 0 : h->cap[kWsXchg];
-        h->xchg_num = 0;
+        if (over) {
+            h->xchg_num = 0;
+            h->state_ready = false;
+        }
     }
     return RL_OK;
 }
@@ -1108,7 +1136,7 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
             h->xchg_num = 0;
         }
         const unsigned base = h->xchg_num;
-        h->xchg_num += (unsigned)kResChunk + 8;
+        h->xchg_num += (unsigned)kResNumbers;
         int64_t *out = h->onchip_out;
         out[4] = plan.form;
         out[5] = plan.groups;
@@ -1139,6 +1167,11 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         // the last bits of its solution, depends on the problem alone.
         *solved = false;
         const int slots = h->state_host->need_slots, rods = h->state_host->need_rods;
+        // (results leave a workgroup after everybody's first launch has begun)
+        if (fail == 1 && !cg && (k0 > 0 || h->state_host->left == base + 1)) {
+            hipLaunchKernelGGL(k_resident_start, dim3((unsigned)((a.nc + 255) / 256)), dim3(256), 0, st, a);
+            RL_HIP(hipGetLastError());
+        }
         hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);
         RL_HIP(hipGetLastError());  // (clears the failure)
         if (fail == 2 && k0 == 0 && resident_larger(plan, slots, rods)) continue;

@@ -73,3 +73,47 @@ def test_results_do_not_depend_on_earlier_calls(gpu_lib):
         h1, V1, _ = slv.solve_lcp(*hub, F=hF)
     assert again == iters and all(torch.equal(a, b) for a, b in zip(got, want))
     assert torch.equal(h0, h1) and torch.equal(V0, V1)
+
+
+def _two_kernels(gpu_lib, prm, solve):
+    with gpu_lib.Solver(**prm) as slv:
+        slv.onchip_control(refuse=2)
+        return solve(slv)
+
+
+@pytest.mark.parametrize("phi,after,general", [
+    (0.04, 0, False), (0.04, 1, False), (0.04, 20, True), (0.04, "last", False), (0.04, "last", True),
+    (0.05, 2056 + 5, False)])
+def test_wait_that_runs_out(gpu_lib, phi, after, general):
+    """Without patience from an exchange on (the last one, when some workgroups
+    have left their results already, and one in a second launch among them) the
+    two kernels solve from the caller's start and give the bits they give alone."""
+    args, prm, F = _suspension(1500, 12, phi)
+    if after == 2056 + 5:
+        prm.update(tol=0.0, max_iter=3000)  # two launches
+    nc = args[2].shape[0]
+    start = _t(np.random.default_rng(3).uniform(-0.2, 1.0, nc))
+    rng = np.random.default_rng(4)
+    kind = _t(rng.random(nc) < 0.2, torch.uint8)
+    pj = args[3].clone()
+    pj[_t(rng.random(nc) < 0.1, torch.bool)] = -1
+
+    def solve(slv):
+        if general:
+            return slv.solve_general(args[0], args[1], args[2], pj, *args[4:], kind, kind.double() * 40.0, F=F,
+                                     gamma=start.clone())
+        return slv.solve_lcp(*args, F=F, gamma=start.clone())
+
+    g0, U0, i0 = _two_kernels(gpu_lib, prm, solve)
+    with gpu_lib.Solver(**prm) as slv:
+        slv.onchip_control(form=2, groups=64, lanes=2)
+        _, _, info = solve(slv)
+        assert slv.onchip_read()["solves"] == 1
+        # exchanges: whether it fits, the start's two products, the iterations, the end
+        last = 4 + info.iterations
+        assert info.iterations == 3000 if after == 2056 + 5 else info.iterations <= 2048
+        slv.onchip_control(form=2, groups=64, lanes=2, patience=0, patient=last - 1 if after == "last" else after)
+        g1, U1, i1 = solve(slv)
+        ran = slv.onchip_read()
+    assert ran["timeouts"] == 1 and ran["solves"] == 1
+    assert i1.iterations == i0.iterations and torch.equal(g1, g0) and torch.equal(U1, U0)

@@ -1095,9 +1095,15 @@ static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsign
         plan->groups = 0;  // the list itself fits, the exchange does not
         return RL_OK;
     }
-    int err = 0;
-    *words = (unsigned long long *)ws_get(h, kWsXchg, bytes, &err);
-    if (err) return err;
+    int err = h->onchip.refuse == RL_ONCHIP_NO_MEMORY ? RL_ERR_NOMEM : 0;
+    if (!err) *words = (unsigned long long *)ws_get(h, kWsXchg, bytes, &err);
+    if (err) {
+        // no memory for the exchange: the two kernels have all they need
+        h->xchg_buf = nullptr;
+        plan->groups = 0;
+        ++h->onchip_out[3];
+        return RL_OK;
+    }
     // a new buffer, the scratch array (anybody's) or numbers about to run out
     // (the state, which holds one of them, begins anew with them)
     const bool arena = h->arena_on, over = h->xchg_num > 0xf0000000u;

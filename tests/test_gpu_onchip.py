@@ -75,6 +75,20 @@ def test_results_do_not_depend_on_earlier_calls(gpu_lib):
     assert torch.equal(h0, h1) and torch.equal(V0, V1)
 
 
+def test_no_memory_for_the_exchange(gpu_lib):
+    """A problem that fitted without the exchange words still does."""
+    args, prm, F = _suspension(2500, 11, 0.02)
+    want = _two_kernels(gpu_lib, prm, lambda slv: slv.solve_lcp(*args, F=F))
+    with gpu_lib.Solver(**prm) as slv:
+        slv.onchip_control(refuse=1)
+        got = slv.solve_lcp(*args, F=F)
+        assert slv.onchip_read()["refused"] == 1 and slv.onchip_read()["groups"] == 0
+        slv.onchip_control()
+        slv.solve_lcp(*args, F=F)
+        assert slv.onchip_read()["solves"] == 1
+    assert got[2] == want[2] and torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def _two_kernels(gpu_lib, prm, solve):
     with gpu_lib.Solver(**prm) as slv:
         slv.onchip_control(refuse=2)

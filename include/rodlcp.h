@@ -273,7 +273,8 @@ int rl_assemble_walls(rl_handle h, int64_t n, const double *x, const double *dir
  * RL_NOALLOC_SCRATCH_BYTES that the library keeps on each device for the
  * life of the process.  The call makes no hipMalloc, hipFree or other
  * allocating call; the handle (rl_create) must already exist.  RL_FP64 only;
- * kernel-event sampling (rl_profile_enable) is ignored.
+ * no kernel is sampled, but with rl_profile_enable on the loop is the one
+ * that sampling needs, as in rl_solve_lcp.
  * Workspace: 152 bytes per constraint and 12 bytes per rod (36 with per-rod
  * lengths) plus a few KB (e.g. 100,000 rods with 468,687 constraints take
  * 73 MB); a larger problem returns RL_ERR_ARG with nothing enqueued.
@@ -555,7 +556,12 @@ int rl_kmc_links(rl_handle h, const rl_kmc_params *kp, const rl_crosslinkers *xl
 /* Kernel timing with HIP events on the handle's stream, for measurement.
  * With every > 0, every every-th BBPGD iteration of later solves records
  * events around its rod kernel and its constraint kernel (iterations after
- * convergence are not counted); every = 0 turns it off.  rl_profile_read
+ * convergence are not counted); every = 0 turns it off.  Sampling changes the
+ * solve: there are two kernels per iteration only in the loop over memory, so
+ * a sampled handle runs that one throughout (and the adjoint's), where it
+ * would run small and middle-sized problems on chip in one launch: 1.4 to 4
+ * times the time per iteration, other rounding, hence other iterates and
+ * another iteration count, to the same tolerance.  rl_profile_read
  * writes {rod_ms_total, rod_launches, constraint_ms_total,
  * constraint_launches} to out[4] (host) and resets the totals. */
 int rl_profile_enable(rl_handle h, int every);

@@ -1077,12 +1077,13 @@ static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResP
 
 // The form of a solve on chip, and its exchange words cleared of any number
 // it could take for one of its own.  groups = 0: the two kernels take it
-// (sampled timing of the loop kernels needs them too).
+// (sampled timing of the loop kernels needs them too, and
+// the allocation-free solve, which takes no samples, has the same bits).
 static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsigned long long **words)
 {
     *words = nullptr;
     plan->groups = 0;
-    if (h->prm.precision != RL_FP64 || (h->prof_every > 0 && !h->arena_on)) return RL_OK;
+    if (h->prm.precision != RL_FP64 || h->prof_every > 0) return RL_OK;
     *plan = resident_plan(h, a.n, a.nc, a.ordered);
     if (plan->groups <= 1) return RL_OK;
     if (h->xchg_skip > 0) {

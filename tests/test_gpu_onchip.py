@@ -131,3 +131,16 @@ def test_wait_that_runs_out(gpu_lib, phi, after, general):
         ran = slv.onchip_read()
     assert ran["timeouts"] == 1 and ran["solves"] == 1
     assert i1.iterations == i0.iterations and torch.equal(g1, g0) and torch.equal(U1, U0)
+
+
+def test_noalloc_is_solve_lcp_when_sampled(gpu_lib):
+    """Kernel sampling takes the two-kernel loop: in both calls."""
+    args, prm, F = _suspension(2500, 11, 0.02)
+    with gpu_lib.Solver(**prm) as slv:
+        slv.profile_enable(8)
+        g0, U0, i0 = slv.solve_lcp(*args, F=F)
+        taken = slv.profile_read()
+        g1, U1 = torch.zeros_like(g0), torch.empty_like(U0)
+        g1, U1, i1 = slv.solve_lcp_noalloc(*args, g1, U1, F=F)
+        assert taken["rod_launches"] > 0 and slv.profile_read()["rod_launches"] == 0
+    assert i0 == i1 and torch.equal(g0, g1) and torch.equal(U0, U1)

@@ -124,7 +124,10 @@ int rl_get_params(rl_handle h, rl_params *prm);
 /* hip_stream: a hipStream_t (e.g. torch.cuda.current_stream().cuda_stream). */
 int rl_set_stream(rl_handle h, void *hip_stream);
 /* Pre-size the workspace for up to max_rods rods and max_pairs constraints
- * so that later calls of that size allocate nothing. */
+ * so that later FP64 calls of that size to rl_step without links and walls
+ * (warm-started, with the stress or with noise as well), rl_solve_lcp and
+ * rl_build_pairs (of a capacity up to max_pairs) allocate nothing, as long as
+ * the search's cells are no more than max_rods or 4,096. */
 int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs);
 const char *rl_status_str(int status);
 const char *rl_last_error(void);

@@ -418,26 +418,45 @@ int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs)
     RL_REQUIRE(max_rods >= 0 && max_pairs >= 0 && max_pairs < 0x7fffffff, "rl_reserve: bad sizes");
     int err = 0;
     const int64_t n = max_rods > 0 ? max_rods : 1, nc = max_pairs > 0 ? max_pairs : 1;
+    // the cells of a search are not known yet (the rods' lengths are not): up
+    // to as many as rods, of eight bins each in the caller's order (up to 2^20)
+    const int64_t cells = std::min<int64_t>(std::max<int64_t>(n, 4096), 1 << 26);
+    const int64_t bins = std::max<int64_t>(cells, std::min<int64_t>(8 * cells, 1 << 23));
+    size_t scan = 0, sort = 0;
+    int rc = scan_tmp_bytes(bins, &scan);
+    if (!rc) rc = sort_tmp_bytes(n, nc, &sort);
+    if (rc) return rc;
     const size_t sz[][2] = {
         {kWsDir, sizeof(double) * 3 * n},  {kWsCoef, sizeof(double) * 3 * n},  {kWsV, sizeof(double) * 6 * n},
         {kWsUnc, sizeof(double) * 6 * n},  {kWsPptr, sizeof(int) * (n + 1)},   {kWsQptr, sizeof(int) * (n + 1)},
-        {kWsQidx, sizeof(int) * nc},       {kWsQcnt, sizeof(int) * n},         {kWsG, sizeof(double) * nc},
+        {kWsQidx, sizeof(int) * nc},       {kWsQcnt, sizeof(int) * (n + 1)},   {kWsG, sizeof(double) * nc},
         {kWsPartial, sizeof(double) * 8 * kConGridMax},
         {kWsCellOf, sizeof(int) * n},      {kWsSorted, sizeof(int) * n},       {kWsXs, sizeof(double) * 3 * n},
         {kWsDs, sizeof(double) * 3 * n},   {kWsLs, sizeof(double) * n},        {kWsStepUnc, sizeof(double) * 6 * n},
         {kWsPoff, sizeof(int) * (n + 1)},  {kWsStepPi, sizeof(int) * nc},      {kWsStepPj, sizeof(int) * nc},
-        {kWsStepImg, sizeof(int) * nc},    {kWsQtmp, sizeof(int) * nc},        {kWsEmit, (size_t)kEmitBytes * nc},
+        {kWsStepImg, sizeof(int) * nc},    {kWsQtmp, sizeof(int) * nc},
+        {kWsPairCnt, sizeof(int) * (4 + bins + 2 * n)}, {kWsCellStart, sizeof(int) * (bins + 1)},
+        {kWsCellCur, sizeof(int) * n},     {kWsCellKey, sizeof(int) * n},      {kWsSortIdx, sizeof(int) * n},
+        {kWsScan, sizeof(int64_t) * 2},    {kWsLenMax, sizeof(int64_t)},       {kWsScanTmp, scan},
+        {kWsSortTmp, sort},                {kWsFtot, sizeof(double) * 6 * n},
+        {kWsStepPhi, sizeof(double) * nc}, {kWsStepE, sizeof(double) * 3 * nc}, {kWsStepArm, sizeof(double) * 2 * nc},
         {kWsStepGamma, sizeof(double) * nc}, {kWsStepU, sizeof(double) * 6 * n}, {kWsQv, sizeof(double) * nc},
         {kWsUP, sizeof(double) * nc},      {kWsUQ, sizeof(double) * nc},
         {kWsPP, sizeof(int) * 2 * nc},     {kWsGeo, sizeof(double) * 4 * nc}, {kWsGeo2, sizeof(double) * 2 * nc},  {kWsSt, sizeof(double) * 2 * nc},
         {kWsAlpha, sizeof(double) * 2},    {kWsQpos, sizeof(int) * nc},        {kWsQgeo, sizeof(double) * 4 * nc},
-        {kWsStq, sizeof(double) * 2 * nc},
+        {kWsStq, sizeof(double) * 2 * nc}, {kWsXchg, resident_bytes(h, n, nc)},
+        {kWsWarmKeys, sizeof(int64_t) * nc}, {kWsWarmKeysNew, sizeof(int64_t) * nc},
+        {kWsWarmGam, sizeof(double) * nc}, {kWsWarmGamNew, sizeof(double) * nc}, {kWsStress, kStressBytes},
     };
     for (auto &e : sz) {
-        ws_get(h, (int)e[0], e[1], &err);
+        if (e[1] > 0) ws_get(h, (int)e[0], e[1], &err);
         if (err) return err;
     }
-    return RL_OK;
+    // a step's search makes use of all that the lists of pairs hold
+    ws_get(h, kWsEmit, kEmitBytes * (h->cap[kWsStepPi] / sizeof(int32_t)), &err);
+    if (err) return err;
+    ws_get_host(h, kStressBytes, &err);
+    return err;
 }
 
 int rl_directors(rl_handle h, int64_t n, const double *quat, double *dir)

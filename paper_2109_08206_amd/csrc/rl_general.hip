@@ -479,7 +479,7 @@ int step_stress(rl_ctx *h, const StepList &L, const double *gamma, double *out)
 {
     const rl_params &p = h->prm;
     const int64_t m = L.np + L.nl;
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((m + kStressBlock - 1) / kStressBlock, 512));
+    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((m + kStressBlock - 1) / kStressBlock, kStressGrid));
     int werr = 0;
     double *part = (double *)ws_get(h, kWsStress, sizeof(double) * 18 * grid, &werr);
     if (werr) return werr;

@@ -245,6 +245,8 @@ void set_error(const char *fmt, ...);
 // Internal building blocks used by the C-ABI layer.
 int build_pairs_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,
                      int64_t capacity, int32_t *pi, int32_t *pj, int32_t *img, uint8_t *flags, int64_t *n_pairs);
+// scratch of the sorts of n rods and of m forces by their keys
+int sort_tmp_bytes(int64_t n, int64_t m, size_t *bytes);
 int stable_sort_by_key(rl_ctx *h, int64_t n, const int *keys, int bits, int *keys_out, int *perm);
 
 // Filaments binned by centre into periodic cells of edge >= L_max/2 +
@@ -332,6 +334,8 @@ int apply_impl(rl_ctx *h, SolveArgs &a, double *w);
 // Solves that stay on chip (rl_resident.hip).
 constexpr int kResMost = 256;  // workgroups of a solve
 constexpr int kResForms = 5;   // forms of several workgroups
+// the most that the exchange of a solve of up to n rods and nc constraints takes
+size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc);
 // What the conjugate gradients of the adjoint read and leave, in the layout of
 // their two-kernel form: (lambda, p, mask, .), (r, s, ., .) and, in the order
 // of the Q lists, (., ., ., lambda).
@@ -428,6 +432,8 @@ int warm_lookup(rl_ctx *h, const StepList &L, double *gamma0);
 // keeps this step's keys and forces (gamma in input order)
 int warm_store(rl_ctx *h, const StepList &L, const double *gamma);
 // the 18 stress components (host) from the forces in input order
+constexpr int kStressGrid = 512;
+constexpr size_t kStressBytes = sizeof(double) * 18 * kStressGrid;
 int step_stress(rl_ctx *h, const StepList &L, const double *gamma, double *out);
 // wall contacts of rods (x, dir, len in one order; Unc = M F in the same)
 int walls_impl(rl_ctx *h, int64_t n, const double *x, const double *dir, const double *len, double len0,

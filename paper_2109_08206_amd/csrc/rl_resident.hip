@@ -1048,6 +1048,12 @@ static int64_t resident_words(const ResPlan &p, int64_t nc)
     return p.groups > 1 ? 2 * (int64_t)p.groups * kResSlots[kResForms - 1] + 2 * nc + 4 * (int64_t)kResMost * kSlot : 0;
 }
 
+size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc)
+{
+    const ResPlan most{kResForms - 1, std::min(h->cus, kResMost), 1};
+    return n <= 1024 && nc < kResSolo ? 0 : sizeof(u64) * (size_t)resident_words(most, nc);
+}
+
 // iterations of one launch of a solve on chip (under 20 ms), and the numbers
 // that its exchanges may take
 constexpr long long kResChunk = 2048, kResNumbers = kResChunk + 8;

@@ -1,5 +1,7 @@
 // Stable key-value radix sort (rocPRIM through hipCUB), used to put rods in
 // cell order deterministically: equal cells keep ascending rod index.
+#include <algorithm>
+
 #include <hipcub/hipcub.hpp>
 
 #include "rl_internal.hpp"
@@ -137,6 +139,20 @@ int device_scan(rl_ctx *h, const int *in, int64_t m, int *out, int64_t *total, v
     }
     hipLaunchKernelGGL(k_scan_ends, dim3(1), dim3(64), 0, st, m, out, total);
     RL_HIP(hipGetLastError());
+    return RL_OK;
+}
+
+int sort_tmp_bytes(int64_t n, int64_t m, size_t *bytes)
+{
+    size_t rods = 0, forces = 0;
+    const int *k = nullptr;
+    const unsigned long long *w = nullptr;
+    const double *v = nullptr;
+    RL_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, rods, k, (int *)nullptr, k, (int *)nullptr, (int)n, 0, 31,
+                                              (hipStream_t)0));
+    RL_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, forces, w, (unsigned long long *)nullptr, v, (double *)nullptr,
+                                              (int)m, 0, 64, (hipStream_t)0));
+    *bytes = std::max(rods, forces);
     return RL_OK;
 }
 

@@ -144,3 +144,33 @@ def test_noalloc_is_solve_lcp_when_sampled(gpu_lib):
         g1, U1, i1 = slv.solve_lcp_noalloc(*args, g1, U1, F=F)
         assert taken["rod_launches"] > 0 and slv.profile_read()["rod_launches"] == 0
     assert i0 == i1 and torch.equal(g0, g1) and torch.equal(U0, U1)
+
+
+@pytest.mark.parametrize("n,phi,lengths", [(700, 0.02, False), (6000, 0.02, True), (20_000, 0.03, False)])
+def test_reserved_sizes_allocate_nothing(gpu_lib, n, phi, lengths):
+    """After rl_reserve the first search, steps (plain, warm-started, with the
+    stress, with noise) and solve of that size take no workspace."""
+    s = rodsynth.make_system(n, seed=6, phi=phi, length=(0.5, 1.5) if lengths else 1.0)
+    L = _t(s.length) if lengths else 1.0
+    quat, F = _t(s.quat), _t(s.force)
+    prm = dict(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-8, max_iter=50)
+    with gpu_lib.Solver(**prm) as slv:
+        dirs = slv.directors(quat)
+        pi, pj, img, _ = slv.build_pairs(_t(s.x), dirs, L)
+        most = pi.shape[0]
+        _, e, arm, q = slv.assemble_D(_t(s.x), dirs, L, pi, pj, img, F)
+    calls = {
+        "search": lambda slv: slv.build_pairs(_t(s.x), dirs, L, capacity=most),
+        "step": lambda slv: slv.step(_t(s.x), quat.clone(), L, F=F),
+        "warm step": lambda slv: slv.step(_t(s.x), quat.clone(), L, F=F, warm_start=True),
+        "step with stress": lambda slv: slv.step(_t(s.x), quat.clone(), L, F=F, stress=True),
+        "step with noise": lambda slv: slv.step(_t(s.x), quat.clone(), L, F=F, kT=0.004,
+                                                noise=torch.ones((n, 6), dtype=torch.float64, device="cuda")),
+        "solve": lambda slv: slv.solve_lcp(dirs, L, pi, pj, e, arm, q, F=F),
+    }
+    for name, call in calls.items():
+        with gpu_lib.Solver(**prm) as slv:
+            slv.reserve(n, most)
+            before = slv.onchip_read()["allocations"]
+            call(slv)
+            assert slv.onchip_read()["allocations"] == before, name

@@ -1033,13 +1033,8 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         return hipGetLastError();
     };
     bool reported = false;
+    int64_t total = 0;
     if (emit) {
-        const int64_t ecap = capacity > 0 ? capacity : 0, eb = ecap > 0 ? ecap : 1;
-        ekeys = (unsigned long long *)ws_get(h, kWsEmit, (size_t)kEmitBytes * eb, &werr);
-        if (werr) return werr;
-        erank = (int2 *)(ekeys + eb);
-        pslot = (int *)(erank + eb);
-        eflags = (uint8_t *)(pslot + eb);
         // two waves per neighbour cell, each on a part of the home rods, up to
         // about 1,500 cells (100,000 rods, 729 cells: 422 us for the whole
         // search with one, 352 with two, 359 with three, 390 with four), four
@@ -1048,21 +1043,42 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         const int rparts = (int)std::max<int64_t>(1, std::min<int64_t>(4, 40000 / (ncell * ns)));
         const int split = (int)std::max<int64_t>(
             1, std::min<int64_t>(((ns / 2 + 1) * rparts + kEmitWaves - 1) / kEmitWaves, 8192 / ncell));
-        auto go = [&](auto order) {
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs_emit<decltype(order)::value>), dim3((unsigned)(ncell * split)),
-                               pblock, 0, st, g, cshift, p.diam, p.cutoff, (const int *)sorted, (const double *)xs,
-                               (const double *)ds, (const double *)ls, (const int *)cell_start, ec, ekeys, eflags,
-                               erank, ecap, kshift, split, rparts, 0.5f * (float)Lmax * (1.0f + 1e-6f));
-            return hipGetLastError();
-        };
-        RL_HIP(internal ? go(std::true_type{}) : go(std::false_type{}));
-        if (one) {
-            // the offsets while the host learns the number of pairs
-            RL_HIP(launch_scan_one(st, n, pcnt, poff, ec.q, qoff, nullptr,
-                                   ScanReport{ec.emitted, ec.err, h->host_scratch}));
-            reported = true;
-        } else {
-            RL_HIP(hipMemcpyAsync(h->host_scratch, counts, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        // The workspace follows the pairs there are, not the room that the
+        // caller has for them: at first as many as it holds, or 32 per rod (the
+        // densest suspensions have 12); a search that finds more runs again.
+        const int64_t room = std::max<int64_t>(capacity, 0);
+        int64_t ecap = internal ? room
+                                : std::min(room, std::max<int64_t>((int64_t)(h->cap[kWsEmit] / kEmitBytes),
+                                                                   32 * n + 4096));
+        for (;; ecap = total) {
+            const int64_t eb = std::max<int64_t>(ecap, 1);
+            ekeys = (unsigned long long *)ws_get(h, kWsEmit, (size_t)kEmitBytes * eb, &werr);
+            if (werr) return werr;
+            erank = (int2 *)(ekeys + eb);
+            pslot = (int *)(erank + eb);
+            eflags = (uint8_t *)(pslot + eb);
+            auto go = [&](auto order) {
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_pairs_emit<decltype(order)::value>),
+                                   dim3((unsigned)(ncell * split)), pblock, 0, st, g, cshift, p.diam, p.cutoff,
+                                   (const int *)sorted, (const double *)xs, (const double *)ds, (const double *)ls,
+                                   (const int *)cell_start, ec, ekeys, eflags, erank, ecap, kshift, split, rparts,
+                                   0.5f * (float)Lmax * (1.0f + 1e-6f));
+                return hipGetLastError();
+            };
+            RL_HIP(internal ? go(std::true_type{}) : go(std::false_type{}));
+            if (one) {
+                // the offsets while the host learns the number of pairs
+                RL_HIP(launch_scan_one(st, n, pcnt, poff, ec.q, qoff, nullptr,
+                                       ScanReport{ec.emitted, ec.err, h->host_scratch}));
+                reported = true;
+            } else {
+                RL_HIP(hipMemcpyAsync(h->host_scratch, counts, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+            }
+            RL_HIP(hipStreamSynchronize(st));
+            total = h->host_scratch[0];
+            if (total <= ecap || total > capacity || ((int *)(h->host_scratch + 1))[0]) break;
+            RL_HIP(hipMemsetAsync(ec.emitted, 0, sizeof(*ec.emitted), st));
+            RL_HIP(hipMemsetAsync(pcnt, 0, sizeof(int) * n, st));
         }
     } else {
         RL_HIP(search(std::integral_constant<int, kPairCount>{}));
@@ -1070,9 +1086,9 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         if (rc) return rc;
         RL_HIP(hipMemcpyAsync(h->host_scratch, tot, sizeof(int64_t), hipMemcpyDeviceToHost, st));
         RL_HIP(hipMemcpyAsync(h->host_scratch + 1, ec.err, sizeof(int), hipMemcpyDeviceToHost, st));
+        RL_HIP(hipStreamSynchronize(st));
+        total = h->host_scratch[0];
     }
-    RL_HIP(hipStreamSynchronize(st));
-    const int64_t total = h->host_scratch[0];
     const int ferr = ((int *)(h->host_scratch + 1))[0];
     if (ferr & 1) {
         set_error("pair search: non-finite centre or director");

@@ -578,7 +578,8 @@ int rl_profile_read(rl_handle h, double *out);
  *   groups > 0: this many workgroups (at most the device's compute units and
  *     256), form `form` (0 to 4: 1,024, 1,536, 2,048, 2,560 or 3,072 slots per
  *     workgroup; with groups = 1 form 0 or 1) and `lanes` (1, 2 or 4) lanes
- *     per rod.  A problem that does not fit is refused as ever;
+ *     per rod, however long the lists.  A problem that does not fit is refused
+ *     as ever;
  *   refuse: RL_ONCHIP_NO_MEMORY, _NO_ROOM: as if there were no memory for the
  *     exchange, or no room for the workgroups on the device;
  *   patience >= 0: polls before a wait between workgroups runs out, from the

@@ -49,7 +49,8 @@ struct SolverState {
     int refresh;  // set by the rod kernel when the inner round ends
     int fail;     // solves on chip: 1 a wait ran out, 2 the problem does not fit
     // of a problem that does not fit, from the workgroups where it does not:
-    // the most slots and rods with records (0 in a state without a failure)
+    // the most slots and rods with records (0 in a state without a failure;
+    // INT_MAX rods where a list is too long for it)
     int need_slots, need_rods;
     // base + 1 of the last launch in which a workgroup left its results
     unsigned left;

@@ -375,14 +375,16 @@ __device__ __forceinline__ int res_boundary(const SolveArgs &a, int n, int64_t t
 // T slots per thread; K rods per thread (1 or 2); HELD: the rods hold the
 // normals of their records in registers; KIND: a contact set, a general set,
 // or the conjugate gradients of a contact set's adjoint; MANY: several
-// workgroups.  ln: lanes per rod.  The launch runs iterations k0 .. kend - 1
+// workgroups.  ln: lanes per rod; a rod with more than `longest` records is
+// refused.  The launch runs iterations k0 .. kend - 1
 // at most (k0 = 0: the start phases first); a stop is latched in the state,
 // else the iterate and the step length are left for the next launch.
 enum ResKind { kResContacts, kResGeneral, kResCg };
 
 template <int T, int NC, int R1, int R2, bool HELD, ResKind KIND, bool MANY>
 __global__ void __launch_bounds__(T, 2)
-    k_resident(SolveArgs a, Exchange x, ResCg io, int ln, double tol, long long max_iter, long long k0, long long kend)
+    k_resident(SolveArgs a, Exchange x, ResCg io, int ln, int longest, double tol, long long max_iter, long long k0,
+               long long kend)
 {
     constexpr bool BIL = KIND == kResGeneral, CG = KIND == kResCg;
     constexpr int NW = T / 64, J = NC / T, kBins = 64;
@@ -391,7 +393,7 @@ __global__ void __launch_bounds__(T, 2)
     __shared__ double sP[HELD ? NC : 1], sQ[HELD ? NC : 1];
     __shared__ unsigned short qslot[NC];
     __shared__ __align__(16) double red[MANY ? 2 : 1][4][4 * NW];
-    __shared__ int hist[kBins], share[4], bad;
+    __shared__ int hist[kBins], share[4], bad, slow;
     const int tid = threadIdx.x;
     const int n = (int)a.n, nc = (int)a.nc;
     SolverState *S = a.state;
@@ -415,7 +417,7 @@ __global__ void __launch_bounds__(T, 2)
     if (tid == 0) {
         share[2] = own;  // slots in use
         share[3] = 0;    // rods with records
-        bad = 0;
+        bad = slow = 0;
     }
     if (tid < kBins) hist[tid] = 0;
     __syncthreads();
@@ -434,10 +436,13 @@ __global__ void __launch_bounds__(T, 2)
     // the rods with records, by descending number of them: slot t of the
     // order goes to lanes ln t ... of the workgroup (which rod a thread holds
     // does not enter any sum)
-    auto key_of = [&](int r) {
-        return kBins - 1 - min(a.pptr[r + 1] - a.pptr[r] + a.qptr[r + 1] - a.qptr[r], kBins - 1);
-    };
-    for (int r = r0 + tid; r < r1; r += T) atomicAdd(&hist[key_of(r)], 1);
+    auto records_of = [&](int r) { return a.pptr[r + 1] - a.pptr[r] + a.qptr[r + 1] - a.qptr[r]; };
+    auto key_of = [&](int r) { return kBins - 1 - min(records_of(r), kBins - 1); };
+    for (int r = r0 + tid; r < r1; r += T) {
+        const int m = records_of(r);
+        atomicAdd(&hist[kBins - 1 - min(m, kBins - 1)], 1);
+        if (m > longest) slow = 1;
+    }
     __syncthreads();
     const int slots = share[2], cap = (R2 ? 2 : 1) * (T >> lsh);
     if (tid < 64) {
@@ -453,10 +458,10 @@ __global__ void __launch_bounds__(T, 2)
     }
     __syncthreads();
     const int nrod = share[3];  // share[3] counts the velocities to send from here on
-    const bool fits = slots < NC && nrod <= cap;  // (slots: of own constraints and of every Q record)
+    const bool fits = slots < NC && nrod <= cap && !slow;  // (slots: of own constraints and of every Q record)
     if (!fits && tid == 0) {
         atomicMax(&S->need_slots, slots);
-        atomicMax(&S->need_rods, nrod);
+        atomicMax(&S->need_rods, slow ? INT_MAX : nrod);
     }
     static_assert((R2 ? 2 : 1) * T <= 2 * NC, "the order fits in half of U");
     if (fits)
@@ -963,6 +968,7 @@ __global__ void k_resident_start(SolveArgs a)
 // form, workgroups (0: no form takes the problem) and lanes per rod
 struct ResPlan {
     int form, groups, ln;
+    int longest;  // list of a rod that it takes
 };
 constexpr int kResSolo = 1536;  // constraints up to which one workgroup is as fast as several
 constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64 are needed
@@ -978,8 +984,8 @@ static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, co
 {
     SolveArgs aa = a;
     ResCg io = cg ? *cg : ResCg{nullptr, nullptr, nullptr};
-    int ln = p.ln;
-    void *args[] = {&aa, &x, &io, &ln, &tol, &max_iter, &k0, &kend};
+    int ln = p.ln, longest = p.longest;
+    void *args[] = {&aa, &x, &io, &ln, &longest, &tol, &max_iter, &k0, &kend};
     const void *f = cg ? (const void *)k_resident<T, NC, R1, R2, HELD, kResCg, MANY>
                     : a.gen ? (const void *)k_resident<T, NC, R1, R2, HELD, kResGeneral, MANY>
                             : (const void *)k_resident<T, NC, R1, R2, HELD, kResContacts, MANY>;
@@ -988,12 +994,32 @@ static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, co
     return hipLaunchKernel(f, dim3(1), dim3(T), args, 0, st);
 }
 
+// The longest list of a rod that a plan takes.  The lanes of one rod walk its
+// records alone while everybody waits: past the held ones 0.27 us a lane and
+// record, 0.40 where the normals come from LDS, and only 0.066 a record of all
+// in the loop over memory, where eight lanes of several rods share a wave.  So
+// lists decide against the chip where the first costs more than the chip
+// gains: 32 records on one lane of one workgroup 8.2 us per iteration (memory
+// 9.1), 48 12.6 (10.0); of 16 workgroups 16 6.2 (8.3), 32 10.6 (9.4); on two
+// lanes 64 10.7 (11.6), 96 15.0 (13.6), of 128 workgroups 96 17.5 (17.6);
+// with the normals from LDS 48 13.8 (14.9), 64 17.2 (16.3); on four lanes 256
+// 19.5 (24.6) and 25.9 (24.6).  (901 rods, 900 contacts of one: 243 and 81.)
+// Suspensions of up to 100,000 rods have lists of 25 to 35, at 30,000 rods and
+// phi 0.08 49 on two lanes: there the chip gains 5 to 7 us.
+static int resident_longest(const ResPlan &p)
+{
+    const bool few = p.groups > 1 && p.groups <= kFlat, held = p.groups == 1 || p.form < 3;
+    if (p.ln == 1) return few ? 26 : (p.groups == 1 ? 36 : 40);
+    if (p.ln == 2) return held ? (few ? 76 : 96) : 64;
+    return held ? INT_MAX : 240;
+}
+
 // Form, workgroups and lanes per rod of a problem; groups = 0: none takes it.
 static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered)
 {
-    ResPlan p{0, 0, 1};
+    ResPlan p{0, 0, 1, INT_MAX};
     if (nc <= 0 || nc >= (1 << 29)) return p;
-    if (h->onchip.groups > 0) return ResPlan{h->onchip.form, h->onchip.groups, h->onchip.lanes};
+    if (h->onchip.groups > 0) return ResPlan{h->onchip.form, h->onchip.groups, h->onchip.lanes, INT_MAX};
     if (n <= 512 && nc < 1024) {
         p.groups = 1;
     } else if (n <= 1024 && nc < kResSolo) {
@@ -1032,6 +1058,7 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
     const double rods = two ? (double)n : 1.15 * (double)n / p.groups + 8.0;
     while (p.ln < 4 && (2 * p.ln * rods <= T || (two && 2 * p.ln * rods <= 2 * T && 2.0 * nc > 6.0 * p.ln * n)))
         p.ln *= 2;
+    p.longest = resident_longest(p);
     return p;
 }
 
@@ -1040,7 +1067,8 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
 static bool resident_larger(ResPlan &p, int slots, int rods)
 {
     while (p.form < kResForms && kResSlots[p.form] <= slots) ++p.form;
-    return p.groups > 1 && p.form < kResForms && rods * p.ln <= kResThreads;
+    if (p.longest < INT_MAX) p.longest = resident_longest(p);
+    return p.groups > 1 && p.form < kResForms && rods <= kResThreads / p.ln;
 }
 
 static int64_t resident_words(const ResPlan &p, int64_t nc)
@@ -1050,7 +1078,7 @@ static int64_t resident_words(const ResPlan &p, int64_t nc)
 
 size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc)
 {
-    const ResPlan most{kResForms - 1, std::min(h->cus, kResMost), 1};
+    const ResPlan most{kResForms - 1, std::min(h->cus, kResMost), 1, INT_MAX};
     return n <= 1024 && nc < kResSolo ? 0 : sizeof(u64) * (size_t)resident_words(most, nc);
 }
 
@@ -1131,7 +1159,7 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
 {
     hipStream_t st = h->stream;
     *solved = false;
-    ResPlan plan{0, 0, 1};
+    ResPlan plan{0, 0, 1, INT_MAX};
     unsigned long long *words = nullptr;
     const int rc = resident_prepare(h, a, &plan, &words);
     if (rc) return rc;

@@ -174,3 +174,31 @@ def test_reserved_sizes_allocate_nothing(gpu_lib, n, phi, lengths):
             before = slv.onchip_read()["allocations"]
             call(slv)
             assert slv.onchip_read()["allocations"] == before, name
+
+
+@pytest.mark.parametrize("n,nc,hub,longest,groups", [
+    (400, 900, 36, 36, 1), (400, 900, 37, 36, 1), (1000, 1400, 400, 36, 1), (100, 900, 99, 1 << 30, 1),
+    (2000, 3000, 76, 76, 12), (2000, 3000, 77, 76, 12), (10_000, 20_000, 500, 76, 64)])
+def test_rod_with_many_contacts(gpu_lib, n, nc, hub, longest, groups):
+    """A rod in so many contacts that its lanes would hold all others up goes to
+    the two kernels; shorter lists stay on chip, whatever else the handle ran."""
+    rng = np.random.default_rng(n + hub)
+    pi = np.concatenate([np.zeros(hub, int), np.tile(np.arange(1, n // 2), nc)[:nc - hub]])
+    pj = np.concatenate([1 + rng.permutation(n - 1)[:hub], rng.integers(n // 2, n, nc - hub)])
+    order = np.argsort(pi, kind="stable")
+    pi, pj = pi[order], pj[order]
+    d, e = rng.normal(size=(n, 3)), rng.normal(size=(nc, 3))
+    d, e = d / np.linalg.norm(d, axis=1)[:, None], e / np.linalg.norm(e, axis=1)[:, None]
+    arm, q = rng.uniform(-0.5, 0.5, (nc, 2)), rng.uniform(-1.0, 0.2, nc)
+    lists = np.bincount(pi, minlength=n) + np.bincount(pj, minlength=n)
+    assert lists[0] == hub and (hub > longest or lists.max() <= longest)
+    with gpu_lib.Solver(box=10.0, diam=0.08, cutoff=0.1, eta=1.0, dt=1e-3, tol=0.0, max_iter=20) as slv:
+        args = (_t(d), 1.0, _t(pi, torch.int32), _t(pj, torch.int32), _t(e), _t(arm), _t(q))
+        slv.solve_lcp(*args)
+        ran = slv.onchip_read()
+        assert ran["groups"] == (groups if hub <= longest else 0) and ran["misfits"] == (hub > longest)
+        g, U, _ = slv.solve_lcp(*args)
+        slv.onchip_control(refuse=2)
+        g2, U2, _ = slv.solve_lcp(*args)
+    # 20 iterations of the same method
+    assert torch.linalg.norm(U - U2) <= 1e-9 * torch.linalg.norm(U2)

@@ -63,10 +63,15 @@ struct Exchange {
 };
 
 constexpr int kSlot = 32;      // words from one workgroup's sums to the next (256 bytes)
-// Above 64 workgroups their sums meet in two steps, teams of 16 and then the
-// teams: every workgroup polling 128 or 256 others takes 1.4 or 2.2 us, the
-// two steps 1.65 us for either.
-constexpr int kTeam = 16, kFlat = 64;
+// Above 128 workgroups their sums meet in two steps, teams of 16 and then the
+// teams.  Up to 128 a thread of each workgroup polls one word pair of the
+// others' sums, with 256 two after each other.  Whole iterations flat and in
+// two steps: 128 workgroups 5.2 and 5.6 us (16,000 rods, 49,000 constraints),
+// 5.5 and 5.9 (20,000, 62,000), 6.5 and 7.1 (30,000 nematic, 57,000), 6.0 and
+// 6.7 (40,000, 62,000); 256 workgroups 6.75 and 6.9 (40,000, 124,000), 6.8 and
+// 6.4 (50,000, 155,000), 10.2 and 10.4 (100,000, 312,000), 14.9 and 15.2
+// (100,000 nematic, 471,000): no difference in the mean.
+constexpr int kTeam = 16, kFlat = 128;
 
 // polls of one word before the wait is given up (about 0.3 s)
 constexpr int kSpin = 1 << 18;
@@ -971,7 +976,8 @@ struct ResPlan {
     int longest;  // list of a rod that it takes
 };
 constexpr int kResSolo = 1536;  // constraints up to which one workgroup is as fast as several
-constexpr int kResPer = 256;    // constraints per workgroup while fewer than 64 are needed
+constexpr int kResFew = 64;     // workgroups up to which a problem takes only as many as it needs,
+constexpr int kResPer = 256;    // of so many constraints
 
 // The forms: threads, slots, records held by a thread's first and second rod,
 // whether with their normals.
@@ -1008,7 +1014,7 @@ static hipError_t launch_form(hipStream_t st, const SolveArgs &a, Exchange x, co
 // phi 0.08 49 on two lanes: there the chip gains 5 to 7 us.
 static int resident_longest(const ResPlan &p)
 {
-    const bool few = p.groups > 1 && p.groups <= kFlat, held = p.groups == 1 || p.form < 3;
+    const bool few = p.groups > 1 && p.groups <= kResFew, held = p.groups == 1 || p.form < 3;
     if (p.ln == 1) return few ? 26 : (p.groups == 1 ? 36 : 40);
     if (p.ln == 2) return held ? (few ? 76 : 96) : 64;
     return held ? INT_MAX : 240;
@@ -1039,13 +1045,13 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
         auto fits = [&](int g, int form) {
             return (double)nc * reach / g <= 0.96 * kResSlots[form] && 1.15 * (double)n / g + 8.0 <= 512.0;
         };
-        int g = (int)std::min<int64_t>((nc + kResPer - 1) / kResPer, kFlat);
+        int g = (int)std::min<int64_t>((nc + kResPer - 1) / kResPer, kResFew);
         g = std::max(g, 2);
-        if (!fits(g, 0)) g = 2 * kFlat;
+        if (!fits(g, 0)) g = 2 * kResFew;
         // past 550 a workgroup the exchange between 256 costs less (50,000
         // rods, 78,000 constraints: 7.7 us per iteration with 128, 7.0; 20,000
         // and 62,000: 6.4 and 6.6)
-        if (!fits(g, 0) || (ordered && nc > 550 * 2 * kFlat)) g = most;
+        if (!fits(g, 0) || (ordered && nc > 550 * 2 * kResFew)) g = most;
         if (g > most) return p;
         while (p.form < forms && !fits(g, p.form)) ++p.form;
         if (p.form == forms) return p;

@@ -176,13 +176,26 @@ __global__ void __launch_bounds__(kKmcBlock) k_kmc_check(KmcArgs A, int *__restr
 // counting sort by bins: nbc of either class, then one per workgroup of the
 // third.  (The stable sort by these keys took 20 launches and 100 us at 400,000
 // crosslinkers, and counting two of the classes on one word another 65.)
-__global__ void __launch_bounds__(kKmcBlock)
+// A workgroup counts its crosslinkers by bin in LDS first, in a table of twice
+// its size, and goes to memory once for each bin it meets: where the bins are
+// few (a small box) or the crosslinkers gather in some, adding one by one to
+// the same words took longer than the rest of a step (times of whole steps, one
+// by one and this way: 400,000 crosslinkers in 27 cells 1,420 and 840 us, all in
+// one corner of 4,100 cells 2,650 and 535, of a box of 100,000 filaments 505
+// either way).
+constexpr int kBinBlock = 1024, kBinTable = 2 * kBinBlock, kBinTries = 8;
+
+__global__ void __launch_bounds__(kBinBlock)
     k_kmc_bins(KmcArgs A, int drop, int nbc, int *__restrict__ bin, int *__restrict__ rank, int *__restrict__ cnt)
 {
-    __shared__ int doubly;
+    __shared__ int key[kBinTable], num[kBinTable], doubly;
     if (threadIdx.x == 0) doubly = 0;
+    for (int k = threadIdx.x; k < kBinTable; k += kBinBlock) {
+        key[k] = -1;
+        num[k] = 0;
+    }
     __syncthreads();
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t c = blockIdx.x * (int64_t)kBinBlock + threadIdx.x;
     const bool live = c < A.m;
     const int s = live ? A.state[c] : -1;
     int cls = 2;
@@ -195,7 +208,7 @@ __global__ void __launch_bounds__(kKmcBlock)
         for (int a = 0; a < 3; ++a) p[a] = wrap1(A.xl[3 * c + a], A.box[a]);
         cls = 1;
     }
-    int id = 0;
+    int id = 2 * nbc + (int)blockIdx.x, at = -1, r = 0;
     if (cls < 2) {
         int k[3];
         for (int a = 0; a < 3; ++a) {
@@ -203,14 +216,24 @@ __global__ void __launch_bounds__(kKmcBlock)
             k[a] = v < 0 ? 0 : (v >= A.nc[a] ? A.nc[a] - 1 : v);
         }
         id = cls * nbc + (((k[0] * A.nc[1] + k[1]) * A.nc[2] + k[2]) >> drop);
-        rank[c] = atomicAdd(cnt + id, 1);
-    } else {
-        id = 2 * nbc + (int)blockIdx.x;
-        if (live) rank[c] = atomicAdd(&doubly, 1);
+        unsigned h = ((unsigned)id * 2654435761u) >> 21;
+        static_assert(kBinTable == 1 << 11, "11 bits of the product");
+        for (int t = 0; t < kBinTries && at < 0; ++t, h = (h + 1) % kBinTable) {
+            const int k0 = atomicCAS(&key[h], -1, id);
+            if (k0 == -1 || k0 == id) at = (int)h;
+        }
+        r = at >= 0 ? atomicAdd(&num[at], 1) : atomicAdd(cnt + id, 1);  // (no place in the table)
+    } else if (live) {
+        r = atomicAdd(&doubly, 1);
     }
-    if (live) bin[c] = id;
     __syncthreads();
+    for (int k = threadIdx.x; k < kBinTable; k += kBinBlock)
+        if (key[k] >= 0) num[k] = atomicAdd(cnt + key[k], num[k]);
     if (threadIdx.x == 0) cnt[2 * nbc + (int)blockIdx.x] = doubly;
+    __syncthreads();
+    if (!live) return;
+    bin[c] = id;
+    rank[c] = at >= 0 ? num[at] + r : r;
 }
 
 __global__ void __launch_bounds__(kKmcBlock)
@@ -697,19 +720,21 @@ int rl_kmc_step(rl_handle h, int64_t n, const double *x, const double *dir, cons
     A.ds = cells.ds;
     A.ls = cells.ls;
     const int64_t ncell = (int64_t)A.nc[0] * A.nc[1] * A.nc[2];
+    // no more bins than serve the locality: few crosslinkers in many cells
+    // spent 25 us on clearing and scanning 235,000 of them
+    const int64_t bins_most = std::min<int64_t>(1 << 17, std::max<int64_t>(4096, 4 * m));
     int drop = 0;
-    while (((ncell - 1) >> drop) >= (1 << 17)) ++drop;
+    while (((ncell - 1) >> drop) >= bins_most) ++drop;
     const int nbc = (int)((ncell - 1) >> drop) + 1;
-    const int64_t nbin = 2 * (int64_t)nbc + grid_of(m, kKmcBlock);
+    const int64_t nbin = 2 * (int64_t)nbc + grid_of(m, kBinBlock);
     int *bin = (int *)ws_get(h, kWsKmcKey, sizeof(int) * m, &werr);
     int *rank = (int *)ws_get(h, kWsKmcKeyOut, sizeof(int) * m, &werr);
     int *perm = (int *)ws_get(h, kWsKmcPerm, sizeof(int) * m, &werr);
     int *bins = (int *)ws_get(h, kWsKmcBins, sizeof(int) * nbin, &werr);
     int *off = (int *)ws_get(h, kWsKmcOff, sizeof(int) * (nbin + 1), &werr);
     if (werr) return werr;
-    RL_HIP(hipMemsetAsync(flag, 0, sizeof(int) * 4, st));
     RL_HIP(hipMemsetAsync(bins, 0, sizeof(int) * nbin, st));
-    hipLaunchKernelGGL(k_kmc_bins, dim3(grid_of(m, kKmcBlock)), dim3(kKmcBlock), 0, st, A, drop, nbc, bin, rank, bins);
+    hipLaunchKernelGGL(k_kmc_bins, dim3(grid_of(m, kBinBlock)), dim3(kBinBlock), 0, st, A, drop, nbc, bin, rank, bins);
     RL_HIP(hipGetLastError());
     rc = device_scan(h, bins, nbin, off, nullptr);
     if (rc) return rc;

@@ -974,6 +974,7 @@ __global__ void k_resident_start(SolveArgs a)
 struct ResPlan {
     int form, groups, ln;
     int longest;  // list of a rod that it takes
+    int forms;    // the first form that it does not go up to
 };
 constexpr int kResSolo = 1536;  // constraints up to which one workgroup is as fast as several
 constexpr int kResFew = 64;     // workgroups up to which a problem takes only as many as it needs,
@@ -1021,11 +1022,11 @@ static int resident_longest(const ResPlan &p)
 }
 
 // Form, workgroups and lanes per rod of a problem; groups = 0: none takes it.
-static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered)
+static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordered, bool cg)
 {
-    ResPlan p{0, 0, 1, INT_MAX};
+    ResPlan p{0, 0, 1, INT_MAX, kResForms};
     if (nc <= 0 || nc >= (1 << 29)) return p;
-    if (h->onchip.groups > 0) return ResPlan{h->onchip.form, h->onchip.groups, h->onchip.lanes, INT_MAX};
+    if (h->onchip.groups > 0) return ResPlan{h->onchip.form, h->onchip.groups, h->onchip.lanes, INT_MAX, kResForms};
     if (n <= 512 && nc < 1024) {
         p.groups = 1;
     } else if (n <= 1024 && nc < kResSolo) {
@@ -1035,12 +1036,15 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
         // slots of a workgroup: its own constraints and those that reach in
         // from outside (the fullest workgroup of the 100,000-rod nematic
         // suspensions has 1.24 times the mean), nearly all of them when the
-        // rods are in no spatial order: there the largest forms lose (100,000
-        // rods, 281,000 constraints: 23.5 us per iteration, two kernels 20.8;
-        // 50,000 and 90,000: 14.3 and 16.8).  A problem that does not fit
-        // after all is tried again with as many slots as it asks for.
+        // rods are in no spatial order: there the larger forms lose (60,000
+        // rods and 180,000 constraints 15.2 us per iteration, two kernels
+        // 17.5; 200,000 18.0 and 17.5, 240,000 20.2 and 17.9; general sets
+        // 180,000 14.9 and 17.6, 240,000 20.3 and 18.4), the conjugate
+        // gradients later (200,000 17.9 and 22.2, 240,000 20.1 and 24.0).  A
+        // problem that does not fit after all is tried again with as many
+        // slots as it asks for.
         const double reach = ordered ? 1.30 : 2.05;
-        const int forms = ordered ? kResForms : 3;
+        const int forms = p.forms = ordered ? kResForms : (cg ? 3 : 2);
         const int most = std::min(h->cus, kResMost);
         auto fits = [&](int g, int form) {
             return (double)nc * reach / g <= 0.96 * kResSlots[form] && 1.15 * (double)n / g + 8.0 <= 512.0;
@@ -1072,9 +1076,9 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
 // several-workgroup forms have the same threads.)
 static bool resident_larger(ResPlan &p, int slots, int rods)
 {
-    while (p.form < kResForms && kResSlots[p.form] <= slots) ++p.form;
+    while (p.form < p.forms && kResSlots[p.form] <= slots) ++p.form;
     if (p.longest < INT_MAX) p.longest = resident_longest(p);
-    return p.groups > 1 && p.form < kResForms && rods <= kResThreads / p.ln;
+    return p.groups > 1 && p.form < p.forms && rods <= kResThreads / p.ln;
 }
 
 static int64_t resident_words(const ResPlan &p, int64_t nc)
@@ -1084,7 +1088,7 @@ static int64_t resident_words(const ResPlan &p, int64_t nc)
 
 size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc)
 {
-    const ResPlan most{kResForms - 1, std::min(h->cus, kResMost), 1, INT_MAX};
+    const ResPlan most{kResForms - 1, std::min(h->cus, kResMost), 1, INT_MAX, kResForms};
     return n <= 1024 && nc < kResSolo ? 0 : sizeof(u64) * (size_t)resident_words(most, nc);
 }
 
@@ -1119,12 +1123,12 @@ static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResP
 // it could take for one of its own.  groups = 0: the two kernels take it
 // (sampled timing of the loop kernels needs them too, and
 // the allocation-free solve, which takes no samples, has the same bits).
-static int resident_prepare(rl_ctx *h, const SolveArgs &a, ResPlan *plan, unsigned long long **words)
+static int resident_prepare(rl_ctx *h, const SolveArgs &a, bool cg, ResPlan *plan, unsigned long long **words)
 {
     *words = nullptr;
     plan->groups = 0;
     if (h->prm.precision != RL_FP64 || h->prof_every > 0) return RL_OK;
-    *plan = resident_plan(h, a.n, a.nc, a.ordered);
+    *plan = resident_plan(h, a.n, a.nc, a.ordered, cg);
     if (plan->groups <= 1) return RL_OK;
     if (h->xchg_skip > 0) {
         --h->xchg_skip;
@@ -1165,9 +1169,9 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
 {
     hipStream_t st = h->stream;
     *solved = false;
-    ResPlan plan{0, 0, 1, INT_MAX};
+    ResPlan plan{0, 0, 1, INT_MAX, kResForms};
     unsigned long long *words = nullptr;
-    const int rc = resident_prepare(h, a, &plan, &words);
+    const int rc = resident_prepare(h, a, cg != nullptr, &plan, &words);
     if (rc) return rc;
     h->onchip_out[5] = 0;
     // the launches start from a state without a failure, which they leave so

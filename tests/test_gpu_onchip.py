@@ -202,3 +202,29 @@ def test_rod_with_many_contacts(gpu_lib, n, nc, hub, longest, groups):
         g2, U2, _ = slv.solve_lcp(*args)
     # 20 iterations of the same method
     assert torch.linalg.norm(U - U2) <= 1e-9 * torch.linalg.norm(U2)
+
+
+@pytest.mark.parametrize("nc,chip,cg_chip", [(180_000, True, True), (200_000, False, True), (260_000, False, False)])
+def test_unordered_lists_leave_the_chip_where_memory_is_faster(gpu_lib, nc, chip, cg_chip):
+    n, rng = 60_000, np.random.default_rng(2)
+    a, b = rng.integers(0, n, nc), rng.integers(0, n - 1, nc)
+    b += b >= a
+    pi, pj = np.minimum(a, b), np.maximum(a, b)
+    order = np.argsort(pi, kind="stable")
+    pi, pj = pi[order], pj[order]
+    d, e = rng.normal(size=(n, 3)), rng.normal(size=(nc, 3))
+    d, e = d / np.linalg.norm(d, axis=1)[:, None], e / np.linalg.norm(e, axis=1)[:, None]
+    args = (_t(d), 1.0, _t(pi, torch.int32), _t(pj, torch.int32), _t(e), _t(rng.uniform(-0.5, 0.5, (nc, 2))),
+            _t(rng.uniform(-1.0, 0.2, nc)))
+    Ub = _t(rng.normal(size=(n, 6)))
+    with gpu_lib.Solver(box=10.0, diam=0.08, cutoff=0.1, eta=1.0, dt=1e-3, tol=0.0, max_iter=20) as slv:
+        g, U, _ = slv.solve_lcp(*args)
+        assert (slv.onchip_read()["groups"] > 0) == chip
+        bars = slv.solve_lcp_adjoint(*args, g, Ub, cg_tol=1e-300)[:5]
+        assert (slv.onchip_read()["groups"] > 0) == cg_chip
+        slv.onchip_control(refuse=2)
+        _, U2, _ = slv.solve_lcp(*args)
+        bars2 = slv.solve_lcp_adjoint(*args, g, Ub, cg_tol=1e-300)[:5]
+    # 20 iterations of the same methods
+    for a, b in zip((U, *bars), (U2, *bars2)):
+        assert torch.linalg.norm(a - b) <= 1e-9 * torch.linalg.norm(b)

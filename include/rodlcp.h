@@ -169,7 +169,21 @@ int rl_apply_M(rl_handle h, int64_t n, const double *dir, const double *len, dou
  * constrainedeom_euler).  gamma is the start on entry (negative entries are
  * clipped to 0; zeros = cold start) and the solution on exit.  F may be NULL
  * (zero external load).  *info (host) receives iterations, residual and
- * status.  Returns info->status (>= 0) or an error.  Synchronises. */
+ * status.  U may be F's array.  Returns info->status (>= 0) or an error.
+ * Synchronises.
+ *
+ * Repeatability.  FP64 problems of up to about 500,000 constraints between
+ * rods in the order of a step, and about 180,000 in any order, are solved on
+ * chip in one launch (rl_onchip_control below), others by a loop of two
+ * kernels per iteration.  Which loop runs depends on the problem and the
+ * device alone, and every sum has a fixed order, so the same call gives the
+ * same bits whatever the handle did before.  The one exception: on chip the
+ * workgroups wait for each other, and where other work (of another stream or
+ * process) keeps compute units from them for about 0.3 s a wait runs out.
+ * That solve then starts again over memory, and the handle's next 64 solves
+ * that several workgroups would take stay there: to the same tolerance, with
+ * other last bits and another iteration count.  rl_onchip_read counts these.
+ * "Bitwise" below is meant with this exception. */
 int rl_solve_lcp(rl_handle h, int64_t n, const double *dir, const double *len, double len0, int64_t nc,
                  const int32_t *pi, const int32_t *pj, const double *e, const double *arm, const double *q,
                  const double *F, double *gamma, double *U, rl_solve_info *info);
@@ -280,7 +294,10 @@ int rl_assemble_walls(rl_handle h, int64_t n, const double *x, const double *dir
  * that sampling needs, as in rl_solve_lcp.
  * Workspace: 152 bytes per constraint and 12 bytes per rod (36 with per-rod
  * lengths) plus a few KB (e.g. 100,000 rods with 468,687 constraints take
- * 73 MB); a larger problem returns RL_ERR_ARG with nothing enqueued.
+ * 73 MB); a larger problem returns RL_ERR_ARG with nothing enqueued.  A solve
+ * on chip by several workgroups takes up to 12.9 MB and 16 bytes per
+ * constraint more for its exchange, which the array always has room for at
+ * the sizes that go there.
  * Every call on one GPU uses that GPU's one array: calls that overlap in time
  * on the same GPU (other threads, other handles, other streams) race and must
  * be serialised by the caller.  Synchronises, like rl_solve_lcp. */
@@ -400,7 +417,7 @@ int rl_batch_tuning(rl_handle h, int rod_block, int con_block, int *chosen);
  * from 0, which gives the minimum-norm lambda when Mc_AA is singular, and
  * stops when ||r||_2 <= cg_tol * ||D_A^T M U_bar||_2 (cg_tol <= 0: 1e-10)
  * or after prm.max_iter iterations.  All arithmetic is FP64 and every sum
- * runs in a fixed order, so results are bitwise repeatable. */
+ * runs in a fixed order, so results are bitwise repeatable (see rl_solve_lcp). */
 typedef struct {
     int64_t cg_iterations;   /* CG iterations (products Mc_AA p) */
     double cg_residual;      /* ||r||_2 / ||b||_2 at exit (0 when b = 0) */
@@ -449,7 +466,9 @@ int rl_solve_lcp_adjoint(rl_handle h, int64_t n, const double *dir, const double
  * gamma_tape (may be NULL) is the tape rl_step recorded for the same
  * (x, quat, len) with tape_len its count.  The forward solve then starts
  * from it and stops at once.  Without it, the solve runs from gamma = 0 to
- * the same bitwise result.  RL_ERR_ARG if tape_len does not match.
+ * the same bitwise result (see rl_solve_lcp: the step and its adjoint take the
+ * same loop, unless a wait ran out in one of them or only one was sampled by
+ * rl_profile_enable).  RL_ERR_ARG if tape_len does not match.
  * Returns the CG status (>= 0; a forward solve that did not converge is
  * reported in info->solve_status), or an error.  Synchronises. */
 int rl_step_adjoint(rl_handle h, int64_t n, const double *x, const double *quat, const double *len, double len0,

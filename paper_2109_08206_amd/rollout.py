@@ -11,7 +11,9 @@
     ``rl_step_adjoint`` step by step in reverse.  A replayed tape starts each
     of those solves at its own solution, so they stop at once.  The results
     are bitwise those of cold solves: every sum runs in a fixed order, and
-    the recomputed states equal the forward ones.
+    the recomputed states equal the forward ones (as long as forward and
+    backward are sampled alike and no wait between a solve's workgroups runs
+    out for other work on the device, see rl_solve_lcp in rodlcp.h).
 The output is the unwrapped centres x0 + h sum_t U_t (plus theta_T), which
 ``rl_step`` advances beside the wrapped ones.
 Wrapping into the periodic box shifts by whole box lengths and does not

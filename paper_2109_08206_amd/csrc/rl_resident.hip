@@ -24,12 +24,10 @@
 // part) and no clearing between iterations.  A workgroup sends its sums after
 // it has read the velocities of the same product and writes the next
 // velocities after it has read everybody's sums, so no word is overwritten
-// unread; the sums alternate between two buffers for the same reason.  A round
-// of the sums takes 1.05 us between up to 64 workgroups and 1.4 us between
-// 128, with velocities in front of it 1.9 and 2.5 us; a grid
-// barrier with device-scope fences took 17 us and more.  Every wait is
-// bounded: past the bound (or where the problem turns out not to fit) all
-// workgroups leave without a result, and the caller runs the two kernels.
+// unread; the sums alternate between two buffers for the same reason.  Every
+// wait is bounded: past the bound (or where the problem turns out not to fit)
+// all workgroups leave without a result, and the caller runs the two kernels.
+// (A grid barrier with device-scope fences took 17 us and more.)
 //
 // What bounds it: the exchanges, and the instruction issue of a compute unit
 // and the dependent chain between the barriers, not memory.  Hence few waves
@@ -37,7 +35,16 @@
 // these took 3,400 clocks of an iteration whatever the size), and rods dealt
 // to the threads in descending order of their number of records (a wave takes
 // as long as its longest list, and a random 64 rods nearly always hold one
-// two or three times the average).
+// two or three times the average).  Where an iteration of a whole step goes, us,
+// by a clock in one wave of each workgroup (mean over the workgroups; the
+// waits hold the others' delay as well):
+//   rods, constraints, workgroups   gamma'  rods  velocities  sums inside, between
+//     2,000    3,108   13   4.0      0.5    0.6      1.2         0.3   1.5
+//    10,000   31,026   64   5.0      0.5    0.7      1.6         0.2   1.9
+//    20,000   62,479  128   5.3      0.5    0.7      1.7         0.2   2.2
+//    50,000  155,397  256   6.7      0.5    0.7      2.4         0.3   2.9
+//   100,000  311,923  256  10.7      0.5    2.8      4.2         0.3   2.9
+//   100,000  470,657  256  15.3      0.6    6.0      4.2         0.8   3.8
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -1034,15 +1041,19 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
         p.groups = 1;
     } else {
         // slots of a workgroup: its own constraints and those that reach in
-        // from outside (the fullest workgroup of the 100,000-rod nematic
-        // suspensions has 1.24 times the mean), nearly all of them when the
-        // rods are in no spatial order: there the larger forms lose (60,000
-        // rods and 180,000 constraints 15.2 us per iteration, two kernels
-        // 17.5; 200,000 18.0 and 17.5, 240,000 20.2 and 17.9; general sets
-        // 180,000 14.9 and 17.6, 240,000 20.3 and 18.4), the conjugate
-        // gradients later (200,000 17.9 and 22.2, 240,000 20.1 and 24.0).  A
-        // problem that does not fit after all is tried again with as many
-        // slots as it asks for.
+        // from outside, nearly all of them when the rods are in no spatial
+        // order.  In a step's order the fullest workgroup of suspensions asks
+        // for 1.33 (100,000 nematic rods, phi 0.03) to 1.45 times the mean of
+        // its own at 390 rods a workgroup, 1.5 to 1.6 at 200, 1.8 at 80.  The
+        // estimate is the lower end: a refused launch costs 65 to 80 us of the
+        // solve, a form larger than needed 0.4 to 1.3 us of each iteration
+        // (100,000 nematic, 281,000 constraints: 8.5 with 1,536 slots, 9.5 with
+        // 2,048).  In no order the larger forms lose (60,000
+        // rods and 180,000 constraints 15.2 us per iteration, two kernels 17.5;
+        // 200,000 18.0 and 17.5, 240,000 20.2 and 17.9; general sets 180,000
+        // 14.9 and 17.6, 240,000 20.3 and 18.4), the conjugate gradients later
+        // (200,000 17.9 and 22.2, 240,000 20.1 and 24.0).  A problem that does
+        // not fit after all is tried again with as many slots as it asks for.
         const double reach = ordered ? 1.30 : 2.05;
         const int forms = p.forms = ordered ? kResForms : (cg ? 3 : 2);
         const int most = std::min(h->cus, kResMost);
@@ -1052,9 +1063,10 @@ static ResPlan resident_plan(const rl_ctx *h, int64_t n, int64_t nc, bool ordere
         int g = (int)std::min<int64_t>((nc + kResPer - 1) / kResPer, kResFew);
         g = std::max(g, 2);
         if (!fits(g, 0)) g = 2 * kResFew;
-        // past 550 a workgroup the exchange between 256 costs less (50,000
-        // rods, 78,000 constraints: 7.7 us per iteration with 128, 7.0; 20,000
-        // and 62,000: 6.4 and 6.6)
+        // past 550 a workgroup 256 cost less, about (50,000 rods, 77,000
+        // constraints: 6.3 us per iteration with 128, 5.9; 20,000 and 62,000:
+        // 5.2 and 5.6; but 24,000 and 82,000, where 128 leave room for two
+        // lanes a rod: 5.4 and 6.0)
         if (!fits(g, 0) || (ordered && nc > 550 * 2 * kResFew)) g = most;
         if (g > most) return p;
         while (p.form < forms && !fits(g, p.form)) ++p.form;
@@ -1092,8 +1104,9 @@ size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc)
     return n <= 1024 && nc < kResSolo ? 0 : sizeof(u64) * (size_t)resident_words(most, nc);
 }
 
-// iterations of one launch of a solve on chip (under 20 ms), and the numbers
-// that its exchanges may take
+// iterations of one launch of a solve on chip (8 ms at 4 us each, 31 ms at the 15
+// of 100,000 rods and 469,000 constraints, more with long lists), and the
+// numbers that its exchanges may take
 constexpr long long kResChunk = 2048, kResNumbers = kResChunk + 8;
 
 static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, const ResCg *cg,

@@ -601,11 +601,11 @@ int rl_profile_read(rl_handle h, double *out);
  *     as ever;
  *   refuse: RL_ONCHIP_NO_MEMORY, _NO_ROOM: as if there were no memory for the
  *     exchange, or no room for the workgroups on the device;
- *   patience >= 0: polls before a wait between workgroups runs out, from the
- *     solve's exchange number `patient` + 1 on (each launch of up to 2,048
- *     iterations has 2,056 numbers: 1 finds out whether the problem fits, then
- *     come one per product, after one for the conjugate gradients' start, and
- *     one that ends a solve of contacts or a general set).
+ *   patient >= 0: waits between workgroups run out at once from the solve's
+ *     exchange number `patient` + 1 on (each launch of up to 2,048 iterations
+ *     has 2,056 numbers: 1 finds out whether the problem fits, then come one
+ *     per product, after one for the conjugate gradients' start, and one that
+ *     ends a solve of contacts or a general set).
  * rl_onchip_read writes to out[8] (host): solves on chip, launches refused
  * because the problem did not fit, waits that ran out, solves without the
  * memory or the room, and form, workgroups and lanes of the last launch (0
@@ -615,7 +615,7 @@ int rl_profile_read(rl_handle h, double *out);
 #define RL_ONCHIP_NO_ROOM 2
 typedef struct {
     int32_t form, groups, lanes, refuse;
-    int64_t patience, patient;
+    int64_t patient;
 } rl_onchip;
 int rl_onchip_control(rl_handle h, const rl_onchip *c);
 int rl_onchip_read(rl_handle h, int64_t *out);

@@ -101,7 +101,7 @@ EV_NONE, EV_BIND, EV_UNBIND, EV_CROSS, EV_RELEASE = 0, 1, 2, 3, 4
 
 class OnChip(C.Structure):
     _fields_ = [("form", C.c_int32), ("groups", C.c_int32), ("lanes", C.c_int32), ("refuse", C.c_int32),
-                ("patience", C.c_int64), ("patient", C.c_int64)]
+                ("patient", C.c_int64)]
 
 
 class AdjointInfo(C.Structure):
@@ -294,10 +294,10 @@ class Solver:
         self._check(self.lib.rl_profile_read(self._h, out), "rl_profile_read")
         return {"rod_ms": out[0], "rod_launches": int(out[1]), "con_ms": out[2], "con_launches": int(out[3])}
 
-    def onchip_control(self, form=0, groups=0, lanes=1, refuse=0, patience=-1, patient=0):
+    def onchip_control(self, form=0, groups=0, lanes=1, refuse=0, patient=-1):
         """For tests and measurement: form, workgroups and lanes of solves on
         chip, or what they have to do without (no arguments: the rule)."""
-        c = OnChip(form, groups, lanes, refuse, patience, patient)
+        c = OnChip(form, groups, lanes, refuse, patient)
         self._check(self.lib.rl_onchip_control(self._h, C.byref(c)), "rl_onchip_control")
 
     def onchip_read(self):

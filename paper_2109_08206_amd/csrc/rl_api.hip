@@ -807,15 +807,14 @@ int rl_profile_read(rl_handle h, double *out)
 int rl_onchip_control(rl_handle h, const rl_onchip *c)
 {
     RL_CHECK_HANDLE(h);
-    const rl_onchip rule{0, 0, 0, 0, -1, 0};
+    const rl_onchip rule{0, 0, 0, 0, -1};
     if (!c) c = &rule;
     RL_REQUIRE(c->groups >= 0 && c->groups <= std::min(h->cus, kResMost), "rl_onchip_control: bad groups");
     RL_REQUIRE(c->groups == 0 || ((c->lanes == 1 || c->lanes == 2 || c->lanes == 4) && c->form >= 0 &&
                                   c->form < (c->groups == 1 ? 2 : kResForms)),
                "rl_onchip_control: bad form or lanes");
     RL_REQUIRE(c->refuse >= 0 && c->refuse <= RL_ONCHIP_NO_ROOM, "rl_onchip_control: bad refuse");
-    RL_REQUIRE(c->patience <= INT32_MAX && c->patient >= 0 && c->patient <= INT32_MAX,
-               "rl_onchip_control: bad patience");
+    RL_REQUIRE(c->patient <= INT32_MAX, "rl_onchip_control: bad patient");
     h->onchip = *c;
     return RL_OK;
 }

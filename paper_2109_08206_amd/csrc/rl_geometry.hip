@@ -1044,12 +1044,11 @@ static int pairs_core(rl_ctx *h, int64_t n, const double *x, const double *dir, 
         const int split = (int)std::max<int64_t>(
             1, std::min<int64_t>(((ns / 2 + 1) * rparts + kEmitWaves - 1) / kEmitWaves, 8192 / ncell));
         // The workspace follows the pairs there are, not the room that the
-        // caller has for them: at first as many as it holds, or 32 per rod (the
-        // densest suspensions have 12); a search that finds more runs again.
-        const int64_t room = std::max<int64_t>(capacity, 0);
-        int64_t ecap = internal ? room
-                                : std::min(room, std::max<int64_t>((int64_t)(h->cap[kWsEmit] / kEmitBytes),
-                                                                   32 * n + 4096));
+        // caller has for them: at first as many as it holds, in a new handle 32
+        // per rod (the densest suspensions have 12); a search that finds more
+        // runs again.
+        const int64_t room = std::max<int64_t>(capacity, 0), holds = (int64_t)(h->cap[kWsEmit] / kEmitBytes);
+        int64_t ecap = internal ? room : std::min(room, holds > 0 ? holds : 32 * n + 4096);
         for (;; ecap = total) {
             const int64_t eb = std::max<int64_t>(ecap, 1);
             ekeys = (unsigned long long *)ws_get(h, kWsEmit, (size_t)kEmitBytes * eb, &werr);

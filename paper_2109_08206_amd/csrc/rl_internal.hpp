@@ -176,7 +176,7 @@ struct rl_ctx {
     size_t xchg_cap = 0;
     unsigned xchg_num = 0;
     int xchg_skip = 0;
-    rl_onchip onchip{0, 0, 0, 0, -1, 0};  // groups 0, patience below 0: the rule, the usual bound
+    rl_onchip onchip{0, 0, 0, 0, -1};     // groups 0, patient below 0: the rule, the usual bound
     int64_t onchip_out[8] = {};           // see rl_onchip_read
     // grow-only workspace slots
     static constexpr int kSlots = 128;

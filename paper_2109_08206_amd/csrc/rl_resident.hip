@@ -64,9 +64,7 @@ struct Exchange {
                     // the workgroups, and of the groups of kTeam workgroups
     unsigned base;  // numbers base + 1, ... belong to this launch
     int *fail;      // set when a wait ran out (1) or the problem does not fit (2)
-    // what the count of polls starts from at numbers above base + patient
-    int spent;
-    unsigned patient;
+    unsigned until;  // waits for numbers above it run out at the first poll
 };
 
 constexpr int kSlot = 32;      // words from one workgroup's sums to the next (256 bytes)
@@ -118,10 +116,7 @@ __device__ __forceinline__ bool give_up(int spin, int *fail, int *bad)
 }
 
 // the count of polls of a wait for number `num` before the first
-__device__ __forceinline__ int spent(const Exchange &x, unsigned num)
-{
-    return num - x.base > x.patient ? x.spent : 0;
-}
+__device__ __forceinline__ int spent(const Exchange &x, unsigned num) { return num > x.until ? kSpin : 0; }
 
 // the two words of a number, polled until both carry `num`
 __device__ __forceinline__ double pair_wait(const u64 *p, const Exchange &x, unsigned num, int *bad)
@@ -1113,12 +1108,12 @@ static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResP
                                   const rl_onchip &ctl, unsigned long long *words, unsigned base, double tol,
                                   long long max_iter, long long k0, long long kend)
 {
-    const long long patient = ctl.patient - k0 / kResChunk * kResNumbers;  // of this launch's exchanges
+    // (of this launch's exchanges)
+    const long long patient = std::max<long long>(0, ctl.patient - k0 / kResChunk * kResNumbers);
     if (ctl.refuse == RL_ONCHIP_NO_ROOM) return hipErrorCooperativeLaunchTooLarge;
     u64 *at = words ? words + 2 * (int64_t)p.groups * kResSlots[p.form] : nullptr;
     const Exchange x{words, at, words ? at + 2 * a.nc : nullptr, base, &a.state->fail,
-                     ctl.patience < 0 ? 0 : kSpin - (int)std::min<int64_t>(ctl.patience, kSpin),
-                     (unsigned)std::max(0ll, patient)};
+                     ctl.patient < 0 ? UINT_MAX : (unsigned)std::min<long long>(base + patient, UINT_MAX)};
     if (p.groups == 1) {
         if (p.form == 0) return launch_form<256, 1024, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);
         return launch_form<512, 2048, 8, 4, true, false>(st, a, x, cg, p, tol, max_iter, k0, kend);

@@ -126,7 +126,7 @@ def test_wait_that_runs_out(gpu_lib, phi, after, general):
         # exchanges: whether it fits, the start's two products, the iterations, the end
         last = 4 + info.iterations
         assert info.iterations == 3000 if after == 2056 + 5 else info.iterations <= 2048
-        slv.onchip_control(form=2, groups=64, lanes=2, patience=0, patient=last - 1 if after == "last" else after)
+        slv.onchip_control(form=2, groups=64, lanes=2, patient=last - 1 if after == "last" else after)
         g1, U1, i1 = solve(slv)
         ran = slv.onchip_read()
     assert ran["timeouts"] == 1 and ran["solves"] == 1

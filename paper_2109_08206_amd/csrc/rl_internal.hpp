@@ -52,8 +52,6 @@ struct SolverState {
     // the most slots and rods with records (0 in a state without a failure;
     // INT_MAX rods where a list is too long for it)
     int need_slots, need_rods;
-    // base + 1 of the last launch in which a workgroup left its results
-    unsigned left;
 };
 
 // Per-rod mobility: a_par, a_perp (translation along / normal to the axis),

@@ -61,13 +61,19 @@ struct Exchange {
                     // sends, in its own order (consecutive lanes, consecutive words)
     u64 *at;        // [nc][2] where in it u_P and -u_Q of a constraint are found
     u64 *tot;       // [2][2][kResMost][kSlot] the four sums, by parity of the number: of
-                    // the workgroups, and of the groups of kTeam workgroups
+                    // the workgroups, and of the groups of kTeam workgroups; behind it
+                    // [kResMost] the number at which a workgroup left its results
     unsigned base;  // numbers base + 1, ... belong to this launch
     int *fail;      // set when a wait ran out (1) or the problem does not fit (2)
     unsigned until;  // waits for numbers above it run out at the first poll
 };
 
 constexpr int kSlot = 32;      // words from one workgroup's sums to the next (256 bytes)
+constexpr int kLeft = 4 * kResMost * kSlot;
+// iterations of one launch of a solve (8 ms at 4 us each, 31 ms at the 15 of
+// 100,000 rods and 469,000 constraints, more with long lists), and the numbers
+// that its exchanges may take
+constexpr long long kResChunk = 2048, kResNumbers = kResChunk + 8;
 // Above 128 workgroups their sums meet in two steps, teams of 16 and then the
 // teams.  Up to 128 a thread of each workgroup polls one word pair of the
 // others' sums, with 256 two after each other.  Whole iterations flat and in
@@ -617,9 +623,6 @@ __global__ void __launch_bounds__(T, 2)
                 g[j] = st.y;
                 q[j] = a.qv[c];
                 if (BIL) cm[j] = a.cmpv[c];
-                // the start, for when a wait runs out after somebody's results
-                // are out (the two kernels' product is not in use here)
-                if (MANY && k0 == 0 && s < own) a.uP[c] = st.x;
             }
             if (MANY) {
                 const int r = a.pp[c].y;  // the Q rod (below 0: a fixed body)
@@ -643,6 +646,12 @@ __global__ void __launch_bounds__(T, 2)
         }
         G[s] = 0.0;
     }
+    // the start, for when a wait runs out after somebody's results are out (the
+    // two kernels' product is not in use here)
+    if (MANY && !CG && k0 == 0)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (tid + j * T < own) a.uP[c0 + tid + j * T] = gam[j];
     ResRod<R1, HELD> rod1;
     ResRod<R2 ? R2 : kGroup, HELD> rod2;
     __syncthreads();
@@ -933,7 +942,7 @@ __global__ void __launch_bounds__(T, 2)
     if (MANY) {
         __syncthreads();
         if (bad) return;  // the flag is set
-        if (tid == 0) __hip_atomic_store(&S->left, x.base + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) x.tot[kLeft + blockIdx.x] = num;  // (all on one word took 10 us)
     }
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -958,10 +967,12 @@ __global__ void __launch_bounds__(T, 2)
 }
 
 // The start of a solve of contacts or a general set back from where the first
-// launch left it.
-__global__ void k_resident_start(SolveArgs a)
+// launch left it, if results are out: always after a second launch (left
+// null), else if a workgroup says so.
+__global__ void __launch_bounds__(kResMost) k_resident_start(SolveArgs a, const u64 *left, unsigned base)
 {
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (left && !__syncthreads_or(left[threadIdx.x] - base - 1 < (u64)kResNumbers)) return;
+    const int64_t c = blockIdx.x * (int64_t)kResMost + threadIdx.x;
     if (c >= a.nc) return;
     const double2 v = make_double2(a.uP[c], 0.0);
     const int k = a.qpos[c];
@@ -1090,7 +1101,7 @@ static bool resident_larger(ResPlan &p, int slots, int rods)
 
 static int64_t resident_words(const ResPlan &p, int64_t nc)
 {
-    return p.groups > 1 ? 2 * (int64_t)p.groups * kResSlots[kResForms - 1] + 2 * nc + 4 * (int64_t)kResMost * kSlot : 0;
+    return p.groups > 1 ? 2 * (int64_t)p.groups * kResSlots[kResForms - 1] + 2 * nc + kLeft + kResMost : 0;
 }
 
 size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc)
@@ -1098,11 +1109,6 @@ size_t resident_bytes(const rl_ctx *h, int64_t n, int64_t nc)
     const ResPlan most{kResForms - 1, std::min(h->cus, kResMost), 1, INT_MAX, kResForms};
     return n <= 1024 && nc < kResSolo ? 0 : sizeof(u64) * (size_t)resident_words(most, nc);
 }
-
-// iterations of one launch of a solve on chip (8 ms at 4 us each, 31 ms at the 15
-// of 100,000 rods and 469,000 constraints, more with long lists), and the
-// numbers that its exchanges may take
-constexpr long long kResChunk = 2048, kResNumbers = kResChunk + 8;
 
 static hipError_t launch_resident(hipStream_t st, const SolveArgs &a, const ResPlan &p, const ResCg *cg,
                                   const rl_onchip &ctl, unsigned long long *words, unsigned base, double tol,
@@ -1158,16 +1164,12 @@ static int resident_prepare(rl_ctx *h, const SolveArgs &a, bool cg, ResPlan *pla
         return RL_OK;
     }
     // a new buffer, the scratch array (anybody's) or numbers about to run out
-    // (the state, which holds one of them, begins anew with them)
-    const bool arena = h->arena_on, over = h->xchg_num > 0xf0000000u;
-    if (arena || h->xchg_buf != *words || h->xchg_cap != h->cap[kWsXchg] || over) {
+    const bool arena = h->arena_on;
+    if (arena || h->xchg_buf != *words || h->xchg_cap != h->cap[kWsXchg] || h->xchg_num > 0xf0000000u) {
         RL_HIP(hipMemsetAsync(*words, 0, arena ? bytes : h->cap[kWsXchg], h->stream));
         h->xchg_buf = arena ? nullptr : *words;
         h->xchg_cap = arena ? 0 : h->cap[kWsXchg];
-        if (over) {
-            h->xchg_num = 0;
-            h->state_ready = false;
-        }
+        h->xchg_num = 0;
     }
     return RL_OK;
 }
@@ -1226,9 +1228,11 @@ int resident_run(rl_ctx *h, const SolveArgs &a, const ResCg *cg, double tol, con
         // the last bits of its solution, depends on the problem alone.
         *solved = false;
         const int slots = h->state_host->need_slots, rods = h->state_host->need_rods;
-        // (results leave a workgroup after everybody's first launch has begun)
-        if (fail == 1 && !cg && (k0 > 0 || h->state_host->left == base + 1)) {
-            hipLaunchKernelGGL(k_resident_start, dim3((unsigned)((a.nc + 255) / 256)), dim3(256), 0, st, a);
+        // (no workgroup's results are out before all have put their start away)
+        if (fail == 1 && !cg) {
+            const u64 *left = words + 2 * (int64_t)plan.groups * kResSlots[plan.form] + 2 * a.nc + kLeft;
+            hipLaunchKernelGGL(k_resident_start, dim3((unsigned)((a.nc + kResMost - 1) / kResMost)), dim3(kResMost), 0,
+                               st, a, k0 > 0 ? nullptr : left, base);
             RL_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, st, h->state, tol, (long long)h->prm.max_iter);

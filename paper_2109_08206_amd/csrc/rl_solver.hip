@@ -403,7 +403,6 @@ __global__ void k_state_init(SolverState *st, double tol, long long max_iter)
         st->refresh = 0;
         st->fail = 0;
         st->need_slots = st->need_rods = 0;
-        st->left = 0;
     }
 }
 

@@ -127,7 +127,9 @@ int rl_set_stream(rl_handle h, void *hip_stream);
  * so that later FP64 calls of that size to rl_step without links and walls
  * (warm-started, with the stress or with noise as well), rl_solve_lcp and
  * rl_build_pairs (of a capacity up to max_pairs) allocate nothing, as long as
- * the search's cells are no more than max_rods or 4,096. */
+ * the search's cells are no more than max_rods or 4,096.  (Where memory runs
+ * short, what only warm starts, noise and the exchange of solves on chip take
+ * is left to the calls.) */
 int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs);
 const char *rl_status_str(int status);
 const char *rl_last_error(void);

@@ -438,15 +438,20 @@ int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs)
         {kWsPairCnt, sizeof(int) * (4 + bins + 2 * n)}, {kWsCellStart, sizeof(int) * (bins + 1)},
         {kWsCellCur, sizeof(int) * n},     {kWsCellKey, sizeof(int) * n},      {kWsSortIdx, sizeof(int) * n},
         {kWsScan, sizeof(int64_t) * 2},    {kWsLenMax, sizeof(int64_t)},       {kWsScanTmp, scan},
-        {kWsSortTmp, sort},                {kWsFtot, sizeof(double) * 6 * n},
         {kWsStepPhi, sizeof(double) * nc}, {kWsStepE, sizeof(double) * 3 * nc}, {kWsStepArm, sizeof(double) * 2 * nc},
         {kWsStepGamma, sizeof(double) * nc}, {kWsStepU, sizeof(double) * 6 * n}, {kWsQv, sizeof(double) * nc},
         {kWsUP, sizeof(double) * nc},      {kWsUQ, sizeof(double) * nc},
         {kWsPP, sizeof(int) * 2 * nc},     {kWsGeo, sizeof(double) * 4 * nc}, {kWsGeo2, sizeof(double) * 2 * nc},  {kWsSt, sizeof(double) * 2 * nc},
         {kWsAlpha, sizeof(double) * 2},    {kWsQpos, sizeof(int) * nc},        {kWsQgeo, sizeof(double) * 4 * nc},
-        {kWsStq, sizeof(double) * 2 * nc}, {kWsXchg, resident_bytes(h, n, nc)},
+        {kWsStq, sizeof(double) * 2 * nc},
+    };
+    // what only some steps take, and the exchange, which a solve does without:
+    // sizes that leave no room for these are still good for the rest
+    const size_t more[][2] = {
+        {kWsXchg, resident_bytes(h, n, nc)}, {kWsSortTmp, sort}, {kWsFtot, sizeof(double) * 6 * n},
+        {kWsStress, kStressBytes},
         {kWsWarmKeys, sizeof(int64_t) * nc}, {kWsWarmKeysNew, sizeof(int64_t) * nc},
-        {kWsWarmGam, sizeof(double) * nc}, {kWsWarmGamNew, sizeof(double) * nc}, {kWsStress, kStressBytes},
+        {kWsWarmGam, sizeof(double) * nc}, {kWsWarmGamNew, sizeof(double) * nc},
     };
     for (auto &e : sz) {
         if (e[1] > 0) ws_get(h, (int)e[0], e[1], &err);
@@ -455,6 +460,9 @@ int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs)
     // a step's search makes use of all that the lists of pairs hold
     ws_get(h, kWsEmit, kEmitBytes * (h->cap[kWsStepPi] / sizeof(int32_t)), &err);
     if (err) return err;
+    for (auto &e : more)
+        if (e[1] > 0) ws_get(h, (int)e[0], e[1], &err);
+    err = 0;
     ws_get_host(h, kStressBytes, &err);
     return err;
 }

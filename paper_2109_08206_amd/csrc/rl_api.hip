@@ -460,8 +460,11 @@ int rl_reserve(rl_handle h, int64_t max_rods, int64_t max_pairs)
     // a step's search makes use of all that the lists of pairs hold
     ws_get(h, kWsEmit, kEmitBytes * (h->cap[kWsStepPi] / sizeof(int32_t)), &err);
     if (err) return err;
-    for (auto &e : more)
+    for (auto &e : more) {
+        // (the forces kept for the next warm step stay where they are)
+        if (h->warm_count >= 0 && (e[0] == kWsWarmKeys || e[0] == kWsWarmGam)) continue;
         if (e[1] > 0) ws_get(h, (int)e[0], e[1], &err);
+    }
     err = 0;
     ws_get_host(h, kStressBytes, &err);
     return err;

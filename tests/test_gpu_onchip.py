@@ -228,3 +228,16 @@ def test_unordered_lists_leave_the_chip_where_memory_is_faster(gpu_lib, nc, chip
     # 20 iterations of the same methods
     for a, b in zip((U, *bars), (U2, *bars2)):
         assert torch.linalg.norm(a - b) <= 1e-9 * torch.linalg.norm(b)
+
+
+def test_reserve_between_warm_steps(gpu_lib):
+    """rl_reserve leaves the forces of the last step where the next one finds
+    them: repeated with the same loads it stops at once."""
+    s = rodsynth.make_system(700, seed=6, phi=0.02)
+    F = _t(s.force)
+    with gpu_lib.Solver(box=s.box, diam=s.diam, cutoff=s.cutoff, eta=s.eta, dt=s.dt, tol=1e-8) as slv:
+        x, quat = _t(s.x), _t(s.quat)
+        _, first, n_pairs = slv.step(x.clone(), quat.clone(), 1.0, F=F, warm_start=True)
+        slv.reserve(70_000, 100 * n_pairs)
+        _, again, _ = slv.step(x.clone(), quat.clone(), 1.0, F=F, warm_start=True)
+    assert first.iterations > 10 and again.iterations == 0
